@@ -386,7 +386,7 @@ def user_halfedges_bench(plans, stream, reps=100):
     t0 = time.perf_counter()
     oracle.user_halfedges(T)
     cpu_s = time.perf_counter() - t0
-    return {"kernels": ["k_he_count", "k_he_offsets", "k_he_scatter", "k_he_solve", "k_he_fallback"],
+    return {"kernels": ["k_he_count", "k_he_offsets", "k_he_scatter", "k_he_solve"],
             "call_us": round(us, 2),
             "halfedges_per_s": round(3 * n_tri / (us * 1e-6), 1), "workspace_bytes": int(ws_n),
             "equals_alg2_he": same,

@@ -28,12 +28,17 @@
 //                  only the buckets that overflowed read
 //   k_he_solve     one workgroup per bucket: an LDS hash table of the
 //                  bucket's keys (compare-and-swap on the key, atomic min of
-//                  each direction's first index), then each entry looks its
-//                  key up and writes its twin
-//   k_he_fallback  one workgroup that returns at once unless a bucket held
-//                  more distinct keys than its LDS table (only inputs built
-//                  against the hash can): then it redoes the whole mesh
-//                  with the global table below, which overlays the regions
+//                  each direction's first index), then each entry takes its
+//                  twin from the slot it found.  A bucket of more distinct
+//                  keys than its LDS table has slots (only inputs built
+//                  against the hash hold one) is solved by its workgroup in
+//                  a table of its own in global memory
+// All of a thread's loads of a pass are issued before the first is used (eight
+// dependent rounds of memory latency were most of a pass before).  On 533 k
+// triangles in a buffer for 612 k, count / offsets / scatter / solve take
+// 5.1 / 4.4 / 15.2 / 22 us (8.2 / 6.0 / 22.9 / 30.0, and 4.7 for a launch that
+// looked for full tables, before), 46.6 us a call (68.1); streaming stores of
+// the twins: solve 47 us; 256 threads: 24 us.
 // Buckets: the power of two nearest above 3 cap / kHeBucketMean; a
 // bucket's keys are the top bits of the hash, its LDS slot the low bits.
 //
@@ -172,14 +177,24 @@ __global__ __launch_bounds__(kHeBlock) void k_he_lookup(const int32_t *__restric
 // Partitioned way
 // ---------------------------------------------------------------------------
 
+constexpr int kHePartBlock = 1024;        // threads of the partitioned way's kernels
 constexpr int kHeChunk = 4096;            // half-edges per row of the histogram
+constexpr int kHePer = kHeChunk / kHePartBlock;   // half-edges of a chunk per thread
 constexpr int kHeBucketMean = 2048;       // mean entries per bucket at n = 3 cap, at most
 constexpr int kHeRegion = 3072;           // entries a bucket's region holds
+constexpr int kHeSolvePer = kHeRegion / kHePartBlock;   // of them per thread
 constexpr int kHeLdsSlots = 4096;         // LDS table of a bucket (64 KB)
 constexpr int kHeMaxBuckets = 8192;       // LDS histogram of a chunk (32 KB)
 constexpr int kHeScanBuckets = 16;        // buckets per offsets workgroup
 constexpr int kHeScanParts = 64;          // parts splitting the chunks of a bucket
 constexpr int kHeScanBlock = kHeScanBuckets * kHeScanParts;
+
+// A half-edge in a bucket's region: its key's points and h | 2^31 when it
+// runs hi -> lo.  Kept together: a chunk's run of a bucket, a few entries
+// long, is then one piece of memory instead of two.
+struct HeEntry {
+    int lo, hi, hd;
+};
 
 int bucket_bits(int cap) {
     const long long want = (3LL * cap + kHeBucketMean - 1) / kHeBucketMean;
@@ -199,57 +214,85 @@ __device__ __forceinline__ int he_bucket(unsigned long long mix, int lg) {
     return lg == 0 ? 0 : (int)(mix >> (64 - lg));
 }
 
-__global__ __launch_bounds__(kHeBlock) void k_he_count(const int32_t *__restrict__ tris,
-                                                       const int32_t *__restrict__ n_tri, int cap,
-                                                       int lg, int32_t *__restrict__ hist_out) {
+// A thread's half-edges base + i kHePartBlock + threadIdx.x of its chunk, all
+// loads in flight at once: rows at or past n (known only when the device-side
+// count has arrived, but inside the capacity) are left out by a == b.
+__device__ __forceinline__ void he_chunk_ends(const int32_t *__restrict__ tris,
+                                              const int32_t *__restrict__ n_tri, int cap, int base,
+                                              int (&a)[kHePer], int (&b)[kHePer], int &n) {
+    const int cnt = *n_tri;
+#pragma unroll
+    for (int i = 0; i < kHePer; ++i) {
+        const int h = base + i * kHePartBlock + (int)threadIdx.x;
+        a[i] = 0;
+        b[i] = 0;
+        if (h < 3 * cap) he_ends(tris, h, a[i], b[i]);
+    }
+    n = 3 * min(max(cnt, 0), cap);
+}
+
+__global__ __launch_bounds__(kHePartBlock) void k_he_count(const int32_t *__restrict__ tris,
+                                                           const int32_t *__restrict__ n_tri,
+                                                           int cap, int lg,
+                                                           int32_t *__restrict__ hist_out) {
     extern __shared__ int hist[];
     const int nb = 1 << lg;
-    const int n = 3 * min(max(*n_tri, 0), cap);
-    for (int i = threadIdx.x; i < nb; i += kHeBlock) hist[i] = 0;
-    __syncthreads();
     const int base = (int)blockIdx.x * kHeChunk;
-#pragma unroll 4
-    for (int i = 0; i < kHeChunk / kHeBlock; ++i) {
-        const int h = base + i * kHeBlock + (int)threadIdx.x;
-        if (h >= n) break;
-        int a, b;
-        he_ends(tris, h, a, b);
-        if (a != b) atomicAdd(&hist[he_bucket(he_mix(he_key(min(a, b), max(a, b))), lg)], 1);
+    int a[kHePer], b[kHePer], n;
+    he_chunk_ends(tris, n_tri, cap, base, a, b, n);
+    for (int i = threadIdx.x; i < nb; i += kHePartBlock) hist[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kHePer; ++i) {
+        const int h = base + i * kHePartBlock + (int)threadIdx.x;
+        if (h < n && a[i] != b[i])
+            atomicAdd(&hist[he_bucket(he_mix(he_key(min(a[i], b[i]), max(a[i], b[i]))), lg)], 1);
     }
     __syncthreads();
     int32_t *row = hist_out + (size_t)blockIdx.x * nb;
-    for (int i = threadIdx.x; i < nb; i += kHeBlock) row[i] = hist[i];
+    for (int i = threadIdx.x; i < nb; i += kHePartBlock) row[i] = hist[i];
 }
 
 // 16 buckets per workgroup of 1024 threads: lane l of wave w takes bucket
 // l mod 16 and part 4 w + l / 16 of the chunks (kHeScanParts parts); each
-// part sums its chunks, the parts are scanned in LDS, then each part writes
-// its chunks' starts.  Also clears the control words.
+// part sums its chunks, the parts are scanned (across the wave's four, then
+// over the waves' sums in LDS), then each part writes its chunks' starts.
+// Also clears the control words.
 __global__ __launch_bounds__(kHeScanBlock) void k_he_offsets(
     const int32_t *__restrict__ hist, int chunks, int lg, int32_t *__restrict__ start,
     int32_t *__restrict__ total, int32_t *__restrict__ ctl) {
-    __shared__ int part_sum[kHeScanParts][kHeScanBuckets];
+    constexpr int kWaves = kHeScanBlock / kWave;
+    __shared__ int wave_total[kWaves][kHeScanBuckets];
     const int nb = 1 << lg;
-    const int col = (int)threadIdx.x % kHeScanBuckets, part = (int)threadIdx.x / kHeScanBuckets;
+    const int lane = (int)threadIdx.x & (kWave - 1), wave = (int)threadIdx.x / kWave;
+    const int col = lane % kHeScanBuckets, part = (int)threadIdx.x / kHeScanBuckets;
     const int b = (int)blockIdx.x * kHeScanBuckets + col;
     if (blockIdx.x == 0 && threadIdx.x < 2) ctl[threadIdx.x] = 0;
     const int per = (chunks + kHeScanParts - 1) / kHeScanParts;
     const int c0 = part * per, c1 = min(c0 + per, chunks);
     int sum = 0;
     if (b < nb) {
-#pragma unroll 4
+#pragma unroll 8
         for (int c = c0; c < c1; ++c) sum += hist[(size_t)c * nb + b];
     }
-    part_sum[part][col] = sum;
+    int incl = sum;                      // over the wave's parts of this bucket
+#pragma unroll
+    for (int d = kHeScanBuckets; d < kWave; d <<= 1) {
+        const int y = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl += y;
+    }
+    if (lane >= kWave - kHeScanBuckets) wave_total[wave][col] = incl;
     __syncthreads();
-    int run = 0, all = 0;
-    for (int k = 0; k < kHeScanParts; ++k) {
-        const int v = part_sum[k][col];
-        run += k < part ? v : 0;
+    int run = incl - sum, all = 0;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        const int v = wave_total[k][col];
+        run += k < wave ? v : 0;
         all += v;
     }
     if (b >= nb) return;
     if (part == 0) total[b] = all;
+#pragma unroll 8
     for (int c = c0; c < c1; ++c) {
         const int v = hist[(size_t)c * nb + b];
         start[(size_t)c * nb + b] = run;
@@ -257,81 +300,85 @@ __global__ __launch_bounds__(kHeScanBlock) void k_he_offsets(
     }
 }
 
-// Entry of a half-edge: its key and h | 2^31 when it runs hi -> lo.  The
-// chunk's entries are first placed in LDS in bucket order (the chunk's
+// Every half-edge's entry into its bucket's region.  The chunk's entries are first placed in LDS in bucket order (the chunk's
 // counts, scanned), then written out: the chunk's entries of one bucket are
 // one contiguous run of the bucket's region, written by consecutive lanes.
-// LDS: the chunk's keys and entries (12 kHeChunk bytes), then its bucket
-// starts and cursors (2 x 4 nb bytes).
-__device__ __forceinline__ int block_exclusive_scan(int x, int *tmp) {
+// LDS: the chunk's keys and entries (12 kHeChunk bytes), then per bucket a
+// cursor and what takes a place in LDS to a place in the bucket's region
+// (2 x 4 nb bytes).
+__device__ __forceinline__ int block_exclusive_scan(int x, int *tmp, int *all) {
     const int lane = (int)threadIdx.x & (kWave - 1), w = (int)threadIdx.x / kWave;
     const int incl = wave_inclusive_scan(x);
     if (lane == kWave - 1) tmp[w] = incl;
     __syncthreads();
-    int before = 0;
-    for (int k = 0; k < w; ++k) before += tmp[k];
+    int before = 0, sum = 0;
+#pragma unroll
+    for (int k = 0; k < kHePartBlock / kWave; ++k) {
+        const int v = tmp[k];
+        before += k < w ? v : 0;
+        sum += v;
+    }
+    *all = sum;
     return before + incl - x;
 }
 
-__global__ __launch_bounds__(kHeBlock) void k_he_scatter(
+__global__ __launch_bounds__(kHePartBlock) void k_he_scatter(
     const int32_t *__restrict__ tris, const int32_t *__restrict__ n_tri, int cap, int lg,
     const int32_t *__restrict__ hist, const int32_t *__restrict__ start,
-    unsigned long long *__restrict__ keys, int32_t *__restrict__ hds, int32_t *__restrict__ ctl,
-    unsigned long long *__restrict__ okeys, int32_t *__restrict__ ohds, int32_t *__restrict__ he) {
+    HeEntry *__restrict__ region, int32_t *__restrict__ ctl, HeEntry *__restrict__ over,
+    int32_t *__restrict__ he) {
     extern __shared__ unsigned long long lds_u64[];
-    __shared__ int tmp[kHeBlock / kWave];
+    __shared__ int tmp[kHePartBlock / kWave];
     const int nb = 1 << lg;
     unsigned long long *skey = lds_u64;                                  // [kHeChunk]
     int *shd = reinterpret_cast<int *>(skey + kHeChunk);                 // [kHeChunk]
-    int *lstart = shd + kHeChunk;                                        // [nb]
-    int *lcur = lstart + nb;                                             // [nb]
-    const int n = 3 * min(max(*n_tri, 0), cap);
+    int *lcur = shd + kHeChunk;                                          // [nb]
+    int *ldelta = lcur + nb;                                             // [nb]
     const int base = (int)blockIdx.x * kHeChunk;
-    if (base >= n) return;
     const int32_t *crow = hist + (size_t)blockIdx.x * nb;
     const int32_t *srow = start + (size_t)blockIdx.x * nb;
+    int a[kHePer], b[kHePer], n;
+    he_chunk_ends(tris, n_tri, cap, base, a, b, n);
     // the chunk's starts per bucket: each thread scans `per` consecutive
-    // counts (nb < kHeBlock: one or none)
-    const int per = (nb + kHeBlock - 1) / kHeBlock;
+    // counts (nb < kHePartBlock: one or none)
+    const int per = (nb + kHePartBlock - 1) / kHePartBlock;
     const int b0 = (int)threadIdx.x * per;
     int own = 0;
     for (int k = 0; k < per && b0 + k < nb; ++k) own += crow[b0 + k];
-    int run = block_exclusive_scan(own, tmp);
+    int m;                                       // entries of the chunk
+    int run = block_exclusive_scan(own, tmp, &m);
     for (int k = 0; k < per && b0 + k < nb; ++k) {
-        lstart[b0 + k] = run;
         lcur[b0 + k] = run;
+        ldelta[b0 + k] = srow[b0 + k] - run;
         run += crow[b0 + k];
     }
     __syncthreads();
-#pragma unroll 4
-    for (int i = 0; i < kHeChunk / kHeBlock; ++i) {
-        const int h = base + i * kHeBlock + (int)threadIdx.x;
-        if (h >= n) break;
-        int a, b;
-        he_ends(tris, h, a, b);
-        if (a == b) {
+#pragma unroll
+    for (int i = 0; i < kHePer; ++i) {
+        const int h = base + i * kHePartBlock + (int)threadIdx.x;
+        if (h >= n) continue;
+        if (a[i] == b[i]) {
             he[h] = -1;                  // from a point to itself: never paired
             continue;
         }
-        const unsigned long long key = he_key(min(a, b), max(a, b));
+        const unsigned long long key = he_key(min(a[i], b[i]), max(a[i], b[i]));
         const int lp = atomicAdd(&lcur[he_bucket(he_mix(key), lg)], 1);
         skey[lp] = key;
-        shd[lp] = a < b ? h : (h | INT_MIN);
+        shd[lp] = a[i] < b[i] ? h : (h | INT_MIN);
     }
     __syncthreads();
-    const int m = lcur[nb - 1];                  // entries staged: the last bucket's end
-    for (int i = threadIdx.x; i < m; i += kHeBlock) {
+#pragma unroll
+    for (int k = 0; k < kHePer; ++k) {
+        const int i = k * kHePartBlock + (int)threadIdx.x;
+        if (i >= m) continue;
         const unsigned long long key = skey[i];
         const int bk = he_bucket(he_mix(key), lg);
-        const int pos = srow[bk] + (i - lstart[bk]);
-        if (pos < kHeRegion) {
-            keys[(size_t)bk * kHeRegion + pos] = key;
-            hds[(size_t)bk * kHeRegion + pos] = shd[i];
-        } else {
-            const int o = atomicAdd(&ctl[0], 1);
-            okeys[o] = key;
-            ohds[o] = shd[i];
-        }
+        const int pos = i + ldelta[bk];
+        const HeEntry e{(int)(key >> 32), (int)key, shd[i]};
+        if (pos < kHeRegion)
+            region[(size_t)bk * kHeRegion + pos] = e;
+        else
+            over[atomicAdd(&ctl[0], 1)] = e;
     }
 }
 
@@ -340,148 +387,155 @@ struct HeLdsTable {
     int2 first[kHeLdsSlots];             // first half-edge lo -> hi, hi -> lo
 };
 
-// Claims the key's slot and lowers its direction's first index; false when
-// the table is full.
-__device__ __forceinline__ bool he_lds_insert(HeLdsTable &t, unsigned long long key, int hd) {
+// Claims the key's slot and lowers its direction's first index: the slot, or
+// -1 when the table is full of other keys.
+__device__ __forceinline__ int he_lds_insert(HeLdsTable &t, unsigned long long key, int hd) {
     int slot = (int)(he_mix(key) & (kHeLdsSlots - 1));
     for (int p = 0; p < kHeLdsSlots; ++p) {
         const unsigned long long prev = atomicCAS(&t.key[slot], kEmpty, key);
         if (prev == kEmpty || prev == key) {
             atomicMin(hd < 0 ? &t.first[slot].y : &t.first[slot].x, hd & INT_MAX);
-            return true;
+            return slot;
         }
         slot = (slot + 1) & (kHeLdsSlots - 1);
     }
-    return false;
+    return -1;
 }
 
-// The twin of entry hd; false if its key is not in the table (it always is
-// once every insert succeeded: the probe is bounded all the same).
-__device__ __forceinline__ bool he_lds_twin(const HeLdsTable &t, unsigned long long key, int hd,
-                                            int &twin) {
+// The slot of a key; -1 if it is not in the table (it always is once every
+// insert succeeded: the probe is bounded all the same).
+__device__ __forceinline__ int he_lds_find(const HeLdsTable &t, unsigned long long key) {
     int slot = (int)(he_mix(key) & (kHeLdsSlots - 1));
     for (int p = 0; p < kHeLdsSlots; ++p) {
-        if (t.key[slot] == key) {
-            const int2 f = t.first[slot];
-            const int h = hd & INT_MAX;
-            const int own = hd < 0 ? f.y : f.x, other = hd < 0 ? f.x : f.y;
-            twin = own == h && other != INT_MAX ? other : -1;
-            return true;
-        }
+        if (t.key[slot] == key) return slot;
         slot = (slot + 1) & (kHeLdsSlots - 1);
     }
-    return false;
+    return -1;
 }
 
-// The global-table way in one workgroup (the fallback).  The table is
-// cleared, filled and read by this workgroup alone, all through atomics
-// (which meet in L2).
-__device__ void he_global_one_group(const int32_t *__restrict__ tris, int n, HeSlot *tab,
-                                    unsigned long long slots, int32_t *__restrict__ he) {
-    for (size_t i = threadIdx.x; i < slots; i += kHeBlock) {
+// The twin of entry hd from its slot's first indices.
+__device__ __forceinline__ int he_twin(int2 f, int hd) {
+    const int own = hd < 0 ? f.y : f.x, other = hd < 0 ? f.x : f.y;
+    return own == (hd & INT_MAX) && other != INT_MAX ? other : -1;
+}
+
+// A bucket with more distinct keys than the LDS table has slots, by its
+// workgroup alone: its entries (the first m of its region, then its own of
+// the overflow list's no) through `slots` > their number slots of a table in
+// global memory, all through atomics (which meet in L2).
+__device__ void he_bucket_global(const HeEntry *__restrict__ r, int m,
+                                 const HeEntry *__restrict__ over, int no, int bk, int lg, HeSlot *tab, unsigned long long slots, int32_t *__restrict__ he) {
+    for (size_t i = threadIdx.x; i < slots; i += kHePartBlock) {
         __hip_atomic_store(&tab[i].key, kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&tab[i].fwd, INT_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&tab[i].bwd, INT_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    for (int h = threadIdx.x; h < n; h += kHeBlock) {
-        int a, b;
-        he_ends(tris, h, a, b);
-        if (a == b) continue;
-        const unsigned long long key = he_key(min(a, b), max(a, b));
-        unsigned long long slot = he_slot(key, slots);
+    for (int i = threadIdx.x; i < m + no; i += kHePartBlock) {
+        const HeEntry e = i < m ? r[i] : over[i - m];
+        const unsigned long long key = he_key(e.lo, e.hi), mix = he_mix(key);
+        if (i >= m && he_bucket(mix, lg) != bk) continue;
+        const int hd = e.hd;
+        // the bucket's keys share the mix's top bits: the rest spreads them
+        unsigned long long slot = __umul64hi(mix << lg, slots);
         for (unsigned long long p = 0; p < slots; ++p) {     // a free slot is always left
             const unsigned long long prev = atomicCAS(&tab[slot].key, kEmpty, key);
             if (prev == kEmpty || prev == key) {
-                atomicMin(a < b ? &tab[slot].fwd : &tab[slot].bwd, h);
+                atomicMin(hd < 0 ? &tab[slot].bwd : &tab[slot].fwd, hd & INT_MAX);
                 break;
             }
             slot = slot + 1 == slots ? 0 : slot + 1;
         }
     }
     __syncthreads();
-    for (int h = threadIdx.x; h < n; h += kHeBlock) {
-        int a, b;
-        he_ends(tris, h, a, b);
-        int twin = -1;
-        if (a != b) {
-            const unsigned long long key = he_key(min(a, b), max(a, b));
-            unsigned long long slot = he_slot(key, slots);
-            for (unsigned long long p = 0; p < slots; ++p) {     // found at once or soon
-                if (__hip_atomic_load(&tab[slot].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == key) {
-                    const int f = __hip_atomic_load(&tab[slot].fwd, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-                    const int g = __hip_atomic_load(&tab[slot].bwd, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-                    const int own = a < b ? f : g, other = a < b ? g : f;
-                    if (own == h && other != INT_MAX) twin = other;
-                    break;
-                }
-                slot = slot + 1 == slots ? 0 : slot + 1;
+    for (int i = threadIdx.x; i < m + no; i += kHePartBlock) {
+        const HeEntry e = i < m ? r[i] : over[i - m];
+        const unsigned long long key = he_key(e.lo, e.hi), mix = he_mix(key);
+        if (i >= m && he_bucket(mix, lg) != bk) continue;
+        const int hd = e.hd;
+        unsigned long long slot = __umul64hi(mix << lg, slots);
+        for (unsigned long long p = 0; p < slots; ++p) {     // found at once or soon
+            if (__hip_atomic_load(&tab[slot].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == key) {
+                int2 f;
+                f.x = __hip_atomic_load(&tab[slot].fwd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                f.y = __hip_atomic_load(&tab[slot].bwd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                he[hd & INT_MAX] = he_twin(f, hd);
+                break;
             }
+            slot = slot + 1 == slots ? 0 : slot + 1;
         }
-        he[h] = twin;
     }
 }
 
-// ctl: [0] overflow entries, [1] some bucket's table was full.
-__global__ __launch_bounds__(kHeBlock) void k_he_solve(
-    const unsigned long long *__restrict__ keys, const int32_t *__restrict__ hds,
-    const int32_t *__restrict__ total, int32_t *ctl,
-    const unsigned long long *__restrict__ okeys, const int32_t *__restrict__ ohds, int lg,
-    int32_t *__restrict__ he) {
+// One workgroup per bucket (two per CU, by the LDS of their tables).  Bound by
+// latency and by the twins' scattered 4-byte writes.  A thread holds its entries of the region in
+// registers, loaded at once, and the slots they found: the twins then need
+// neither a second read of the entries nor a second probe.
+// ctl: [0] overflow entries, [1] slots taken of the global table `tab`, whose
+// 4 cap slots suffice: a bucket takes 4/3 of its entries, and all buckets
+// together hold at most 3 cap.
+__global__ __launch_bounds__(kHePartBlock) void k_he_solve(
+    const HeEntry *__restrict__ region, const int32_t *__restrict__ total, int32_t *ctl,
+    const HeEntry *__restrict__ over, int lg, HeSlot *tab, int32_t *__restrict__ he) {
     __shared__ HeLdsTable t;
+    __shared__ int full, tab_base;
     const int bk = (int)blockIdx.x;
-    for (int i = threadIdx.x; i < kHeLdsSlots; i += kHeBlock) {
-        t.key[i] = kEmpty;
-        t.first[i] = make_int2(INT_MAX, INT_MAX);
-    }
-    __syncthreads();
     const int tot = total[bk], m = min(tot, kHeRegion);
     // a bucket that overflowed also takes its entries from the overflow list
     const int no = tot > kHeRegion ? ctl[0] : 0;
-    const unsigned long long *rk = keys + (size_t)bk * kHeRegion;
-    const int32_t *rh = hds + (size_t)bk * kHeRegion;
-    for (int i = threadIdx.x; i < m + no; i += kHeBlock) {
-        const unsigned long long key = i < m ? rk[i] : okeys[i - m];
-        if (i >= m && he_bucket(he_mix(key), lg) != bk) continue;
-        if (!he_lds_insert(t, key, i < m ? rh[i] : ohds[i - m]))    // table full
-            __hip_atomic_store(&ctl[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const HeEntry *r = region + (size_t)bk * kHeRegion;
+    HeEntry e[kHeSolvePer];
+    int slot[kHeSolvePer];
+#pragma unroll
+    for (int k = 0; k < kHeSolvePer; ++k) {
+        const int i = k * kHePartBlock + (int)threadIdx.x;
+        e[k] = i < m ? r[i] : HeEntry{0, 0, 0};
     }
+    for (int i = threadIdx.x; i < kHeLdsSlots; i += kHePartBlock) {
+        t.key[i] = kEmpty;
+        t.first[i] = make_int2(INT_MAX, INT_MAX);
+    }
+    if (threadIdx.x == 0) full = 0;
     __syncthreads();
-    // once any bucket's table was full the fallback redoes the whole mesh
-    if (__hip_atomic_load(&ctl[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
-        for (int i = threadIdx.x; i < m + no; i += kHeBlock) {
-            const unsigned long long key = i < m ? rk[i] : okeys[i - m];
-            if (i >= m && he_bucket(he_mix(key), lg) != bk) continue;
-            const int hd = i < m ? rh[i] : ohds[i - m];
-            int twin;
-            if (he_lds_twin(t, key, hd, twin))
-                he[hd & INT_MAX] = twin;
-            else
-                __hip_atomic_store(&ctl[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int k = 0; k < kHeSolvePer; ++k) {
+        slot[k] = -1;
+        if (k * kHePartBlock + (int)threadIdx.x < m) {
+            slot[k] = he_lds_insert(t, he_key(e[k].lo, e[k].hi), e[k].hd);
+            if (slot[k] < 0) full = 1;
         }
     }
-}
-
-// One workgroup after the buckets: returns at once unless some bucket's
-// table was full, and then redoes the whole mesh with the global table
-// (the launch boundary orders it after every bucket's writes).
-__global__ __launch_bounds__(kHeBlock) void k_he_fallback(const int32_t *__restrict__ tris,
-                                                          const int32_t *__restrict__ n_tri,
-                                                          int cap, const int32_t *__restrict__ ctl,
-                                                          HeSlot *tab, unsigned long long slots,
-                                                          int32_t *__restrict__ he) {
-    if (ctl[1] == 0) return;
-    he_global_one_group(tris, 3 * min(max(*n_tri, 0), cap), tab, slots, he);
+    for (int i = threadIdx.x; i < no; i += kHePartBlock) {
+        const HeEntry o = over[i];
+        const unsigned long long k = he_key(o.lo, o.hi);
+        if (he_bucket(he_mix(k), lg) == bk && he_lds_insert(t, k, o.hd) < 0) full = 1;
+    }
+    __syncthreads();
+    if (full) {
+        if (threadIdx.x == 0) tab_base = atomicAdd(&ctl[1], tot + tot / 3);
+        __syncthreads();
+        he_bucket_global(r, m, over, no, bk, lg, tab + tab_base,
+                         (unsigned long long)(tot + tot / 3), he);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kHeSolvePer; ++k)
+        if (slot[k] >= 0) he[e[k].hd & INT_MAX] = he_twin(t.first[slot[k]], e[k].hd);
+    for (int i = threadIdx.x; i < no; i += kHePartBlock) {
+        const HeEntry o = over[i];
+        const unsigned long long k = he_key(o.lo, o.hi);
+        if (he_bucket(he_mix(k), lg) != bk) continue;
+        const int s = he_lds_find(t, k);
+        if (s >= 0) he[o.hd & INT_MAX] = he_twin(t.first[s], o.hd);
+    }
 }
 
 // Workspace of the partitioned way: the histogram rows and their starts,
-// the bucket totals, two control words, then the regions and the overflow
-// list, which the fallback's global table overlays.
+// the bucket totals, two control words, the regions, the overflow list and
+// the global table of buckets that outgrow their LDS table.
 struct HeParts {
     int lg, nb, chunks;
-    size_t hist, start, total, ctl, keys, hds, okeys, ohds, end;
+    size_t hist, start, total, ctl, region, over, tab, end;
 };
 
 HeParts he_parts(int cap) {
@@ -495,15 +549,10 @@ HeParts he_parts(int cap) {
     p.start = take(4 * (size_t)p.chunks * p.nb);
     p.total = take(4 * (size_t)p.nb);
     p.ctl = take(8);
-    const size_t region = (size_t)p.nb * kHeRegion;
-    const size_t lists = align_up(8 * region, 256) + align_up(4 * region, 256) +
-                         align_up(24 * (size_t)cap, 256) + align_up(12 * (size_t)cap, 256);
-    p.keys = o;
-    p.hds = p.keys + align_up(8 * region, 256);
-    p.okeys = p.hds + align_up(4 * region, 256);
-    p.ohds = p.okeys + align_up(24 * (size_t)cap, 256);
-    const size_t table = sizeof(HeSlot) * table_slots(cap);
-    p.end = o + std::max(lists, align_up(table, 256));
+    p.region = take(sizeof(HeEntry) * (size_t)p.nb * kHeRegion);
+    p.over = take(sizeof(HeEntry) * 3 * (size_t)cap);
+    p.tab = take(sizeof(HeSlot) * 4 * (size_t)cap);
+    p.end = o;
     return p;
 }
 
@@ -526,27 +575,22 @@ pl_status launch_user_halfedges(const int32_t *tris, const int32_t *n_tri, int c
         auto *start = reinterpret_cast<int32_t *>(w + p.start);
         auto *total = reinterpret_cast<int32_t *>(w + p.total);
         auto *ctl = reinterpret_cast<int32_t *>(w + p.ctl);
-        auto *keys = reinterpret_cast<unsigned long long *>(w + p.keys);
-        auto *hds = reinterpret_cast<int32_t *>(w + p.hds);
-        auto *okeys = reinterpret_cast<unsigned long long *>(w + p.okeys);
-        auto *ohds = reinterpret_cast<int32_t *>(w + p.ohds);
+        auto *region = reinterpret_cast<HeEntry *>(w + p.region);
+        auto *over = reinterpret_cast<HeEntry *>(w + p.over);
         const size_t hist_lds = 4 * (size_t)p.nb;
-        k_he_count<<<p.chunks, kHeBlock, hist_lds, s>>>(tris, n_tri, cap, p.lg, hist);
+        k_he_count<<<p.chunks, kHePartBlock, hist_lds, s>>>(tris, n_tri, cap, p.lg, hist);
         if (pl_status st = hip_check(hipGetLastError(), "k_he_count")) return st;
         k_he_offsets<<<(p.nb + kHeScanBuckets - 1) / kHeScanBuckets, kHeScanBlock, 0, s>>>(
             hist, p.chunks, p.lg, start, total, ctl);
         if (pl_status st = hip_check(hipGetLastError(), "k_he_offsets")) return st;
         const size_t scatter_lds = 12 * (size_t)kHeChunk + 8 * (size_t)p.nb;
         if (pl_status st = allow_lds((const void *)k_he_scatter, scatter_lds)) return st;
-        k_he_scatter<<<p.chunks, kHeBlock, scatter_lds, s>>>(tris, n_tri, cap, p.lg, hist, start,
-                                                             keys, hds, ctl, okeys, ohds, he);
+        k_he_scatter<<<p.chunks, kHePartBlock, scatter_lds, s>>>(tris, n_tri, cap, p.lg, hist, start,
+                                                                 region, ctl, over, he);
         if (pl_status st = hip_check(hipGetLastError(), "k_he_scatter")) return st;
-        k_he_solve<<<p.nb, kHeBlock, 0, s>>>(keys, hds, total, ctl, okeys, ohds, p.lg, he);
-        if (pl_status st = hip_check(hipGetLastError(), "k_he_solve")) return st;
-        k_he_fallback<<<1, kHeBlock, 0, s>>>(tris, n_tri, cap, ctl,
-                                             reinterpret_cast<HeSlot *>(w + p.keys),
-                                             table_slots(cap), he);
-        return hip_check(hipGetLastError(), "k_he_fallback");
+        k_he_solve<<<p.nb, kHePartBlock, 0, s>>>(region, total, ctl, over, p.lg,
+                                                 reinterpret_cast<HeSlot *>(w + p.tab), he);
+        return hip_check(hipGetLastError(), "k_he_solve");
     }
     const size_t slots = table_slots(cap);
     auto *tab = static_cast<HeSlot *>(ws);

@@ -193,6 +193,37 @@ def test_full_lds_table_falls_back(pl):
     assert (want >= 0).sum() >= 2 * (n // 5)
 
 
+@pytest.mark.parametrize("extra", [1, 300])
+def test_two_full_buckets(pl, extra):
+    """Two buckets with `extra` more distinct keys than their LDS tables have
+    slots, beside ordinary ones: each is solved in its own part of the global
+    table."""
+    cap, lg = 20000, 5
+    rng = np.random.default_rng(80 + extra)
+    edges = set()
+    for bucket in (3, 30):
+        want = len(edges) + 4096 + extra
+        while len(edges) < want:
+            v = (bucket << (64 - lg)) | int(rng.integers(0, 1 << (64 - lg)))
+            key = _unmix(v)
+            lo, hi = _signed(key >> 32), _signed(key & 0xffffffff)
+            if lo < hi:
+                edges.add((lo, hi))
+    E = np.array(sorted(edges), dtype=np.int64)
+    third = rng.integers(-1000, 1000, size=len(E))
+    T = np.concatenate([np.stack([E[:, 0], E[:, 1], third], axis=1),
+                        np.stack([E[::4, 1], E[::4, 0], third[::4] + 7], axis=1)]).astype(np.int32)
+    T = T[rng.permutation(len(T))]
+    assert len(T) <= cap
+    P = np.zeros((cap, 3), dtype=np.int32)
+    P[:len(T)] = T
+    say("user halfedges two full buckets", len(T), "cap", cap)
+    got = gpu_he(pl, P, len(T))
+    want = oracle.user_halfedges(T)
+    assert np.array_equal(got[:3 * len(T)], want)
+    assert (want >= 0).sum() >= 2 * (len(E) // 4)
+
+
 def test_global_table_way(pl):
     """A capacity past the partitioned way's bound (more than 8192 buckets):
     the global table, on the first rows."""
