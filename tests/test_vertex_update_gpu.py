@@ -69,3 +69,14 @@ def test_full_frames(pl, orc, kind):
     nf = r["filtered"].astype(np.float32)
     say("vertex update full", kind)
     check(pl, pts, nf, 3)
+
+
+@pytest.mark.parametrize("M,N", [(16, 32), (17, 33), (31, 65), (2, 40), (50, 2)])
+def test_sweeps_over_launches(pl, orc, M, N):
+    """Up to five sweeps share a launch: at the edges of its 16 x 32 tiles, in
+    one, two and three launches."""
+    g = synth.random_grid(M, N, 7 * M + N, nan_frac=0.1, noise=0.02)
+    n, _ = orc.tri_normals(g)
+    for iters in (4, 5, 6, 11):
+        say("vertex update", M, N, "iters", iters)
+        check(pl, g, n.astype(np.float32), iters)
