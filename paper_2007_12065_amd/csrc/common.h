@@ -19,6 +19,13 @@ __device__ __forceinline__ bool is_nan_bits(float x) {
     return (__float_as_uint(x) & 0x7fffffffu) > 0x7f800000u;
 }
 
+// Whether any of three values is NaN: two unordered comparisons (each takes
+// two operands), where three bit-pattern tests take six instructions.  The
+// library is built without any fast-math flag.
+__device__ __forceinline__ bool any_nan(float x, float y, float z) {
+    return __builtin_isunordered(x, y) || __builtin_isunordered(z, z);
+}
+
 __device__ __forceinline__ float qnan() { return __uint_as_float(0x7fc00000u); }
 
 // Workgroups are dispatched round-robin over the XCDs (workgroup b runs on

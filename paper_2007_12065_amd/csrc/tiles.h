@@ -463,19 +463,31 @@ __device__ __forceinline__ void lap_tile(const float *__restrict__ src, float *_
     const int oy = ty0 - halo, ox = tx0 - halo;
     const float inf = __builtin_inff();
 
+    // three points per thread and pass, their loads issued before the first is
+    // used: a 16 x 16 tile with its halo of four waits for memory once
+    constexpr int kU = 3;
     const DivBy byW(W);
-    for (int idx = threadIdx.x; idx < H * W; idx += kTileBlock) {
-        const int ly = byW.div(idx), lx = idx - ly * W;
-        const int gy = oy + ly, gx = ox + lx;
-        float4 p = make_float4(0.f, 0.f, 0.f, inf);
-        if (gy >= 0 && gy < M && gx >= 0 && gx < N) {
-            const float *q = src + 3 * ((size_t)gy * N + gx);
-            const float x = q[0], y = q[1], z = q[2];
-            const bool inner = gy >= R && gy < M - R && gx >= R && gx < N - R;
-            if (!(is_nan_bits(x) || is_nan_bits(y) || is_nan_bits(z)))
-                p = make_float4(x, y, z, inner ? 0.f : -0.f);
+    for (int base = threadIdx.x; base < H * W; base += kU * kTileBlock) {
+        float4 p[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int idx = base + u * kTileBlock;
+            const int ly = byW.div(idx), lx = idx - ly * W;
+            const int gy = oy + ly, gx = ox + lx;
+            p[u] = make_float4(qnan(), 0.f, 0.f, inf);
+            if (idx < H * W && (unsigned)gy < (unsigned)M && (unsigned)gx < (unsigned)N) {
+                const float *q = src + 3 * ((size_t)gy * N + gx);
+                const bool inner = gy >= R && gy < M - R && gx >= R && gx < N - R;
+                p[u] = make_float4(q[0], q[1], q[2], inner ? 0.f : -0.f);
+            }
         }
-        A[idx] = p;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int idx = base + u * kTileBlock;
+            if (idx >= H * W) break;
+            if (any_nan(p[u].x, p[u].y, p[u].z)) p[u] = make_float4(0.f, 0.f, 0.f, inf);
+            A[idx] = p[u];
+        }
     }
     __syncthreads();
 
@@ -558,9 +570,7 @@ struct V3 {
     float x, y, z;
 };
 
-__device__ __forceinline__ bool ok3(const V3 &a) {
-    return !(is_nan_bits(a.x) || is_nan_bits(a.y) || is_nan_bits(a.z));
-}
+__device__ __forceinline__ bool ok3(const V3 &a) { return !any_nan(a.x, a.y, a.z); }
 
 // centroid (a + b + c) / 3 and unit normal of (b - a) x (c - a); NaN normal
 // when the cross product vanishes.
@@ -597,6 +607,17 @@ __device__ __forceinline__ void quad_geom(const V3 &p1, const V3 &p2, const V3 &
     c0 = nan3; n0 = nan3; c1 = nan3; n1 = nan3;
     if (v1 & v2 & v3) tri_geom(p3, p2, p1, c0, n0);     // first triangle
     if (v1 & v3 & v4) tri_geom(p1, p4, p3, c1, n1);     // second triangle
+}
+
+// The corners of quad (qy, qx) of a frame with N points per row.
+struct QuadPoints {
+    V3 p1, p2, p3, p4;
+};
+
+__device__ __forceinline__ QuadPoints quad_points(const float *__restrict__ pts, int N, int qy, int qx) {
+    const float *r0 = pts + 3 * ((size_t)qy * N + qx);
+    const float *r1 = r0 + 3 * (size_t)N;
+    return QuadPoints{{r0[0], r0[1], r0[2]}, {r0[3], r0[4], r0[5]}, {r1[3], r1[4], r1[5]}, {r1[0], r1[1], r1[2]}};
 }
 
 // Quad (qy, qx) of a frame with N points per row: centroids and normals.
@@ -716,16 +737,18 @@ __device__ __forceinline__ void normals_block(const float *__restrict__ pts, int
 // of quad a-d.  The order is the same for every tile shape and fusion depth,
 // so float32 results are too.
 //
-// Off-grid quads and triangles with a NaN normal or centroid are staged with
-// an infinite centroid and a zero normal: infinite exponent, weight exactly 0,
-// contribution 0.  A triangle that is itself missing is copied through (its
+// A staged quad is 12 floats (c0, c1, n0, n1) in three planes of float4: three
+// 16-byte reads per neighbour, 48 bytes per quad (one float4 per vector, 64
+// bytes, took four reads and a fourth address).  Off-grid quads and triangles
+// with a NaN normal or centroid are staged with an infinite centroid and a
+// zero normal: infinite exponent, weight exactly 0, contribution 0.  A triangle that is itself missing is copied through (its
 // input bits).  Float16-stored normals produced by an intermediate sweep are
 // re-rounded to float16, as if stored between launches, so results do not
 // depend on F.  F = 0 copies the tile (and gathers).
-// LDS: (TQH + 2RF) * (TQW + 2RF) float4 times 4 (centroids and normals of
-// both triangles) or, with F > 1, times 6 (a second normal buffer), and the
-// queue of underflowed triangles (one int per triangle of the region, and
-// its count).
+// LDS: (TQH + 2RF) * (TQW + 2RF) quads of 48 bytes, twice with F > 1 (a sweep
+// writes the second buffer, centroids along), a byte of flags per quad and
+// the queue of underflowed triangles (16 bits per triangle of the region, and
+// its counts).
 // ---------------------------------------------------------------------------
 
 constexpr float kBilUnderflow2 = 0x1p-120f;       // (2^-60)^2
@@ -759,10 +782,11 @@ __host__ __device__ constexpr int bil_xch_floats(int R) {
     return R >= 2 ? (PL_BIL_PARTS_K5 - 1) * 6 * 64 : 0;
 }
 __host__ __device__ constexpr size_t bil_lds_bytes(int R, int F, int TQH, int TQW, bool waves) {
-    return (F > 1 ? 6 : 4) * sizeof(float4) * (size_t)(TQH + 2 * R * F) * (size_t)(TQW + 2 * R * F) +
-           sizeof(int) * (2 * (size_t)(TQH + 2 * R * F) * (size_t)(TQW + 2 * R * F) + kBilMaxSweeps + 1) +
+    const size_t S = (size_t)(TQH + 2 * R * F) * (size_t)(TQW + 2 * R * F);
+    return (F > 1 ? 6 : 3) * sizeof(float4) * S +
+           sizeof(int) * (kBilMaxSweeps + 1) + sizeof(uint16_t) * 2 * S +
            sizeof(int) * (size_t)TQH * TQW +    // T ranks of the tile (gather from the mesh codes)
-           (waves ? sizeof(float) * (size_t)bil_xch_floats(R) : 0);
+           (waves ? sizeof(float) * (size_t)bil_xch_floats(R) : 0) + S;
 }
 
 // The mesh's codes and per-segment counts (pl_mesh_opc's first pass): with
@@ -791,13 +815,48 @@ struct BilOwn {
     float ka, kb;
 };
 
-__device__ __forceinline__ float bil_pair_e(const BilOwn &o, const float4 c, const float4 n) {
+__device__ __forceinline__ float bil_pair_e(const BilOwn &o, const V3 &c, const V3 &n) {
     const float ax = o.nx - n.x, ay = o.ny - n.y, az = o.nz - n.z;
     const float dn2 = fmaf(ax, ax, fmaf(ay, ay, az * az));
     const float dx = o.cx - c.x, dy = o.cy - c.y, dz = o.cz - c.z;
     const float dc2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
     return fmaf(dc2, o.ka, dn2 * o.kb);
 }
+
+// A quad's centroids and normals, and their place in LDS: floats 0..11 of
+// (c0, c1, n0, n1) are plane i / 4, component i mod 4.
+struct BilQuad {
+    V3 c0, c1, n0, n1;
+};
+
+__device__ __forceinline__ BilQuad bil_read(const float4 *s, int a, int plane) {
+    const float4 p = s[a], q = s[plane + a], r = s[2 * plane + a];
+    return BilQuad{{p.x, p.y, p.z}, {p.w, q.x, q.y}, {q.z, q.w, r.x}, {r.y, r.z, r.w}};
+}
+
+__device__ __forceinline__ void bil_write(float4 *s, int a, int plane, const V3 &c0, const V3 &c1,
+                                          const V3 &n0, const V3 &n1) {
+    s[a] = make_float4(c0.x, c0.y, c0.z, c1.x);
+    s[plane + a] = make_float4(c1.y, c1.z, n0.x, n0.y);
+    s[2 * plane + a] = make_float4(n0.z, n1.x, n1.y, n1.z);
+}
+
+// Vector v (0: c0, 1: c1, 2: n0, 3: n1) of the quad at a.
+__device__ __forceinline__ float *bil_at(float4 *s, int a, int plane, int i) {
+    return reinterpret_cast<float *>(s + (i >> 2) * plane + a) + (i & 3);
+}
+__device__ __forceinline__ V3 bil_vec(const float4 *s, int a, int plane, int v) {
+    float4 *t = const_cast<float4 *>(s);
+    return V3{*bil_at(t, a, plane, 3 * v), *bil_at(t, a, plane, 3 * v + 1), *bil_at(t, a, plane, 3 * v + 2)};
+}
+
+// Flags of a staged quad: bit k: triangle k is usable; bit 2 + k: it is not,
+// and its normal as stored is the canonical NaN in every component (from the
+// points: for a missing corner, where its centroid is that too).
+constexpr int kBilUsable = 1, kBilCanonical = 4;
+
+__device__ __forceinline__ bool is_qnan(float x) { return __float_as_uint(x) == 0x7fc00000u; }
+__device__ __forceinline__ bool is_qnan(__half x) { return __half_as_ushort(x) == 0x7e00u; }
 
 // Sum of weighted neighbour normals.  Eq. 6 renormalises it, so the sum of
 // the weights is not needed; the underflow test uses the vector's norm,
@@ -807,7 +866,7 @@ struct BilAcc {
 };
 
 // s += 2^(m - e) * n
-__device__ __forceinline__ void bil_add(BilAcc &s, float m, float e, const float4 n) {
+__device__ __forceinline__ void bil_add(BilAcc &s, float m, float e, const V3 &n) {
     const float w = __builtin_amdgcn_exp2f(m - e);
     s.x = fmaf(w, n.x, s.x);
     s.y = fmaf(w, n.y, s.y);
@@ -833,12 +892,11 @@ __device__ __forceinline__ float bil_norm2(const BilAcc &s) {
 }
 
 template <typename NT>
-__device__ __forceinline__ float4 bil_finish(BilAcc s, float4 cur) {
+__device__ __forceinline__ V3 bil_finish(BilAcc s, const V3 &cur) {
     const float l2 = bil_norm2(s);
     if (!(l2 > 0.f)) return cur;            // no usable neighbour
     const float k = __builtin_amdgcn_rsqf(l2);
-    return make_float4(round_storage<NT>(s.x * k), round_storage<NT>(s.y * k),
-                       round_storage<NT>(s.z * k), cur.w);
+    return V3{round_storage<NT>(s.x * k), round_storage<NT>(s.y * k), round_storage<NT>(s.z * k)};
 }
 
 // Weight of a triangle pair (Eqs. 4-5 with log2(e) folded into ka and kb),
@@ -846,8 +904,8 @@ __device__ __forceinline__ float4 bil_finish(BilAcc s, float4 cur) {
 // only: swapping the triangles changes the sign of every difference exactly
 // and none of the squares.  A pair with an off-grid or missing triangle has
 // e = +inf and weight 0 (NaN only when both are missing; no sum uses that).
-__device__ __forceinline__ float bil_w(const float4 ci, const float4 ni, const float4 cj,
-                                       const float4 nj, float ka, float kb) {
+__device__ __forceinline__ float bil_w(const V3 &ci, const V3 &ni, const V3 &cj, const V3 &nj,
+                                       float ka, float kb) {
     const float ax = ni.x - nj.x, ay = ni.y - nj.y, az = ni.z - nj.z;
     const float dn2 = fmaf(ax, ax, fmaf(ay, ay, az * az));
     const float dx = ci.x - cj.x, dy = ci.y - cj.y, dz = ci.z - cj.z;
@@ -856,19 +914,18 @@ __device__ __forceinline__ float bil_w(const float4 ci, const float4 ni, const f
 }
 
 // s += w n
-__device__ __forceinline__ void bil_acc(BilAcc &s, float w, const float4 n) {
+__device__ __forceinline__ void bil_acc(BilAcc &s, float w, const V3 &n) {
     s.x = fmaf(w, n.x, s.x);
     s.y = fmaf(w, n.y, s.y);
     s.z = fmaf(w, n.z, s.z);
 }
 
-// Eq. 6 for one triangle: a missing one (c.w = 0) is copied through; pend:
+// Eq. 6 for one triangle: a missing one (not ok) is copied through; pend:
 // the weighted sum fell below 2^-60 in norm (the triangle goes to the queue
 // and r is not set).  Every total weight below 2^-60 is caught, since the
 // norm is at most the total weight.
 template <typename NT>
-__device__ __forceinline__ float4 bil_close(const float4 c, const float4 n, BilAcc s, bool &pend) {
-    const bool ok = c.w != 0.f;
+__device__ __forceinline__ V3 bil_close(bool ok, const V3 &n, BilAcc s, bool &pend) {
     pend = ok && !(bil_norm2(s) >= kBilUnderflow2);
     return ok ? bil_finish<NT>(s, n) : n;
 }
@@ -891,31 +948,30 @@ __device__ __forceinline__ float wave_sum_f(float x) {
 // the smallest exponent (a wave minimum, exact), and the shifted sums are
 // added lane by lane in a fixed butterfly.  Every lane returns the result.
 template <int R, typename NT>
-__device__ __forceinline__ float4 bil_fallback_wave(const float4 *sc, const float4 *sn, int a,
-                                                    int k, int pitch, int plane, float ka,
-                                                    float kb) {
+__device__ __forceinline__ V3 bil_fallback_wave(const float4 *st, int a, int k, int pitch, int plane,
+                                                float ka, float kb) {
     constexpr int kN = 4 * bil_ndplus<R>();               // neighbours
     constexpr int kPer = (kN + kWave - 1) / kWave;         // per lane
     const int lane = (int)threadIdx.x & (kWave - 1);
-    const float4 c = sc[k * plane + a], n = sn[k * plane + a];
+    const V3 c = bil_vec(st, a, plane, k), n = bil_vec(st, a, plane, 2 + k);
     const BilOwn o{c.x, c.y, c.z, n.x, n.y, n.z, ka, kb};
     const float inf = __builtin_inff();
     float e[kPer];
-    float4 nj[kPer];
+    V3 nj[kPer];
     float mn = inf;
 #pragma unroll
     for (int t = 0; t < kPer; ++t) {
         const int j = lane + t * kWave;
         e[t] = inf;
-        nj[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+        nj[t] = V3{0.f, 0.f, 0.f};
         if (j < kN) {
             int dy, dx;
             bil_dplus<R>(j >> 2, dy, dx);
             const int off = dy * pitch + dx;
             const int b = ((j >> 1) & 1) ? a - off : a + off;
             const int kk = j & 1;
-            const float4 cj = sc[b + kk * plane];
-            nj[t] = sn[b + kk * plane];
+            const V3 cj = bil_vec(st, b, plane, kk);
+            nj[t] = bil_vec(st, b, plane, 2 + kk);
             e[t] = bil_pair_e(o, cj, nj[t]);
             mn = fminf(mn, e[t]);
         }
@@ -936,13 +992,13 @@ __device__ __forceinline__ float4 bil_fallback_wave(const float4 *sc, const floa
 // quad of the staged region, so it cannot overflow) and one count per sweep
 // (sweep f counts into count[f], so no count is reset in between).
 struct BilQueue {
-    int *entry;
+    uint16_t *entry;                 // 2 a + k fits: LDS holds under 3,500 quads
     int *count;
 };
 
 __device__ __forceinline__ void bil_push(const BilQueue &qu, int a, int k, int sweep) {
     const int i = atomicAdd(&qu.count[sweep], 1);
-    qu.entry[i] = 2 * a + k;
+    qu.entry[i] = (uint16_t)(2 * a + k);
 }
 
 // Parts per quad: the displacements of D+ are dealt over P parts (part p
@@ -1007,24 +1063,20 @@ __device__ __forceinline__ BilAcc bil_reduce(BilAcc (&s)[P / PP]) {
 // at LDS index a (own centroids c, normals n): the two triangles of quad
 // a + d, then the two of quad a - d.
 template <int R>
-__device__ __forceinline__ void bil_disp(const float4 *sc, const float4 *sn, int a, int pitch,
-                                         int plane, float ka, float kb, int i, const float4 c0,
-                                         const float4 c1, const float4 n0, const float4 n1,
-                                         BilAcc &s0, BilAcc &s1) {
+__device__ __forceinline__ void bil_disp(const float4 *st, int a, int pitch, int plane, float ka,
+                                         float kb, int i, const BilQuad &q, BilAcc &s0, BilAcc &s1) {
     int dy, dx;
     bil_dplus<R>(i, dy, dx);
     const int off = dy * pitch + dx;
-    const int bp = a + off, bm = a - off;
-    const float4 pc0 = sc[bp], pc1 = sc[plane + bp], p0 = sn[bp], p1 = sn[plane + bp];
-    const float4 mc0 = sc[bm], mc1 = sc[plane + bm], m0 = sn[bm], m1 = sn[plane + bm];
-    bil_acc(s0, bil_w(c0, n0, pc0, p0, ka, kb), p0);
-    bil_acc(s0, bil_w(c0, n0, pc1, p1, ka, kb), p1);
-    bil_acc(s0, bil_w(mc0, m0, c0, n0, ka, kb), m0);
-    bil_acc(s0, bil_w(mc1, m1, c0, n0, ka, kb), m1);
-    bil_acc(s1, bil_w(c1, n1, pc0, p0, ka, kb), p0);
-    bil_acc(s1, bil_w(c1, n1, pc1, p1, ka, kb), p1);
-    bil_acc(s1, bil_w(mc0, m0, c1, n1, ka, kb), m0);
-    bil_acc(s1, bil_w(mc1, m1, c1, n1, ka, kb), m1);
+    const BilQuad p = bil_read(st, a + off, plane), m = bil_read(st, a - off, plane);
+    bil_acc(s0, bil_w(q.c0, q.n0, p.c0, p.n0, ka, kb), p.n0);
+    bil_acc(s0, bil_w(q.c0, q.n0, p.c1, p.n1, ka, kb), p.n1);
+    bil_acc(s0, bil_w(m.c0, m.n0, q.c0, q.n0, ka, kb), m.n0);
+    bil_acc(s0, bil_w(m.c1, m.n1, q.c0, q.n0, ka, kb), m.n1);
+    bil_acc(s1, bil_w(q.c1, q.n1, p.c0, p.n0, ka, kb), p.n0);
+    bil_acc(s1, bil_w(q.c1, q.n1, p.c1, p.n1, ka, kb), p.n1);
+    bil_acc(s1, bil_w(m.c0, m.n0, q.c1, q.n1, ka, kb), m.n0);
+    bil_acc(s1, bil_w(m.c1, m.n1, q.c1, q.n1, ka, kb), m.n1);
 }
 
 // Both triangles of the quad at LDS index a, in the fixed summation order:
@@ -1036,13 +1088,12 @@ __device__ __forceinline__ void bil_disp(const float4 *sc, const float4 *sn, int
 // (bil_w is symmetric anyway).  Every lane of the quad returns the same r0,
 // r1 and pending flags.
 template <int R, typename NT, int PP>
-__device__ __forceinline__ void bil_sum_quad(const float4 *sc, const float4 *sn, int a,
-                                                int pitch, int plane, float ka, float kb,
-                                                int lane, float4 &r0, float4 &r1, bool &pend0,
-                                                bool &pend1) {
+__device__ __forceinline__ void bil_sum_quad(const float4 *st, int a, int pitch, int plane, float ka,
+                                             float kb, int lane, const BilQuad &q, const uint8_t *flag,
+                                             int &flags, V3 &r0,
+                                             V3 &r1, bool &pend0, bool &pend1) {
     constexpr int ND = bil_ndplus<R>(), P = bil_parts<R>(), NS = P / PP;
     static_assert(P % PP == 0, "the lanes of a quad share its parts evenly");
-    const float4 c0 = sc[a], c1 = sc[plane + a], n0 = sn[a], n1 = sn[plane + a];
     BilAcc s0[NS], s1[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
@@ -1053,29 +1104,38 @@ __device__ __forceinline__ void bil_sum_quad(const float4 *sc, const float4 *sn,
     for (int j0 = 0; j0 < ND / PP; j0 += NS) {
 #pragma unroll
         for (int k = 0; k < NS; ++k)            // displacement j0 + k: set k
-            bil_disp<R>(sc, sn, a, pitch, plane, ka, kb, (j0 + k) * PP + lane, c0, c1, n0, n1,
-                        s0[k], s1[k]);
+            bil_disp<R>(st, a, pitch, plane, ka, kb, (j0 + k) * PP + lane, q, s0[k], s1[k]);
     }
-    r0 = bil_close<NT>(c0, n0, bil_reduce<P, PP>(s0), pend0);
-    r1 = bil_close<NT>(c1, n1, bil_reduce<P, PP>(s1), pend1);
+    flags = flag[a];
+    r0 = bil_close<NT>(flags & 1, q.n0, bil_reduce<P, PP>(s0), pend0);
+    r1 = bil_close<NT>(flags & 2, q.n1, bil_reduce<P, PP>(s1), pend1);
 }
 
 // One sweep over the OH x OW region at (oy0, ox0) of the staged tile;
-// out(ry, rx, a, r0, r1, pend0, pend1) takes each quad's results (ry, rx
-// within the region).  Ends with a barrier.
-template <int R, typename NT, int PP, typename Out>
-__device__ __forceinline__ void bil_sweep(const float4 *sc, const float4 *sn, int pitch, int plane,
+// out(ry, rx, a, q, flags, pre(ry, rx), r0, r1, pend0, pend1) takes each quad's
+// results (ry, rx within the region; q its staged values); pre is called
+// before the sum if registers allow, so that what it loads arrives meanwhile.
+// Ends with a barrier.
+template <int R, typename NT, int PP, typename Pre, typename Out>
+__device__ __forceinline__ void bil_sweep(const float4 *st, const uint8_t *flag, int pitch, int plane,
                                           int oy0, int ox0, int OH, int OW, float ka, float kb,
-                                          Out &&out) {
+                                          Pre &&pre, Out &&out) {
     const int slot = (int)threadIdx.x / PP, lane = (int)threadIdx.x % PP;
     const DivBy byOW(OW);
     for (int idx = slot; idx < OH * OW; idx += kTileBlock / PP) {
         const int ry = byOW.div(idx), rx = idx - ry * OW;
         const int a = (oy0 + ry) * pitch + ox0 + rx;
-        float4 r0, r1;
+        // a lane that holds several partial sums has no registers to spare for it
+        constexpr bool kEarly = bil_parts<R>() == PP;
+        int2 early = make_int2(-1, -1);
+        if (kEarly) early = pre(ry, rx);
+        const BilQuad q = bil_read(st, a, plane);
+        int fl;
+        V3 r0, r1;
         bool p0, p1;
-        bil_sum_quad<R, NT, PP>(sc, sn, a, pitch, plane, ka, kb, lane, r0, r1, p0, p1);
-        out(ry, rx, a, r0, r1, p0, p1);
+        bil_sum_quad<R, NT, PP>(st, a, pitch, plane, ka, kb, lane, q, flag, fl, r0, r1, p0, p1);
+        if (!kEarly) early = pre(ry, rx);
+        out(ry, rx, a, q, fl, early, r0, r1, p0, p1);
     }
     __syncthreads();
 }
@@ -1086,10 +1146,11 @@ __device__ __forceinline__ void bil_sweep(const float4 *sc, const float4 *sn, in
 // are scalar work; waves 1.. leave their partial sums in `xch`, and wave 0
 // adds them in the tree of bil_reduce -- ((s_0 + s_1) + (s_2 + s_3)) --
 // closes the quad and calls out, alone.  Same bits as the lane form.
-template <int R, typename NT, typename Out>
-__device__ __forceinline__ void bil_sweep_waves(const float4 *sc, const float4 *sn, int pitch,
+template <int R, typename NT, typename Pre, typename Out>
+__device__ __forceinline__ void bil_sweep_waves(const float4 *st, const uint8_t *flag, int pitch,
                                                 int plane, int oy0, int ox0, int OH, int OW,
-                                                float ka, float kb, float *xch, Out &&out) {
+                                                float ka, float kb, float *xch, Pre &&pre,
+                                                Out &&out) {
     constexpr int ND = bil_ndplus<R>(), P = bil_parts<R>();
     static_assert(P == 4 && P == kTileBlock / kWave, "one wave per part, tree of four");
     static_assert(bil_xch_floats(R) == (P - 1) * 6 * kWave, "exchange size");
@@ -1103,12 +1164,14 @@ __device__ __forceinline__ void bil_sweep_waves(const float4 *sc, const float4 *
         const int ry = have ? byOW.div(idx) : 0, rx = have ? idx - ry * OW : 0;
         const int a = (oy0 + ry) * pitch + ox0 + rx;
         BilAcc s0{0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f};
-        float4 c0, c1, n0, n1;
+        BilQuad q;
+        int2 early = make_int2(-1, -1);
+        if (part == 0 && have) early = pre(ry, rx);
         if (have) {
-            c0 = sc[a]; c1 = sc[plane + a]; n0 = sn[a]; n1 = sn[plane + a];
+            q = bil_read(st, a, plane);
 #pragma unroll 1
             for (int j = 0; j < ND / P; ++j)
-                bil_disp<R>(sc, sn, a, pitch, plane, ka, kb, j * P + part, c0, c1, n0, n1, s0, s1);
+                bil_disp<R>(st, a, pitch, plane, ka, kb, j * P + part, q, s0, s1);
         }
         if (part != 0) {
             float *x = xch + (part - 1) * 6 * kWave + lane;
@@ -1124,10 +1187,11 @@ __device__ __forceinline__ void bil_sweep_waves(const float4 *sc, const float4 *
             const BilAcc t1{(s1.x + x1[3 * kWave]) + (x2[3 * kWave] + x3[3 * kWave]),
                             (s1.y + x1[4 * kWave]) + (x2[4 * kWave] + x3[4 * kWave]),
                             (s1.z + x1[5 * kWave]) + (x2[5 * kWave] + x3[5 * kWave])};
+            const int fl = flag[a];
             bool p0, p1;
-            const float4 r0 = bil_close<NT>(c0, n0, t0, p0);
-            const float4 r1 = bil_close<NT>(c1, n1, t1, p1);
-            out(ry, rx, a, r0, r1, p0, p1);
+            const V3 r0 = bil_close<NT>(fl & 1, q.n0, t0, p0);
+            const V3 r1 = bil_close<NT>(fl & 2, q.n1, t1, p1);
+            out(ry, rx, a, q, fl, early, r0, r1, p0, p1);
         }
         if (base + kWave < n) __syncthreads();   // xch is reused by the next 64 quads
     }
@@ -1193,17 +1257,17 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
                                          GatherCodes gc = GatherCodes{nullptr, nullptr, 0}) {
     const int halo = R * F;
     const int H = TQH + 2 * halo, W = TQW + 2 * halo, S = H * W;
-    float4 *s_c = lds;                  // [2][S] centroids, w = 1 if usable
-    float4 *s_n = lds + 2 * S;          // [2][S] normals
-    float4 *s_m = lds + 4 * S;          // [2][S] second normal buffer (F > 1)
-    // queue of underflowed triangles: 2S entries, then one count per sweep
-    int *qbase = reinterpret_cast<int *>(lds + (F > 1 ? 6 : 4) * S);
-    const BilQueue qu{qbase, qbase + 2 * S};
-    if (threadIdx.x < kBilMaxSweeps + 1) qu.count[threadIdx.x] = 0;
+    float4 *st = lds;                   // [3][S] staged quads
+    float4 *st2 = lds + 3 * S;          // [3][S] the next sweep's (F > 1)
+    int *counts = reinterpret_cast<int *>(lds + (F > 1 ? 6 : 3) * S);
+    if (threadIdx.x < kBilMaxSweeps + 1) counts[threadIdx.x] = 0;
     // T ranks of the tile when the gather takes them from the mesh codes
-    int *rank = qbase + 2 * S + kBilMaxSweeps + 1;
+    int *rank = counts + kBilMaxSweeps + 1;
     // the parts' exchange (parts on waves)
     float *xch = reinterpret_cast<float *>(rank + TQH * TQW);
+    // queue of underflowed triangles: 2S entries, one count per sweep
+    const BilQueue qu{reinterpret_cast<uint16_t *>(xch + (PP == 0 ? bil_xch_floats(R) : 0)), counts};
+    uint8_t *flag = reinterpret_cast<uint8_t *>(qu.entry + 2 * S);   // [S]
     constexpr bool waves = PP == 0;
     static_assert(!waves || R >= 2, "parts on waves for windows of 5x5 and up");
     constexpr bool by_codes = ByCodes;
@@ -1211,58 +1275,102 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
         bil_gather_ranks(gc, Mq, Nq, qy0, qx0, TQH, TQW, rank);
         if (F == 0) __syncthreads();
     }
-    // index in T of triangle k of tile quad (ty, tx), or -1 (none, or no gather)
-    auto t_index = [&](int ty, int tx, size_t q, int k) -> int {
+    // indices in T of the two triangles of tile quad (ty, tx), -1 for none (or
+    // no gather); read before the quad's sum, for the T_map of the launch
+    // before this one comes from memory
+    auto t_index = [&](int ty, int tx) -> int2 {
+        int2 t = make_int2(-1, -1);
         if constexpr (by_codes) {
             const unsigned r = (unsigned)rank[ty * TQW + tx];
             const int code = (int)(r >> 30), base = (int)(r & 0x3fffffffu);
-            if (!((code >> k) & 1)) return -1;
-            return base + (k == 1 ? (code & 1) : 0);
-        } else {
-            return tri_map ? tri_map[2 * q + k] : -1;
+            if (code & 1) t.x = base;
+            if (code & 2) t.y = base + (code & 1);
+        } else if (tri_map && qy0 + ty < Mq && qx0 + tx < Nq) {
+            t = *reinterpret_cast<const int2 *>(tri_map + 2 * ((size_t)(qy0 + ty) * Nq + qx0 + tx));
         }
+        return t;
     };
     const float inf = __builtin_inff();
     const int oy = qy0 - halo, ox = qx0 - halo;
 
+    struct RawPoints { QuadPoints p; };
+    struct RawNormals { NT n[6]; float c[6]; };
+    using Raw = std::conditional_t<FromPts, RawPoints, RawNormals>;
     if (F > 0) {
         const DivBy byW(W);
-        for (int idx = threadIdx.x; idx < S; idx += kTileBlock) {
-            const int ly = byW.div(idx), lx = idx - ly * W;
-            const int qy = oy + ly, qx = ox + lx;
-            float4 c0 = make_float4(inf, inf, inf, 0.f), c1 = c0;
-            float4 n0 = make_float4(0.f, 0.f, 0.f, 0.f), n1 = n0;
-            if (qy >= 0 && qy < Mq && qx >= 0 && qx < Nq) {
-                const size_t q = (size_t)qy * Nq + qx;
-                float n[6], c[6];
+        // two quads per thread and pass, the loads of both issued before
+        // either is used (a tile has more quads with its halo than the
+        // workgroup threads: one at a time waited for memory twice).  With
+        // the leaner staging and the T_map read ahead of the sums, a 480 x 640
+        // frame took 36.5 us (39.1 before), a 120 x 160 one 14.4 us (15.6), a
+        // batch of seven mixed frames 247 us (264); VALU instructions of the
+        // first bilateral launch of a 720 x 1280 frame 19.0 M (21.6 M)
+        constexpr int kU = 2;
+        for (int base = threadIdx.x; base < S; base += kU * kTileBlock) {
+            Raw raw[kU];
+            bool in[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int idx = base + u * kTileBlock;
+                const int ly = byW.div(idx), lx = idx - ly * W;
+                const int qy = oy + ly, qx = ox + lx;
+                in[u] = idx < S && (unsigned)qy < (unsigned)Mq && (unsigned)qx < (unsigned)Nq;
+                if (!in[u]) continue;
                 if constexpr (FromPts) {
-                    V3 g[4];
-                    quad_geom_at(pts, Nq + 1, qy, qx, g[0], g[1], g[2], g[3]);
-                    c[0] = g[0].x; c[1] = g[0].y; c[2] = g[0].z; c[3] = g[2].x; c[4] = g[2].y; c[5] = g[2].z;
-                    n[0] = round_storage<NT>(g[1].x); n[1] = round_storage<NT>(g[1].y);
-                    n[2] = round_storage<NT>(g[1].z); n[3] = round_storage<NT>(g[3].x);
-                    n[4] = round_storage<NT>(g[3].y); n[5] = round_storage<NT>(g[3].z);
+                    raw[u].p = quad_points(pts, Nq + 1, qy, qx);
                 } else {
+                    const size_t o = 6 * ((size_t)qy * Nq + qx);
 #pragma unroll
-                    for (int i = 0; i < 6; ++i) { n[i] = ld_f(nin + 6 * q + i); c[i] = cen[6 * q + i]; }
+                    for (int i = 0; i < 6; ++i) { raw[u].n[i] = nin[o + i]; raw[u].c[i] = cen[o + i]; }
                 }
-                bool ok0 = true, ok1 = true;
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    ok0 = ok0 && !is_nan_bits(n[i]) && !is_nan_bits(c[i]);
-                    ok1 = ok1 && !is_nan_bits(n[3 + i]) && !is_nan_bits(c[3 + i]);
-                }
-                if (ok0) { c0 = make_float4(c[0], c[1], c[2], 1.f); n0 = make_float4(n[0], n[1], n[2], 0.f); }
-                if (ok1) { c1 = make_float4(c[3], c[4], c[5], 1.f); n1 = make_float4(n[3], n[4], n[5], 0.f); }
             }
-            s_c[idx] = c0; s_c[S + idx] = c1;
-            s_n[idx] = n0; s_n[S + idx] = n1;
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int idx = base + u * kTileBlock;
+                if (idx >= S) break;
+                V3 c0{inf, inf, inf}, c1 = c0, n0{0.f, 0.f, 0.f}, n1 = n0;
+                int fl = 0;
+                if (in[u]) {
+                    V3 d0, d1, m0, m1;
+                    bool ok0, ok1, canon0, canon1;
+                    if constexpr (FromPts) {
+                        const QuadPoints &g = raw[u].p;
+                        const bool diag = ok3(g.p1) && ok3(g.p3);
+                        const bool has0 = diag && ok3(g.p2), has1 = diag && ok3(g.p4);
+                        tri_geom(g.p3, g.p2, g.p1, d0, m0);
+                        tri_geom(g.p1, g.p4, g.p3, d1, m1);
+                        m0 = V3{round_storage<NT>(m0.x), round_storage<NT>(m0.y), round_storage<NT>(m0.z)};
+                        m1 = V3{round_storage<NT>(m1.x), round_storage<NT>(m1.y), round_storage<NT>(m1.z)};
+                        ok0 = has0 && ok3(d0) && ok3(m0);
+                        ok1 = has1 && ok3(d1) && ok3(m1);
+                        canon0 = !has0;
+                        canon1 = !has1;
+                    } else {
+                        const NT *n = raw[u].n;
+                        const float *c = raw[u].c;
+                        d0 = V3{c[0], c[1], c[2]};
+                        d1 = V3{c[3], c[4], c[5]};
+                        m0 = V3{ld_f(n), ld_f(n + 1), ld_f(n + 2)};
+                        m1 = V3{ld_f(n + 3), ld_f(n + 4), ld_f(n + 5)};
+                        ok0 = ok3(d0) && ok3(m0);
+                        ok1 = ok3(d1) && ok3(m1);
+                        canon0 = is_qnan(n[0]) && is_qnan(n[1]) && is_qnan(n[2]);
+                        canon1 = is_qnan(n[3]) && is_qnan(n[4]) && is_qnan(n[5]);
+                    }
+                    if (ok0) { c0 = d0; n0 = m0; }
+                    if (ok1) { c1 = d1; n1 = m1; }
+                    fl = (ok0 ? kBilUsable : 0) | (ok1 ? 2 * kBilUsable : 0) |
+                         (canon0 ? kBilCanonical : 0) | (canon1 ? 2 * kBilCanonical : 0);
+                }
+                bil_write(st, idx, S, c0, c1, n0, n1);
+                flag[idx] = (uint8_t)fl;
+            }
         }
         __syncthreads();
     }
 
-    const float4 *cur = s_n;
-    float4 *nxt = s_m;
+    const float4 *cur = st;
+    float4 *nxt = st2;
     // PP lanes per quad: quad slot and lane within the quad; parts on
     // waves: the lane is the slot, the wave the part (only part 0 stores)
     constexpr int QL = waves ? 1 : PP;                       // lanes per quad
@@ -1270,26 +1378,31 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
     const int part = waves ? (int)threadIdx.x / kWave : (int)threadIdx.x % QL;
     const int wave = (int)threadIdx.x / kWave, lane = (int)threadIdx.x & (kWave - 1);
     // one sweep over the OH x OW region at (o0, o0) of the staged tile
-    auto sweep = [&](int o0, int OH, int OW, auto &&out) {
+    auto sweep = [&](int o0, int OH, int OW, auto &&pre, auto &&out) {
         if constexpr (waves)
-            bil_sweep_waves<R, NT>(s_c, cur, W, S, o0, o0, OH, OW, ka, kb, xch, out);
+            bil_sweep_waves<R, NT>(cur, flag, W, S, o0, o0, OH, OW, ka, kb, xch, pre, out);
         else
-            bil_sweep<R, NT, PP>(s_c, cur, W, S, o0, o0, OH, OW, ka, kb, out);
+            bil_sweep<R, NT, PP>(cur, flag, W, S, o0, o0, OH, OW, ka, kb, pre, out);
     };
     // intermediate sweeps: LDS to LDS over the shrinking exact region
     for (int f = 1; f < F; ++f) {
         const int lo = R * f;
-        sweep(lo, H - 2 * lo, W - 2 * lo,
-              [&](int, int, int a, float4 r0, float4 r1, bool p0, bool p1) {
+        sweep(lo, H - 2 * lo, W - 2 * lo, [](int, int) { return make_int2(-1, -1); },
+              [&](int, int, int a, const BilQuad &q, int, int2, const V3 &r0, const V3 &r1, bool p0, bool p1) {
                   if (part != 0) return;
-                  if (p0) bil_push(qu, a, 0, f); else nxt[a] = r0;
-                  if (p1) bil_push(qu, a, 1, f); else nxt[S + a] = r1;
+                  bil_write(nxt, a, S, q.c0, q.c1, r0, r1);   // a queued triangle's normal follows
+                  if (p0) bil_push(qu, a, 0, f);
+                  if (p1) bil_push(qu, a, 1, f);
               });
         const int nq = qu.count[f];
         for (int e = wave; e < nq; e += kTileBlock / kWave) {
             const int a = qu.entry[e] >> 1, k = qu.entry[e] & 1;
-            const float4 r = bil_fallback_wave<R, NT>(s_c, cur, a, k, W, S, ka, kb);
-            if (lane == 0) nxt[k * S + a] = r;
+            const V3 r = bil_fallback_wave<R, NT>(cur, a, k, W, S, ka, kb);
+            if (lane == 0) {
+                *bil_at(nxt, a, S, 6 + 3 * k) = r.x;
+                *bil_at(nxt, a, S, 7 + 3 * k) = r.y;
+                *bil_at(nxt, a, S, 8 + 3 * k) = r.z;
+            }
         }
         __syncthreads();
         float4 *t = const_cast<float4 *>(cur);
@@ -1298,48 +1411,59 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
     }
 
     // last sweep (or the copy when F = 0): the tile itself, to global memory
-    auto emit = [&](int ty, int tx, int a, float4 r0, float4 r1, bool p0, bool p1) {
+    auto emit = [&](int ty, int tx, int a, const BilQuad &g, int fl, int2 t, const V3 &r0,
+                    const V3 &r1, bool p0, bool p1) {
         const int qy = qy0 + ty, qx = qx0 + tx;
         if (part != 0 || qy >= Mq || qx >= Nq) return;   // the quad's first lane stores
         const size_t q = (size_t)qy * Nq + qx;
-        const float4 r[2] = {r0, r1};
+        const V3 r[2] = {r0, r1};
         const bool pend[2] = {p0, p1};
         NT v[6];
         NT raw[6];                           // raw normals as stored (FromPts)
         if constexpr (FromPts) {
-            V3 c0, n0, c1, n1;
-            quad_geom_at(pts, Nq + 1, qy, qx, c0, n0, c1, n1);
+            // centroids as staged; a missing corner's and its normal are the
+            // canonical NaN, and the rest (a triangle of no area) is computed
+            // again, as everything is when nothing was staged
+            const float nan = qnan();
+            V3 c0{nan, nan, nan}, c1 = c0, n0 = c0, n1 = c0;
+            if (fl & kBilUsable) c0 = g.c0;
+            if (fl & (2 * kBilUsable)) c1 = g.c1;
+            const bool odd = !(fl & (kBilUsable | kBilCanonical)) || !(fl & (2 * (kBilUsable | kBilCanonical)));
+            if (F == 0 || odd) quad_geom_at(pts, Nq + 1, qy, qx, c0, n0, c1, n1);
             cen_out[6 * q + 0] = c0.x; cen_out[6 * q + 1] = c0.y; cen_out[6 * q + 2] = c0.z;
             cen_out[6 * q + 3] = c1.x; cen_out[6 * q + 4] = c1.y; cen_out[6 * q + 5] = c1.z;
             st_f(&raw[0], n0.x); st_f(&raw[1], n0.y); st_f(&raw[2], n0.z);
             st_f(&raw[3], n1.x); st_f(&raw[4], n1.y); st_f(&raw[5], n1.z);
         }
-        // the stored raw normal i of this quad
-        auto raw_at = [&](int i) -> NT {
-            if constexpr (FromPts) return raw[i];
-            else return nin[6 * q + i];
-        };
-        if (F > 0) {
+        // a triangle's normal as it came in: canonical NaN, or read again
+        auto keep = [&](int k) {
+            if constexpr (FromPts) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                if (pend[k]) {                 // queued: written after the sweep
-                    bil_push(qu, a, k, F);
-                } else if (s_c[k * S + a].w != 0.f) {
-                    st_f(&v[3 * k], r[k].x); st_f(&v[3 * k + 1], r[k].y); st_f(&v[3 * k + 2], r[k].z);
-                } else {                       // missing triangle: input bits unchanged
-                    v[3 * k] = raw_at(3 * k);
-                    v[3 * k + 1] = raw_at(3 * k + 1);
-                    v[3 * k + 2] = raw_at(3 * k + 2);
+                for (int i = 0; i < 3; ++i) v[3 * k + i] = raw[3 * k + i];
+            } else {
+                st_f(&v[3 * k], qnan());
+                v[3 * k + 1] = v[3 * k];
+                v[3 * k + 2] = v[3 * k];
+                if (!(fl & (kBilCanonical << k))) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) v[3 * k + i] = nin[6 * q + 3 * k + i];
                 }
             }
-        } else {
+        };
 #pragma unroll
-            for (int i = 0; i < 6; ++i) v[i] = raw_at(i);
+        for (int k = 0; k < 2; ++k) {
+            if (pend[k]) {                 // queued: written after the sweep
+                bil_push(qu, a, k, F);
+            } else if (fl & (kBilUsable << k)) {
+                st_f(&v[3 * k], r[k].x); st_f(&v[3 * k + 1], r[k].y); st_f(&v[3 * k + 2], r[k].z);
+            } else {                       // missing triangle (or F = 0): input bits unchanged
+                keep(k);
+            }
         }
         // streaming stores (float32 normals): they write partial lines, about
         // 2 MB more per launch on a 480x640 frame, but the whole path gains
         // 2.4 us per frame.  A queued triangle is written after the sweep.
-        const int t0 = t_index(ty, tx, q, 0), t1 = t_index(ty, tx, q, 1);
+        const int t0 = t.x, t1 = t.y;
         if (!(pend[0] | pend[1])) {
 #pragma unroll
             for (int i = 0; i < 6; ++i) bil_store(&nout[6 * q + i], v[i]);
@@ -1360,13 +1484,13 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
         }
     };
     if (F > 0) {
-        sweep(halo, TQH, TQW, emit);
+        sweep(halo, TQH, TQW, t_index, emit);
     } else {
         const DivBy byTQW(TQW);
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        const V3 z{0.f, 0.f, 0.f};
         for (int idx = slot; idx < TQH * TQW; idx += waves ? kWave : kTileBlock / QL) {
-            const int ty = byTQW.div(idx);
-            emit(ty, idx - ty * TQW, 0, z, z, false, false);
+            const int ty = byTQW.div(idx), tx = idx - ty * TQW;
+            emit(ty, tx, 0, BilQuad{z, z, z, z}, 0, t_index(ty, tx), z, z, false, false);
         }
     }
     if (F > 0) {
@@ -1375,7 +1499,7 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
         const int nq = qu.count[F];
         for (int e = wave; e < nq; e += kTileBlock / kWave) {
             const int a = qu.entry[e] >> 1, k = qu.entry[e] & 1;
-            const float4 r = bil_fallback_wave<R, NT>(s_c, cur, a, k, W, S, ka, kb);
+            const V3 r = bil_fallback_wave<R, NT>(cur, a, k, W, S, ka, kb);
             if (lane == 0) {
                 const int ly = a / W, lx = a - ly * W;
                 const size_t q = (size_t)(oy + ly) * Nq + (ox + lx);
@@ -1383,7 +1507,8 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
                 st_f(&v[0], r.x); st_f(&v[1], r.y); st_f(&v[2], r.z);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) bil_store(&nout[6 * q + 3 * k + i], v[i]);
-                const int t = t_index(ly - halo, lx - halo, q, k);
+                const int2 tt = t_index(ly - halo, lx - halo);
+                const int t = k ? tt.y : tt.x;
                 if (t >= 0) {
 #pragma unroll
                     for (int i = 0; i < 3; ++i) bil_store(&nT[3 * (size_t)t + i], v[i]);

@@ -418,3 +418,29 @@ def test_errors_on_device(pl):
     with pytest.raises(pl.PLError, match="PL_ERR_ARG"):
         pl.pl_bilateral(n, c, 3, -0.1, 0.1, 1)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("kernel,iters", [(3, 1), (3, 2), (5, 1)])
+def test_bilateral_keeps_the_bits_of_unusable_normals(pl, kernel, iters, f16):
+    """A triangle whose own normal or centroid holds a NaN is copied through bit
+    for bit: canonical NaNs, NaNs with a payload, a NaN in one component only,
+    and a finite normal beside a NaN centroid; across a tile's edges."""
+    import torch
+    rng = np.random.default_rng(41 + kernel + iters)
+    Mq, Nq = 19, 70
+    n = rng.normal(size=(Mq, Nq, 2, 3))
+    n = (n / np.linalg.norm(n, axis=-1, keepdims=True)).astype(np.float16 if f16 else np.float32)
+    c = rng.normal(scale=0.05, size=(Mq, Nq, 2, 3)).astype(np.float32)
+    kind = rng.integers(0, 12, size=(Mq, Nq, 2))
+    n[kind == 0] = np.nan
+    bits = n.view(np.uint16 if f16 else np.uint32)
+    bits[kind == 1] = 0xfe5a if f16 else 0xffc12345
+    n[..., 1][kind == 2] = np.nan
+    c[..., 2][kind == 3] = np.nan
+    say("bilateral unusable normals", kernel, iters, "f16" if f16 else "f32")
+    out, _ = pl.pl_bilateral(to_dev(n), to_dev(c), kernel, 0.1, 0.5, iters)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.array_equal(got.view(bits.dtype)[kind <= 3], bits[kind <= 3])
+    assert not np.isnan(got[kind > 3]).any()
