@@ -5,15 +5,16 @@
 // Plan (pl_batch_create, host): validates every frame, lays out a workspace
 // holding one descriptor per frame, the per-pass source/destination tables
 // of the multi-sweep stages, each stage's per-frame tile counts and the
-// per-frame scratch (validity codes, row counts, ping-pong buffers), uploads
+// per-frame scratch (validity masks, segment counts, ping-pong buffers), uploads
 // the tables once and sizes each launch for all frames active.
 //
 // Run (pl_batch_run, device only, graph-capturable), over the frames whose
 // entry in a device-side activity mask is non-zero:
 //   k_batch_prepare    one workgroup per stage: prefix sums of the active
 //                      frames' tile counts (the stage's tile queue)
-//   k_batch_mesh_count tiles = (frame, quad row)        -> codes, row counts
-//   k_batch_mesh_emit  tiles = (frame, quad row)        -> T_map, T, HE, |T|
+//   k_batch_mesh_count tiles = (frame, 256-quad segment) -> masks, counts
+//   k_batch_mesh_sums  (plans with a frame of more than kMeshSegMax segments)
+//   k_batch_mesh_emit  tiles = (frame, 256-quad segment) -> T_map, T, HE, |T|
 //   k_batch_laplacian  one launch per sweep pass, tiles = (frame, point tile)
 //   k_batch_bilateral  one launch per sweep pass, tiles = (frame, quad tile);
 //                      the first pass computes the raw normals and centroids
@@ -58,9 +59,8 @@ struct BFrame {
     float *pts_out, *lap_tmp;
     void *normals, *bil_tmp;
     float *centroids;
-    uint8_t *tri_valid, *codes;
-    int32_t *tri_map, *triangles, *halfedges, *n_tri;
-    int *row_count;
+    MeshArgs mesh;
+    int32_t *tri_map, *triangles, *n_tri;
     void *normals_T;
     int M, N, Mq, Nq;
     int Rl, Rb;
@@ -147,18 +147,23 @@ __device__ __forceinline__ bool queue_tile(const QueueDev &Q, int n, int *s_star
 __global__ __launch_bounds__(kTileBlock) void k_batch_mesh_count(const BFrame *__restrict__ fr,
                                                                  QueueDev Q, int n) {
     PL_QUEUE_TILE(Q, n, t)
-    __shared__ MeshCountRowLds L;
-    const BFrame &f = fr[t.x];
-    mesh_count_row(f.pts, f.N, t.y, f.codes, f.tri_valid, f.row_count, L);
+    mesh_count_seg(fr[t.x].mesh, t.y);
 }
 
 __global__ __launch_bounds__(kTileBlock) void k_batch_mesh_emit(const BFrame *__restrict__ fr,
                                                                 QueueDev Q, int n) {
     PL_QUEUE_TILE(Q, n, t)
-    const BFrame &f = fr[t.x];
-    __shared__ MeshEmitRowLds L;
-    mesh_emit_row(f.codes, f.row_count, f.Mq, f.N, t.y, f.tri_map, f.triangles, f.halfedges,
-                  2 * f.Mq * f.Nq, f.n_tri, L);
+    const MeshArgs &m = fr[t.x].mesh;
+    if (mesh_segments((size_t)m.Q) > kMeshSegMax) mesh_emit_seg<true>(m, t.y);
+    else mesh_emit_seg<false>(m, t.y);
+}
+
+// Segment sums of the frames that need them, one workgroup per frame of the
+// plan (a frame left out of the run has its own, unused, sums summed again).
+__global__ __launch_bounds__(kMeshSumBlock) void k_batch_mesh_sums(const BFrame *__restrict__ fr) {
+    const MeshArgs &m = fr[blockIdx.x].mesh;
+    const int S = mesh_segments((size_t)m.Q);
+    if (S > kMeshSegMax) mesh_scan_segs(m.seg, m.sums, S);
 }
 
 template <int R>
@@ -246,6 +251,7 @@ struct pl_batch_s {
     size_t off_frames = 0, off_queues = 0, off_ones = 0;
     int n_queues = 0;              // stage queues with any tile, in table order
     pl::HostQueue mc, me;          // mesh count, mesh emit
+    bool mesh_sums = false;        // some frame's segments are summed by a launch
     pl::HostQueue grp;             // group assignment (frames with groups)
     std::vector<pl::Pass> lap, bil;
     std::map<int, hipGraphExec_t> graphs;   // bound on active frames -> captured run
@@ -298,8 +304,8 @@ size_t batch_layout(const pl_frame *frames, int n, pl_dtype ndt, pl_batch_s *pla
     for (int i = 0; i < n; ++i) {
         const pl_frame &f = frames[i];
         const int Mq = f.M - 1, Nq = f.N - 1;
-        b.mc.count[i] = Mq;
-        b.me.count[i] = Mq;
+        b.mc.count[i] = b.me.count[i] = mesh_segments((size_t)Mq * Nq);
+        b.mesh_sums |= b.mc.count[i] > kMeshSegMax;
         const TileCfg cl = tile_cfg(kStageBatchLaplacian, f.kernel_lap / 2);
         const TileCfg cb = tile_cfg(kStageBatchBilateral, f.kernel_bil / 2);
         const int ltiles = ((f.N + cl.tw - 1) / cl.tw) * ((f.M + cl.th - 1) / cl.th);
@@ -327,13 +333,11 @@ size_t batch_layout(const pl_frame *frames, int n, pl_dtype ndt, pl_batch_s *pla
     const size_t table_end = L.off;
     // per-frame scratch
     std::vector<BFrame> bf(n);
-    std::vector<size_t> o_codes(n), o_rows(n), o_lap(n, 0), o_bil(n, 0);
+    std::vector<size_t> o_mesh(n), o_lap(n, 0), o_bil(n, 0);
     for (int i = 0; i < n; ++i) {
         const pl_frame &f = frames[i];
-        const size_t Q = (size_t)(f.M - 1) * (f.N - 1);
-        const size_t T = 2 * Q;
-        o_codes[i] = L.take(Q);
-        o_rows[i] = L.take(sizeof(int) * (f.M - 1));
+        const size_t T = 2 * (size_t)(f.M - 1) * (f.N - 1);
+        o_mesh[i] = L.take(mesh_workspace(f.M, f.N));
         const int lp = passes_for(f.iters_lap, tile_cfg(kStageBatchLaplacian, f.kernel_lap / 2).fuse);
         const int bp = passes_for(f.iters_bil, tile_cfg(kStageBatchBilateral, f.kernel_bil / 2).fuse);
         if (lp > 1) o_lap[i] = L.take(12 * (size_t)f.M * f.N);
@@ -346,18 +350,16 @@ size_t batch_layout(const pl_frame *frames, int n, pl_dtype ndt, pl_batch_s *pla
     for (int i = 0; i < n; ++i) {
         const pl_frame &f = frames[i];
         BFrame &d = bf[i];
-        d.codes = base + o_codes[i];
-        d.row_count = reinterpret_cast<int *>(base + o_rows[i]);
+        d.mesh = mesh_args(f.pts, f.M, f.N, f.tri_valid, f.tri_map, f.triangles, f.halfedges,
+                           2 * (f.M - 1) * (f.N - 1), f.n_tri, base + o_mesh[i]);
         d.lap_tmp = o_lap[i] ? reinterpret_cast<float *>(base + o_lap[i]) : nullptr;
         d.bil_tmp = o_bil[i] ? static_cast<void *>(base + o_bil[i]) : nullptr;
         d.pts = f.pts;
         d.pts_out = f.pts_out;
         d.normals = f.normals;
         d.centroids = f.centroids;
-        d.tri_valid = f.tri_valid;
         d.tri_map = f.tri_map;
         d.triangles = f.triangles;
-        d.halfedges = f.halfedges;
         d.n_tri = f.n_tri;
         d.normals_T = f.normals_T;
         d.M = f.M; d.N = f.N; d.Mq = f.M - 1; d.Nq = f.N - 1;
@@ -489,6 +491,10 @@ pl_status run_batch(const pl_batch_s &b, const uint8_t *active, hipStream_t s, i
     if (pl_status st = hip_check(hipGetLastError(), "k_batch_prepare")) return st;
     k_batch_mesh_count<<<bounded_grid(b.mc, bound), kTileBlock, 0, s>>>(fr, dev_queue(b, b.mc), n);
     if (pl_status st = hip_check(hipGetLastError(), "k_batch_mesh_count")) return st;
+    if (b.mesh_sums) {
+        k_batch_mesh_sums<<<n, kMeshSumBlock, 0, s>>>(fr);
+        if (pl_status st = hip_check(hipGetLastError(), "k_batch_mesh_sums")) return st;
+    }
     k_batch_mesh_emit<<<bounded_grid(b.me, bound), kTileBlock, 0, s>>>(fr, dev_queue(b, b.me), n);
     if (pl_status st = hip_check(hipGetLastError(), "k_batch_mesh_emit")) return st;
     for (const Pass &p : b.lap) {

@@ -13,12 +13,6 @@ namespace pl {
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kNumXcd = 8;       // MI355X: 8 accelerator complex dies, 32 CUs each
 
-// NaN test on the bit pattern: exponent all ones, mantissa non-zero.  Immune
-// to any fast-math or finite-math compiler flag.
-__device__ __forceinline__ bool is_nan_bits(float x) {
-    return (__float_as_uint(x) & 0x7fffffffu) > 0x7f800000u;
-}
-
 // Whether any of three values is NaN: two unordered comparisons (each takes
 // two operands), where three bit-pattern tests take six instructions.  The
 // library is built without any fast-math flag.
@@ -67,21 +61,48 @@ struct DivBy {
     __device__ __forceinline__ int div(int i) const { return (int)__umulhi((unsigned)i, m); }
 };
 
-// Inclusive prefix sum across one 64-wide wavefront.
-__device__ __forceinline__ int wave_inclusive_scan(int x) {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int y = __shfl_up(x, d, kWave);
-        if (lane >= d) x += y;
+// Division of a quad index q < 2^29 (6 Q < 2^31) by a frame-uniform divisor d:
+// with s = 29 + ceil(log2 d) and m = ceil(2^s / d) <= 2^30, q m < 2^59 and the
+// error term q (m d - 2^s) < 2^s, so floor(q / d) = (q m) >> s exactly.
+struct QuadDiv {
+    unsigned m;
+    int s, d;
+    __host__ static QuadDiv by(int d) {
+        int lg = 0;
+        while ((1u << lg) < (unsigned)d) ++lg;
+        const unsigned long long one = 1ull << (29 + lg);
+        return QuadDiv{(unsigned)((one + (unsigned)d - 1) / (unsigned)d), 29 + lg, d};
     }
+    __device__ __forceinline__ int div(int q) const {
+        return (int)(((unsigned long long)(unsigned)q * m) >> s);
+    }
+};
+
+// Inclusive prefix sum across one 64-wide wavefront, every lane active: within
+// rows of 16 lanes by row shifts, then each row's last lane is broadcast into
+// the rows after it (DPP operands: six adds, no trip through LDS).
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);    // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);    // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);    // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);    // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);    // row_bcast:15, rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);    // row_bcast:31, rows 2 and 3
     return x;
 }
 
+// The wavefront's sum (uniform), every lane active.
 __device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, kWave);
-    return x;
+    return __builtin_amdgcn_readlane(wave_inclusive_scan(x), kWave - 1);
+}
+
+// Bits of a 64-bit mask below this lane's.
+__device__ __forceinline__ int bits_below(unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+// This lane's bit of a wave-uniform mask (the mask as it is, for a select).
+__device__ __forceinline__ bool lane_bit(unsigned long long m) {
+    return __builtin_amdgcn_inverse_ballot_w64(m);
 }
 
 // Half storage helpers (normals in PL_F16 mode).

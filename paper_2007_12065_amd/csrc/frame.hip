@@ -8,7 +8,7 @@
 //
 // Launch sequence:
 //   1. the Laplacian's first pass over its point tiles and, in the same
-//      launch, the mesh's validity codes and counts (both read only the
+//      launch, the mesh's validity masks and counts (both read only the
 //      input points);
 //   2. the Laplacian's further passes, then the bilateral passes.  The first
 //      bilateral pass computes the centroids and raw normals of every quad it
@@ -18,19 +18,17 @@
 // The mesh emit (T_map, T, HE) needs every count, so it rides in the second
 // launch.  When that one is the gathering bilateral pass, the gather cannot
 // read T_map (written by the same launch): it ranks each triangle in T
-// from the mesh's codes and segment counts instead (the same numbers), so a
+// from the mesh's masks and segment counts instead (the same numbers), so a
 // 480 x 640 frame whose two bilateral sweeps fuse into one pass takes two
 // launches.
 //
 // A launch that carries mesh work has two kinds of workgroups: the filter's
-// tiles first, then one workgroup per 256-quad row segment of the mesh.
-// (Frames of more than kMeshSegMax segments are meshed by whole quad rows,
-// whose emit body needs more registers than the filters may use; they get
-// pl_mesh_opc's own two launches before the filters, which at that size
-// cost little.)  Each kind is dealt over the eight XCDs on its own (each
+// tiles first, then one workgroup per 256-quad segment of the mesh.  (Frames
+// of more than kMeshSegMax segments need the segments' sums between count and
+// emit; they get pl_mesh_opc's own launches before the filters, which at that
+// size cost little.)  Each kind is dealt over the eight XCDs on its own (each
 // part padded to a multiple of eight workgroups, and xcd_remap_active gives
-// each XCD a contiguous run), and mesh workgroups stage their data in the
-// same dynamic LDS the filter tiles use.
+// each XCD a contiguous run).
 #include "groups.h"
 #include "tiles.h"
 #include "tuning.h"
@@ -41,45 +39,26 @@ namespace {
 
 enum MeshKind { kMeshNone = 0, kMeshCount = 1, kMeshEmit = 2 };
 
-struct MeshJob {
-    const float *pts;
-    uint8_t *codes, *tri_valid;
-    int *counts;
-    int32_t *tri_map, *tris, *he, *n_tri;
-    int cap, Mq, N, S;
-    int units;       // row segments, Mq S
-    int per_group;   // consecutive segments per workgroup (1)
-    int groups;      // mesh workgroups: ceil(units / per_group)
-};
-
 // Mesh workgroups of a launch, padded to whole rounds of the eight XCDs.
-__host__ __device__ inline int mesh_blocks(const MeshJob &mj) {
-    return (mj.groups + kNumXcd - 1) / kNumXcd * kNumXcd;
+__host__ __device__ inline int mesh_blocks(const MeshArgs &m) {
+    return (mesh_segments((size_t)m.Q) + kNumXcd - 1) / kNumXcd * kNumXcd;
 }
 
-template <int Kind>
-__device__ __forceinline__ void mesh_job(const MeshJob &j, int g, float4 *lds) {
-    const int k0 = g * j.per_group;
-    const int k1 = min(k0 + j.per_group, j.units);
-    for (int k = k0; k < k1; ++k) {
-        if constexpr (Kind == kMeshCount)
-            mesh_count_seg(j.pts, j.N, k / j.S, k % j.S, j.S, j.codes, j.tri_valid, j.counts,
-                           *reinterpret_cast<MeshCountSegLds *>(lds));
-        else
-            mesh_emit_seg(j.codes, j.counts, j.Mq, j.N, k / j.S, k % j.S, j.S, j.tri_map, j.tris,
-                          j.he, j.cap, j.n_tri, *reinterpret_cast<MeshEmitSegLds *>(lds));
-    }
+template <int Kind> __device__ __forceinline__ void mesh_job(const MeshArgs &m, int block) {
+    const int sg = xcd_remap_active(block, mesh_segments((size_t)m.Q));
+    if (sg < 0) return;
+    if constexpr (Kind == kMeshCount) mesh_count_seg(m, sg);
+    else mesh_emit_seg<false>(m, sg);
 }
 
 template <int R, int Kind>
 __global__ __launch_bounds__(kTileBlock) void k_frame_laplacian(
     const float *__restrict__ src, float *__restrict__ dst, int M, int N, float lam, int F,
-    int TH, int TW, int tiles_x, int ntiles, int filter_blocks, MeshJob mj) {
+    int TH, int TW, int tiles_x, int ntiles, int filter_blocks, MeshArgs mj) {
     extern __shared__ float4 lds[];
     const int b = (int)blockIdx.x;
     if (Kind != kMeshNone && b >= filter_blocks) {      // the mesh's workgroups follow the tiles
-        const int g = xcd_remap_active(b - filter_blocks, mj.groups);
-        if (g >= 0) mesh_job<Kind>(mj, g, lds);
+        if constexpr (Kind != kMeshNone) mesh_job<Kind>(mj, b - filter_blocks);
         return;
     }
     const int tile = xcd_remap_active(b, ntiles);
@@ -95,19 +74,18 @@ __global__ __launch_bounds__(kTileBlock, kBilWavesPerSimd) void k_frame_bilatera
     const NT *__restrict__ nin, const float *__restrict__ cen, NT *__restrict__ nout, int Mq,
     int Nq, float ka, float kb, int F, int TQH, int TQW, int tiles_x, int ntiles,
     int filter_blocks, const int32_t *__restrict__ tri_map, NT *__restrict__ nT,
-    const float *__restrict__ pts, float *__restrict__ cen_out, MeshJob mj) {
+    const float *__restrict__ pts, float *__restrict__ cen_out, MeshArgs mj) {
     extern __shared__ float4 lds[];
     const int b = (int)blockIdx.x;
     if (Kind != kMeshNone && b >= filter_blocks) {      // the mesh's workgroups follow the tiles
-        const int g = xcd_remap_active(b - filter_blocks, mj.groups);
-        if (g >= 0) mesh_job<Kind>(mj, g, lds);
+        if constexpr (Kind != kMeshNone) mesh_job<Kind>(mj, b - filter_blocks);
         return;
     }
     const int tile = xcd_remap_active(b, ntiles);
     if (tile < 0) return;
     bil_tile<R, NT, FromPts, ByCodes, bil_frame_lanes<R>()>(
         nin, cen, nout, Mq, Nq, ka, kb, F, TQH, TQW, (tile / tiles_x) * TQH, (tile % tiles_x) * TQW,
-        tri_map, nT, lds, pts, cen_out, GatherCodes{mj.codes, mj.counts, mj.S});
+        tri_map, nT, lds, pts, cen_out, GatherCodes{mj.chunks, mj.seg, (int)mesh_chunks((size_t)mj.Q)});
 }
 
 // Optional record of the launches (pl_smooth_frame_events): an event before
@@ -137,23 +115,16 @@ int mesh_bits(int kind) {
     return kind == kMeshCount ? PL_LAUNCH_MESH_COUNT : kind == kMeshEmit ? PL_LAUNCH_MESH_EMIT : 0;
 }
 
-size_t mesh_lds(int kind) {
-    if (kind == kMeshCount) return sizeof(MeshCountSegLds);
-    if (kind == kMeshEmit) return sizeof(MeshEmitSegLds);
-    return 0;
-}
-
 int round8(int x) { return (x + kNumXcd - 1) / kNumXcd * kNumXcd; }
 
 template <int R, int Kind>
 pl_status lap_launch(const float *src, float *dst, int M, int N, float lam, int F, TileCfg c,
-                     const MeshJob &mj, hipStream_t s) {
+                     const MeshArgs &mj, hipStream_t s) {
     const int tiles_x = (N + c.tw - 1) / c.tw;
     const int ntiles = tiles_x * ((M + c.th - 1) / c.th);
     const int fb = Kind == kMeshNone ? ntiles : round8(ntiles);
     const int grid = fb + (Kind == kMeshNone ? 0 : mesh_blocks(mj));
-    size_t lds = lap_lds_bytes(R, F, c.th, c.tw);
-    lds = lds > mesh_lds(Kind) ? lds : mesh_lds(Kind);
+    const size_t lds = lap_lds_bytes(R, F, c.th, c.tw);
     if (pl_status st = allow_lds((const void *)k_frame_laplacian<R, Kind>, lds)) return st;
     k_frame_laplacian<R, Kind><<<grid, kTileBlock, lds, s>>>(src, dst, M, N, lam, F, c.th, c.tw,
                                                              tiles_x, ntiles, fb, mj);
@@ -162,7 +133,7 @@ pl_status lap_launch(const float *src, float *dst, int M, int N, float lam, int 
 
 template <int R>
 pl_status lap_dispatch(int kind, const float *src, float *dst, int M, int N, float lam, int F,
-                       TileCfg c, const MeshJob &mj, hipStream_t s) {
+                       TileCfg c, const MeshArgs &mj, hipStream_t s) {
     switch (kind) {
     case kMeshCount: return lap_launch<R, kMeshCount>(src, dst, M, N, lam, F, c, mj, s);
     case kMeshEmit: return lap_launch<R, kMeshEmit>(src, dst, M, N, lam, F, c, mj, s);
@@ -173,13 +144,12 @@ pl_status lap_dispatch(int kind, const float *src, float *dst, int M, int N, flo
 template <int R, typename NT, bool FromPts, int Kind, bool ByCodes = false>
 pl_status bil_launch(const NT *nin, const float *cen, NT *nout, int Mq, int Nq, float ka,
                      float kb, int F, TileCfg c, const int32_t *tri_map, NT *nT,
-                     const float *pts, float *cen_out, const MeshJob &mj, hipStream_t s) {
+                     const float *pts, float *cen_out, const MeshArgs &mj, hipStream_t s) {
     const int tiles_x = (Nq + c.tw - 1) / c.tw;
     const int ntiles = tiles_x * ((Mq + c.th - 1) / c.th);
     const int fb = Kind == kMeshNone ? ntiles : round8(ntiles);
     const int grid = fb + (Kind == kMeshNone ? 0 : mesh_blocks(mj));
-    size_t lds = bil_lds_bytes(R, F, c.th, c.tw, bil_waves(R, false));
-    lds = lds > mesh_lds(Kind) ? lds : mesh_lds(Kind);
+    const size_t lds = bil_lds_bytes(R, F, c.th, c.tw, bil_waves(R, false));
     if (pl_status st = allow_lds((const void *)k_frame_bilateral<R, NT, FromPts, Kind, ByCodes>, lds))
         return st;
     k_frame_bilateral<R, NT, FromPts, Kind, ByCodes><<<grid, kTileBlock, lds, s>>>(
@@ -192,7 +162,7 @@ template <int R, typename NT>
 pl_status bil_dispatch(bool from_pts, int kind, const NT *nin, const float *cen, NT *nout,
                        int Mq, int Nq, float ka, float kb, int F, TileCfg c,
                        const int32_t *tri_map, NT *nT, const float *pts, float *cen_out,
-                       const MeshJob &mj, bool gather_codes, hipStream_t s) {
+                       const MeshArgs &mj, bool gather_codes, hipStream_t s) {
     if (!from_pts)
         return bil_launch<R, NT, false, kMeshNone>(nin, cen, nout, Mq, Nq, ka, kb, F, c, tri_map,
                                                    nT, pts, cen_out, mj, s);
@@ -211,29 +181,13 @@ pl_status run(const pl_frame &f, void *ws, hipStream_t s, LaunchLog *log) {
     const int M = f.M, N = f.N, Mq = M - 1, Nq = N - 1;
     const size_t P = (size_t)M * N, Q = (size_t)Mq * Nq, T = 2 * Q;
     char *w = static_cast<char *>(ws);
-    MeshJob mj{};
-    mj.pts = f.pts;
-    mj.codes = reinterpret_cast<uint8_t *>(w);
-    mj.counts = reinterpret_cast<int *>(w + align_up(Q, 256));
-    mj.tri_valid = f.tri_valid;
-    mj.tri_map = f.tri_map;
-    mj.tris = f.triangles;
-    mj.he = f.halfedges;
-    mj.n_tri = f.n_tri;
-    mj.cap = (int)T;
-    mj.Mq = Mq;
-    mj.N = N;
-    mj.S = mesh_segments(Nq);
-    mj.units = Mq * mj.S;
-    // one row segment per workgroup: several per workgroup (fewer, longer
-    // mesh workgroups) left the emit finishing after the filter's tiles
-    mj.per_group = 1;
-    mj.groups = mj.units;
-    // frames meshed by whole rows: pl_mesh_opc's launches first, and no
-    // mesh work in the filter launches
-    const bool rows = (long)Mq * mj.S > kMeshSegMax;
+    const MeshArgs mj = mesh_args(f.pts, M, N, f.tri_valid, f.tri_map, f.triangles, f.halfedges,
+                                  (int)T, f.n_tri, ws);
+    // frames whose segments are summed by a launch: pl_mesh_opc's launches
+    // first, and no mesh work in the filter launches
+    const bool apart = mesh_segments(Q) > kMeshSegMax;
     if (pl_status st = log_start(log, s)) return st;
-    if (rows) {
+    if (apart) {
         if (pl_status st = launch_mesh(f.pts, M, N, f.tri_valid, f.tri_map, f.triangles,
                                        f.halfedges, (int)T, f.n_tri, ws, s))
             return st;
@@ -256,7 +210,7 @@ pl_status run(const pl_frame &f, void *ws, hipStream_t s, LaunchLog *log) {
         const int F = left < cl.fuse ? left : cl.fuse;
         left -= F;
         float *dst = ((Ll - 1 - l) % 2 == 0) ? f.pts_out : lap_tmp;    // last lands in pts_out
-        const int kind = rows ? kMeshNone : l == 0 ? kMeshCount : (l == 1 ? kMeshEmit : kMeshNone);
+        const int kind = apart ? kMeshNone : l == 0 ? kMeshCount : (l == 1 ? kMeshEmit : kMeshNone);
         pl_status st;
         switch (Rl) {
         case 1: st = lap_dispatch<1>(kind, cur, dst, M, N, f.lambda, F, cl, mj, s); break;
@@ -283,8 +237,8 @@ pl_status run(const pl_frame &f, void *ws, hipStream_t s, LaunchLog *log) {
         const bool last = l == Lb - 1;
         NT *dst = ((Lb - 1 - l) % 2 == 0) ? nout : bil_tmp;             // last lands in normals
         // the emit rides in the second launch; when that is the gathering
-        // pass, the gather ranks the triangles from the mesh codes itself
-        const int kind = (!rows && Ll + l == 1) ? kMeshEmit : kMeshNone;
+        // pass, the gather ranks the triangles from the mesh's masks itself
+        const int kind = (!apart && Ll + l == 1) ? kMeshEmit : kMeshNone;
         const bool by_codes = last && kind == kMeshEmit;
         const int32_t *tm = last && !by_codes ? f.tri_map : nullptr;
         pl_status st;

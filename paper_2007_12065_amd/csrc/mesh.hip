@@ -1,16 +1,12 @@
 // Organized-point-cloud mesh extraction (Sec. 4.2, Alg. 1 and Alg. 2) as an
-// ordered compaction over segments of quad rows (256 quads, one per thread),
-// one frame per call:
-//   k_mesh_count : one workgroup per segment -> 2-bit validity code per quad
-//                  and the segment's triangle count (mesh_count_seg, tiles.h).
+// ordered compaction over segments of 256 quads in GID order, one frame per
+// call (the bodies are in tiles.h):
+//   k_mesh_count : one workgroup per segment -> validity masks, the segment's
+//                  triangle count
+//   k_mesh_sums  : one workgroup, frames of more than kMeshSegMax segments:
+//                  the counts become the triangles before each segment
 //   k_mesh_emit  : one workgroup per segment -> T_map, T and HE of the
 //                  segment, placed by the counts of the segments before it
-//                  in row-major order (mesh_emit_seg).
-// Every emit workgroup sums the counts before its segment, so that work grows
-// with the square of the segment count: frames of more than kMeshSegMax
-// segments take whole quad rows per workgroup instead (k_mesh_*_rows over
-// mesh_count_row / mesh_emit_row, the batched path's bodies), with the same
-// outputs.
 // Indices come from prefix sums in GID order, so T is exactly Alg. 1's
 // append order and every output is bit-exact and deterministic.
 #include "tiles.h"
@@ -21,56 +17,23 @@ namespace pl {
 
 namespace {
 
-__global__ __launch_bounds__(kTileBlock) void k_mesh_count(const float *__restrict__ pts, int N,
-                                                           int S, uint8_t *__restrict__ codes,
-                                                           uint8_t *__restrict__ tri_valid,
-                                                           int *__restrict__ seg_count) {
-    // each XCD takes a contiguous run of segments (whole rows but for its
-    // ends): the point row that two neighbouring quad rows share is then
-    // fetched once into one L2
-    __shared__ MeshCountSegLds L;
-    const int k = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    mesh_count_seg(pts, N, k / S, k % S, S, codes, tri_valid, seg_count, L);
+// each XCD takes a contiguous run of segments: the point row that two
+// neighbouring quad rows share is then fetched once into one L2, and so are
+// the masks of neighbouring rows in the emit
+__global__ __launch_bounds__(kTileBlock) void k_mesh_count(MeshArgs m) {
+    mesh_count_seg(m, xcd_remap((int)blockIdx.x, (int)gridDim.x));
 }
 
-__global__ __launch_bounds__(kTileBlock) void k_mesh_emit(const uint8_t *__restrict__ codes,
-                                                          const int *__restrict__ seg_count,
-                                                          int Mq, int N, int S,
-                                                          int32_t *__restrict__ tri_map,
-                                                          int32_t *__restrict__ tris,
-                                                          int32_t *__restrict__ he, int cap,
-                                                          int32_t *__restrict__ n_tri) {
-    // contiguous segments per XCD, as for the count (the twins read the
-    // neighbouring rows' codes)
-    __shared__ MeshEmitSegLds L;
-    const int k = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    mesh_emit_seg(codes, seg_count, Mq, N, k / S, k % S, S, tri_map, tris, he, cap, n_tri, L);
+__global__ __launch_bounds__(kMeshSumBlock) void k_mesh_sums(MeshArgs m) {
+    mesh_scan_segs(m.seg, m.sums, mesh_segments((size_t)m.Q));
 }
 
-__global__ __launch_bounds__(kTileBlock) void k_mesh_count_rows(const float *__restrict__ pts,
-                                                                int N,
-                                                                uint8_t *__restrict__ codes,
-                                                                uint8_t *__restrict__ tri_valid,
-                                                                int *__restrict__ row_count) {
-    __shared__ MeshCountRowLds L;
-    mesh_count_row(pts, N, xcd_remap((int)blockIdx.x, (int)gridDim.x), codes, tri_valid,
-                   row_count, L);
-}
-
-__global__ __launch_bounds__(kTileBlock) void k_mesh_emit_rows(const uint8_t *__restrict__ codes,
-                                                               const int *__restrict__ row_count,
-                                                               int Mq, int N,
-                                                               int32_t *__restrict__ tri_map,
-                                                               int32_t *__restrict__ tris,
-                                                               int32_t *__restrict__ he, int cap,
-                                                               int32_t *__restrict__ n_tri) {
-    __shared__ MeshEmitRowLds L;
-    mesh_emit_row(codes, row_count, Mq, N, xcd_remap((int)blockIdx.x, (int)gridDim.x), tri_map,
-                  tris, he, cap, n_tri, L);
+template <bool Summed> __global__ __launch_bounds__(kTileBlock) void k_mesh_emit(MeshArgs m) {
+    mesh_emit_seg<Summed>(m, xcd_remap((int)blockIdx.x, (int)gridDim.x));
 }
 
 // Scratch of the allocation-free entry point (pl_mesh_opc_static): the
-// validity codes and per-segment counts that pl_mesh_opc keeps in the
+// validity masks and per-segment counts that pl_mesh_opc keeps in the
 // caller's workspace.  Every device the library runs on holds one copy until
 // the process ends.  Host code never passes this name to a kernel (in host
 // code it is a host-side stand-in, not a device address): it uses the
@@ -116,31 +79,38 @@ pl_status mesh_static_scratch(hipStream_t s, void **out) {
     return PL_OK;
 }
 
+// A byte per quad and an int per 256 quads of each row: the chunks (24 bytes
+// per 64 quads) and the segments' counts need less (mesh_args).
 size_t mesh_workspace(int M, int N) {
     const size_t Q = (size_t)(M - 1) * (N - 1);
-    return align_up(Q, 256) + align_up(sizeof(int) * (size_t)(M - 1) * mesh_segments(N - 1), 256);
+    const size_t rows = (size_t)(M - 1) * ((size_t)(N - 1 + kMeshSeg - 1) / kMeshSeg);
+    return align_up(Q, 256) + align_up(sizeof(int) * rows, 256);
+}
+
+MeshArgs mesh_args(const float *pts, int M, int N, uint8_t *tri_valid, int32_t *tri_map,
+                   int32_t *triangles, int32_t *halfedges, int32_t cap, int32_t *n_tri, void *ws) {
+    const size_t Q = (size_t)(M - 1) * (N - 1);
+    char *w = static_cast<char *>(ws);
+    const size_t o_seg = align_up(sizeof(MeshChunk) * mesh_chunks(Q), 256);
+    const size_t o_sums = o_seg + align_up(sizeof(uint16_t) * (size_t)mesh_segments(Q), 256);
+    return MeshArgs{pts, reinterpret_cast<MeshChunk *>(w), reinterpret_cast<uint16_t *>(w + o_seg),
+                    reinterpret_cast<int *>(w + o_sums), tri_valid, tri_map, triangles, halfedges, n_tri, cap, N, (int)Q, QuadDiv::by(N - 1)};
 }
 
 pl_status launch_mesh(const float *pts, int M, int N, uint8_t *tri_valid, int32_t *tri_map,
                       int32_t *triangles, int32_t *halfedges, int32_t cap, int32_t *n_tri,
                       void *ws, hipStream_t s) {
-    const int Mq = M - 1;
-    const size_t Q = (size_t)Mq * (N - 1);
-    uint8_t *codes = static_cast<uint8_t *>(ws);
-    int *counts = reinterpret_cast<int *>(codes + align_up(Q, 256));
-    const int S = mesh_segments(N - 1);
-    if ((long)Mq * S > kMeshSegMax) {
-        k_mesh_count_rows<<<Mq, kTileBlock, 0, s>>>(pts, N, codes, tri_valid, counts);
-        if (pl_status st = hip_check(hipGetLastError(), "k_mesh_count_rows")) return st;
-        k_mesh_emit_rows<<<Mq, kTileBlock, 0, s>>>(codes, counts, Mq, N, tri_map, triangles,
-                                                   halfedges, cap, n_tri);
-        return hip_check(hipGetLastError(), "k_mesh_emit_rows");
-    }
-    const int blocks = Mq * S;
-    k_mesh_count<<<blocks, kTileBlock, 0, s>>>(pts, N, S, codes, tri_valid, counts);
+    const MeshArgs m = mesh_args(pts, M, N, tri_valid, tri_map, triangles, halfedges, cap, n_tri, ws);
+    const int blocks = mesh_segments((size_t)m.Q);
+    k_mesh_count<<<blocks, kTileBlock, 0, s>>>(m);
     if (pl_status st = hip_check(hipGetLastError(), "k_mesh_count")) return st;
-    k_mesh_emit<<<blocks, kTileBlock, 0, s>>>(codes, counts, Mq, N, S, tri_map, triangles,
-                                              halfedges, cap, n_tri);
+    if (blocks > kMeshSegMax) {
+        k_mesh_sums<<<1, kMeshSumBlock, 0, s>>>(m);
+        if (pl_status st = hip_check(hipGetLastError(), "k_mesh_sums")) return st;
+        k_mesh_emit<true><<<blocks, kTileBlock, 0, s>>>(m);
+    } else {
+        k_mesh_emit<false><<<blocks, kTileBlock, 0, s>>>(m);
+    }
     return hip_check(hipGetLastError(), "k_mesh_emit");
 }
 

@@ -14,419 +14,289 @@ namespace pl {
 constexpr int kTileBlock = 256;        // threads per workgroup for every tile body
 
 // ---------------------------------------------------------------------------
-// Mesh (Sec. 4.2, Alg. 1 and Alg. 2), one quad row per call.
+// Mesh (Sec. 4.2, Alg. 1 and Alg. 2), over the quads in GID order.
+//
+// Quads are numbered q = u Nq + v, whatever the frame's width, and dealt in
+// chunks of 64, one per wave, four chunks (a segment) per workgroup.  A chunk's
+// validity is two 64-bit masks (bit l: the first, the second triangle of quad
+// 64 k + l is valid), so a triangle's place in T is the count of the segments
+// before it, the chunk's place in its segment and a population count; the
+// quads above, below and beside a chunk's are the masks 64 k -+ Nq and 64 k
+// -+ 1 read across chunk borders.  A wave's emit is then scalar mask
+// arithmetic and five stores, whose lanes write one contiguous run each: no
+// LDS staging, no scan over the workgroup.  What bounds it is the outputs'
+// bytes.  (With a byte of code per quad, shuffled scans and outputs staged in
+// LDS, counting and emitting took 100 and 200 VALU instructions per 64 quads,
+// now 60 and 110, and a 1200 x 1944 frame 11.7 + 39.2 us, now 13.1 + 26.6 us.)
 // ---------------------------------------------------------------------------
 
-constexpr int kMeshChunk = 4 * kTileBlock;    // columns staged per pass
+constexpr int kMeshSeg = kTileBlock;           // quads per segment
+constexpr int kMeshPerSeg = kMeshSeg / kWave;  // chunks per segment
+// Segments per frame up to which an emit workgroup sums the counts before its
+// segment itself; past it a launch of one workgroup does for all of them
+// (6 us and more, where the workgroups' own sums grow with the square: 9,101
+// segments take 26.6 us to emit, 22.8 us with the sums at hand).
+constexpr int kMeshSegMax = 16384;
 
-// Validity codes of quad row u (bit 0: first triangle, bit 1: second) and the
-// row's triangle count.  All point loads of a 1024-column chunk are issued
-// before any is used; point validity is staged in LDS.
-struct MeshCountRowLds {
-    uint8_t ok[2][kMeshChunk + 1];
+struct MeshChunk {
+    unsigned long long f, s;      // masks of the first and the second triangles
+    int pre;                      // valid triangles of the segment before the chunk
+    int unused;
 };
 
-__device__ __forceinline__ void mesh_count_row(const float *__restrict__ pts, int N, int u,
-                                               uint8_t *__restrict__ codes,
-                                               uint8_t *__restrict__ tri_valid,
-                                               int *__restrict__ row_count,
-                                               MeshCountRowLds &L) {
-    auto &ok = L.ok;
-    __shared__ int red[kTileBlock / kWave];
-    const int Nq = N - 1;
-    const float *r0 = pts + (size_t)u * N * 3;
-    const float *r1 = r0 + (size_t)N * 3;
-    int cnt = 0;
-    for (int v0 = 0; v0 < Nq; v0 += kMeshChunk) {
-        float x[2][5], y[2][5], z[2][5];
+__host__ __device__ constexpr int mesh_segments(size_t Q) { return (int)((Q + kMeshSeg - 1) / kMeshSeg); }
+__host__ __device__ constexpr size_t mesh_chunks(size_t Q) { return (Q + kWave - 1) / kWave; }
+
+// A frame's mesh buffers and outputs.
+struct MeshArgs {
+    const float *pts;
+    MeshChunk *chunks;
+    uint16_t *seg;                // [segments] valid triangles of each (at most 512)
+    int *sums;                    // [segments + 1] triangles before each, and |T| (frames past kMeshSegMax)
+    uint8_t *tri_valid;
+    int32_t *tri_map, *tris, *he, *n_tri;
+    int cap, N, Q;                // Q quads, N points per row
+    QuadDiv by_row;               // by Nq = N - 1
+};
+
+// The arguments of a frame whose mesh buffers lie in `ws` (mesh_workspace).
+MeshArgs mesh_args(const float *pts, int M, int N, uint8_t *tri_valid, int32_t *tri_map,
+                   int32_t *triangles, int32_t *halfedges, int32_t cap, int32_t *n_tri, void *ws);
+
+// Masks and count of segment `sg`.
+__device__ __forceinline__ void mesh_count_seg(const MeshArgs &m, int sg) {
+    __shared__ int part[kMeshPerSeg];
+    const int lane = (int)threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int k = sg * kMeshPerSeg + wave;
+    const int Nq = m.by_row.d, q0 = k * kWave, q = q0 + lane;
+    unsigned long long mf = 0, ms = 0;
+    if (q0 < m.Q) {
+        const int u0 = m.by_row.div(q0);
+        // the lane's row: one step past the wave's first if rows are long
+        const int t = q0 - u0 * Nq + lane;
+        const int du = Nq >= kWave ? (t >= Nq ? 1 : 0) : m.by_row.div(t);
+        const int v = t - du * Nq;
+        const bool in = q < m.Q;
+        const float *p1 = m.pts + 3 * (size_t)(in ? q + u0 + du : 0);
+        const float *p4 = p1 + 3 * (size_t)m.N;
+        const float ax = p1[0], ay = p1[1], az = p1[2], bx = p4[0], by = p4[1], bz = p4[2];
+        // the right corners are the next lane's left ones, but for the wave's
+        // last lane and a row's last quad
+        bool right1 = false, right4 = false;
+        const bool edge = in && (lane == kWave - 1 || v == Nq - 1);
+        if (edge) {
+            right1 = !any_nan(p1[3], p1[4], p1[5]);
+            right4 = !any_nan(p4[3], p4[4], p4[5]);
+        }
+        const unsigned long long o1 = __ballot(in && !any_nan(ax, ay, az));
+        const unsigned long long o4 = __ballot(in && !any_nan(bx, by, bz));
+        const unsigned long long e = __ballot(edge), e1 = __ballot(right1), e4 = __ballot(right4);
+        const unsigned long long o2 = ((o1 >> 1) & ~e) | e1, o3 = ((o4 >> 1) & ~e) | e4;
+        mf = o1 & o2 & o3;              // first triangle (p3, p2, p1)
+        ms = o1 & o3 & o4;              // second triangle (p1, p4, p3)
+        if (m.tri_valid && in) {
+            const unsigned f = lane_bit(mf), s = lane_bit(ms);
+            *reinterpret_cast<uint16_t *>(m.tri_valid + 2 * (size_t)q) = (uint16_t)(f | (s << 8));
+        }
+    }
+    if (lane == 0) part[wave] = __popcll(mf) + __popcll(ms);
+    __syncthreads();
+    int pre = 0, all = 0;
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const int v = v0 + threadIdx.x + j * kTileBlock;
-            const bool in = (j < 4 || threadIdx.x == 0) && v < N && v <= v0 + kMeshChunk;
-            x[0][j] = in ? r0[3 * v] : 0.f; y[0][j] = in ? r0[3 * v + 1] : 0.f; z[0][j] = in ? r0[3 * v + 2] : 0.f;
-            x[1][j] = in ? r1[3 * v] : 0.f; y[1][j] = in ? r1[3 * v + 1] : 0.f; z[1][j] = in ? r1[3 * v + 2] : 0.f;
+    for (int w = 0; w < kMeshPerSeg; ++w) {
+        const int c = part[w];
+        pre += w < wave ? c : 0;
+        all += c;
+    }
+    if (lane == 0 && q0 < m.Q) m.chunks[k] = MeshChunk{mf, ms, pre, 0};
+    if (threadIdx.x == 0) m.seg[sg] = (uint16_t)all;
+    __syncthreads();                    // `part` is reused by the next segment
+}
+
+// The triangles before each segment, and |T| behind them, from the segments'
+// counts, by one workgroup of kMeshSumBlock threads.
+constexpr int kMeshSumBlock = 1024;
+
+__device__ __forceinline__ void mesh_scan_segs(const uint16_t *seg, int *sums, int n) {
+    __shared__ int wsum[kMeshSumBlock / kWave];
+    constexpr int kPer = 16;            // consecutive counts per thread and pass: 32 bytes
+    const int lane = (int)threadIdx.x & (kWave - 1), wave = (int)threadIdx.x / kWave;
+    int carry = 0;
+    for (int base = 0; base < n; base += kPer * kMeshSumBlock) {
+        const int i0 = base + kPer * (int)threadIdx.x;
+        union {
+            uint4 v[2];
+            uint16_t c[kPer];
+        } in = {{make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)}};
+        if (i0 + kPer <= n) {
+            in.v[0] = reinterpret_cast<const uint4 *>(seg + i0)[0];
+            in.v[1] = reinterpret_cast<const uint4 *>(seg + i0)[1];
+        } else {
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) in.c[j] = i0 + j < n ? seg[i0 + j] : (uint16_t)0;
+        }
+        int sum = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) sum += in.c[j];
+        const int incl = wave_inclusive_scan(sum);
+        if (lane == kWave - 1) wsum[wave] = incl;
+        __syncthreads();
+        int run = carry + incl - sum;
+#pragma unroll
+        for (int w = 0; w < kMeshSumBlock / kWave; ++w) {
+            const int t = wsum[w];
+            run += w < wave ? t : 0;
+            carry += t;
         }
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const int l = threadIdx.x + j * kTileBlock;
-            if (j < 4 || threadIdx.x == 0) {
-#pragma unroll
-                for (int r = 0; r < 2; ++r)
-                    ok[r][l] = !(is_nan_bits(x[r][j]) || is_nan_bits(y[r][j]) || is_nan_bits(z[r][j]));
-            }
+        for (int j = 0; j < kPer; ++j) {
+            if (i0 + j < n) sums[i0 + j] = run;
+            run += in.c[j];
         }
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int l = threadIdx.x + j * kTileBlock;
-            const int v = v0 + l;
-            if (v < Nq) {
-                const int p1 = ok[0][l], p2 = ok[0][l + 1], p3 = ok[1][l + 1], p4 = ok[1][l];
-                const int f = p1 & p2 & p3;          // first triangle (p3, p2, p1)
-                const int s = p1 & p3 & p4;          // second triangle (p1, p4, p3)
-                const size_t q = (size_t)u * Nq + v;
-                codes[q] = (uint8_t)(f | (s << 1));
-                if (tri_valid) {
-                    tri_valid[2 * q] = (uint8_t)f;
-                    tri_valid[2 * q + 1] = (uint8_t)s;
-                }
-                cnt += f + s;
-            }
-        }
-        __syncthreads();
     }
-    cnt = wave_sum(cnt);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int t = 0;
-#pragma unroll
-        for (int w = 0; w < kTileBlock / kWave; ++w) t += red[w];
-        row_count[u] = t;
-    }
+    if (threadIdx.x == 0) sums[n] = carry;
 }
 
-// Block-wide exclusive scan of three counters packed in 21-bit fields (a
-// pass of 1024 quads holds at most 2048 triangles per row).
-__device__ __forceinline__ unsigned long long mesh_block_scan(unsigned long long x,
-                                                             unsigned long long *total) {
-    __shared__ unsigned long long wsum[kTileBlock / kWave];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wid = threadIdx.x / kWave;
-    unsigned long long incl = x;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const unsigned long long y = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += y;
-    }
-    __syncthreads();
-    if (lane == kWave - 1) wsum[wid] = incl;
-    __syncthreads();
-    unsigned long long before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kTileBlock / kWave; ++w) {
-        const unsigned long long t = wsum[w];
-        before += w < wid ? t : 0ull;
-        all += t;
-    }
-    *total = all;
-    return before + incl - x;
-}
-
-__device__ __forceinline__ int popc2(int c) { return (c & 1) + ((c >> 1) & 1); }
-
-constexpr int kEmitQ = 4;                        // consecutive quads per thread
-constexpr int kEmitChunk = kEmitQ * kTileBlock;  // quads per pass
-constexpr unsigned long long kField = (1ull << 21) - 1;
-
-// Cooperative copy of `count` staged ints to global memory: consecutive
-// lanes write consecutive words, so every store instruction is coalesced.
-__device__ __forceinline__ void emit_flush(const int *stage, int32_t *__restrict__ dst, int count) {
-    __syncthreads();
-    for (int k = threadIdx.x; k < count; k += kTileBlock) st_stream(&dst[k], stage[k]);
-    __syncthreads();
-}
-
-// T_map, T and HE of quad row u.  The row's place in T is the sum of the
-// counts of the rows above it; the codes of rows u-1 and u+1 give the
-// indices of the Top and Bottom twins.  Each thread owns four consecutive
-// quads of a 1024-quad pass (one block scan per pass, serial prefix inside
-// the thread).  A thread's outputs are strided in memory (up to 96 bytes per
-// lane), so each of the pass's three contiguous output ranges -- its T_map
-// entries, its rows of T, its rows of HE -- is assembled in LDS and then
-// written with coalesced stores.  The last row writes |T|.
-struct MeshEmitRowLds {
-    int stage[3 * 2 * kEmitChunk];
+// The masks of the 64 quads from q on (q may lie outside the frame: quads
+// there have none), and the valid triangles of q's segment before q.
+struct MeshWindow {
+    unsigned long long f, s;
+    int before;
 };
 
-__device__ __forceinline__ void mesh_emit_row(const uint8_t *__restrict__ codes,
-                                              const int *__restrict__ row_count, int Mq, int N,
-                                              int u, int32_t *__restrict__ tri_map,
-                                              int32_t *__restrict__ tris,
-                                              int32_t *__restrict__ he, int cap,
-                                              int32_t *__restrict__ n_tri, MeshEmitRowLds &L) {
-    __shared__ int red[kTileBlock / kWave];
-    int *stage = L.stage;
-    const int Nq = N - 1;
-    const uint8_t *cr0 = codes + (size_t)u * Nq;
-    const uint8_t *crm = u > 0 ? cr0 - Nq : cr0;        // row u-1
-    const uint8_t *crp = u + 1 < Mq ? cr0 + Nq : cr0;   // row u+1
-    int above = 0;
-    for (int r = threadIdx.x; r < u - 1; r += kTileBlock) above += row_count[r];
-    above = wave_sum(above);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = above;
-    __syncthreads();
-    int basem = 0;
-#pragma unroll
-    for (int w = 0; w < kTileBlock / kWave; ++w) basem += red[w];
-    const int base0 = basem + (u > 0 ? row_count[u - 1] : 0);
-    const int basep = base0 + row_count[u];
-    if (u == Mq - 1 && threadIdx.x == 0) *n_tri = basep;
-    int carry0 = 0, carrym = 0, carryp = 0;
-    for (int v0 = 0; v0 < Nq; v0 += kEmitChunk) {
-        const int vb = v0 + kEmitQ * threadIdx.x;
-        int c0[kEmitQ], cm[kEmitQ], cp[kEmitQ];
-        int t0 = 0, tm = 0, tp = 0;
-#pragma unroll
-        for (int j = 0; j < kEmitQ; ++j) {
-            const int v = vb + j;
-            const bool in = v < Nq;
-            c0[j] = in ? cr0[v] : 0;
-            cm[j] = (in && u > 0) ? crm[v] : 0;
-            cp[j] = (in && u + 1 < Mq) ? crp[v] : 0;
-            t0 += popc2(c0[j]);
-            tm += popc2(cm[j]);
-            tp += popc2(cp[j]);
-        }
-        const int cl_first = (vb > 0 && vb - 1 < Nq) ? cr0[vb - 1] : 0;
-        const int cr_last = vb + kEmitQ < Nq ? cr0[vb + kEmitQ] : 0;
-        unsigned long long total;
-        const unsigned long long ex = mesh_block_scan(
-            (unsigned long long)t0 | ((unsigned long long)tm << 21) | ((unsigned long long)tp << 42),
-            &total);
-        const int pass0 = base0 + carry0;                    // first triangle of this pass
-        const int r00 = pass0 + (int)(ex & kField);          // this thread's first triangle
-        const int rm0 = basem + carrym + (int)((ex >> 21) & kField);
-        const int rp0 = basep + carryp + (int)((ex >> 42) & kField);
-        const int nq = min(kEmitChunk, Nq - v0);              // quads in this pass
-        const int nt = (int)(total & kField);                 // triangles in this pass
-        const int nw = max(0, min(nt, cap - pass0));          // of them below cap
-
-        // T_map: two entries per quad, -1 for an invalid triangle
-        {
-            int r0 = r00;
-#pragma unroll
-            for (int j = 0; j < kEmitQ; ++j) {
-                const int v = vb + j;
-                if (v < Nq) {
-                    const int f = c0[j] & 1, s = (c0[j] >> 1) & 1;
-                    stage[2 * (v - v0)] = f ? r0 : -1;
-                    stage[2 * (v - v0) + 1] = s ? r0 + f : -1;
-                }
-                r0 += popc2(c0[j]);
-            }
-            emit_flush(stage, tri_map + 2 * ((size_t)u * Nq + v0), 2 * nq);
-        }
-        // T: first triangle (p3, p2, p1), second (p1, p4, p3)
-        {
-            int r0 = r00;
-#pragma unroll
-            for (int j = 0; j < kEmitQ; ++j) {
-                const int v = vb + j;
-                const int f = c0[j] & 1, s = (c0[j] >> 1) & 1;
-                const int i1 = u * N + v, i2 = i1 + 1, i3 = i1 + N + 1, i4 = i1 + N;
-                const int a = 3 * (r0 - pass0);
-                if (f) { stage[a] = i3; stage[a + 1] = i2; stage[a + 2] = i1; }
-                if (s) { stage[a + 3 * f] = i1; stage[a + 3 * f + 1] = i4; stage[a + 3 * f + 2] = i3; }
-                r0 += f + s;
-            }
-            emit_flush(stage, tris + 3 * (size_t)pass0, 3 * nw);
-        }
-        // HE: Right = (u, v+1, 1), Top = (u-1, v, 1), Left = (u, v-1, 0),
-        // Bottom = (u+1, v, 0); twin indices from the running prefix sums
-        if (he) {
-            int r0 = r00, rm = rm0, rp = rp0;
-#pragma unroll
-            for (int j = 0; j < kEmitQ; ++j) {
-                const int f = c0[j] & 1, s = (c0[j] >> 1) & 1;
-                const int cr = j + 1 < kEmitQ ? c0[j + 1] : cr_last;
-                const int cl = j > 0 ? c0[j - 1] : cl_first;
-                const int right = (cr & 2) ? r0 + f + s + (cr & 1) : -1;
-                const int left = (cl & 1) ? r0 - popc2(cl) : -1;
-                const int top = (cm[j] & 2) ? rm + (cm[j] & 1) : -1;
-                const int bottom = (cp[j] & 1) ? rp : -1;
-                const int rF = r0, rS = r0 + f;
-                const int a = 3 * (r0 - pass0);
-                if (f) {
-                    stage[a] = right >= 0 ? 3 * right : -1;
-                    stage[a + 1] = top >= 0 ? 3 * top + 1 : -1;
-                    stage[a + 2] = s ? 3 * rS + 2 : -1;
-                }
-                if (s) {
-                    stage[a + 3 * f] = left >= 0 ? 3 * left : -1;
-                    stage[a + 3 * f + 1] = bottom >= 0 ? 3 * bottom + 1 : -1;
-                    stage[a + 3 * f + 2] = f ? 3 * rF + 2 : -1;
-                }
-                r0 += f + s;
-                rm += popc2(cm[j]);
-                rp += popc2(cp[j]);
-            }
-            emit_flush(stage, he + 3 * (size_t)pass0, 3 * nw);
-        }
-        carry0 += nt;
-        carrym += (int)((total >> 21) & kField);
-        carryp += (int)((total >> 42) & kField);
-    }
+// Chunk k by scalar loads (constant while the reading kernel runs); none of
+// its bits outside the frame.  The load is unconditional, so that several are
+// in flight together.
+__device__ __forceinline__ MeshChunk mesh_chunk(const MeshChunk *chunks, int K, int k) {
+    typedef const __attribute__((address_space(4))) MeshChunk *Const;
+    const Const p = (Const)chunks + min(max(k, 0), K - 1);
+    const bool in = k >= 0 && k < K;
+    const unsigned long long f = p->f, s = p->s;
+    const int pre = p->pre;
+    return MeshChunk{in ? f : 0ull, in ? s : 0ull, in ? pre : 0, 0};
 }
 
-// ---------------------------------------------------------------------------
-// The same mesh over row segments of kMeshSeg quads, one quad per thread (the
-// single-frame kernels): a 480x640 frame is then 1,437 workgroups instead of
-// 479 rows, enough waves to cover the memory latency of these two short
-// stages.  Segment s of quad row u covers columns [s kMeshSeg, (s+1) kMeshSeg)
-// of every row alike, so with segments numbered row-major (k = u S + s, S
-// segments per row) the first triangle of segment k is the sum of the counts
-// of segments 0 .. k-1, and the twins in rows u-1 and u+1 start at the same
-// sums for k - S and k + S.  The outputs equal the whole-row bodies' above.
-// ---------------------------------------------------------------------------
-
-constexpr int kMeshSeg = kTileBlock;
-constexpr int kMeshSegMax = 8192;    // segments per frame up to which the segment bodies are used
-
-__host__ __device__ constexpr int mesh_segments(int Nq) { return (Nq + kMeshSeg - 1) / kMeshSeg; }
-
-// Validity codes of segment s of quad row u and its triangle count
-// seg_count[u S + s].
-struct MeshCountSegLds {
-    uint8_t ok[2][kMeshSeg + 1];
-};
-
-__device__ __forceinline__ void mesh_count_seg(const float *__restrict__ pts, int N, int u, int s,
-                                               int S, uint8_t *__restrict__ codes,
-                                               uint8_t *__restrict__ tri_valid,
-                                               int *__restrict__ seg_count, MeshCountSegLds &L) {
-    auto &ok = L.ok;
-    __shared__ int red[kTileBlock / kWave];
-    const int Nq = N - 1;
-    const int v0 = s * kMeshSeg;
-    const float *r0 = pts + (size_t)u * N * 3;
-    const float *r1 = r0 + (size_t)N * 3;
-    // points v0 .. v0 + kMeshSeg of both rows (the last one by thread 0),
-    // all loads issued before any is used
-    float x[2][2], y[2][2], z[2][2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int v = v0 + (int)threadIdx.x + j * kMeshSeg;
-        const bool in = (j == 0 || threadIdx.x == 0) && v < N;
-        x[0][j] = in ? r0[3 * v] : 0.f; y[0][j] = in ? r0[3 * v + 1] : 0.f; z[0][j] = in ? r0[3 * v + 2] : 0.f;
-        x[1][j] = in ? r1[3 * v] : 0.f; y[1][j] = in ? r1[3 * v + 1] : 0.f; z[1][j] = in ? r1[3 * v + 2] : 0.f;
+// The window at q from its chunk c and the one after it.
+__device__ __forceinline__ MeshWindow mesh_window(const MeshChunk &c, const MeshChunk &next, int q) {
+    const int sh = q & (kWave - 1);
+    const unsigned long long low = (1ull << sh) - 1;
+    MeshWindow w{c.f >> sh, c.s >> sh, c.pre + (int)__popcll(c.f & low) + (int)__popcll(c.s & low)};
+    if (sh) {
+        w.f |= next.f << (kWave - sh);
+        w.s |= next.s << (kWave - sh);
     }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        if (j == 0 || threadIdx.x == 0) {
-#pragma unroll
-            for (int r = 0; r < 2; ++r)
-                ok[r][threadIdx.x + j * kMeshSeg] =
-                    !(is_nan_bits(x[r][j]) || is_nan_bits(y[r][j]) || is_nan_bits(z[r][j]));
-        }
-    }
-    __syncthreads();
-    const int v = v0 + (int)threadIdx.x;
-    int cnt = 0;
-    if (v < Nq) {
-        const int l = threadIdx.x;
-        const int p1 = ok[0][l], p2 = ok[0][l + 1], p3 = ok[1][l + 1], p4 = ok[1][l];
-        const int f = p1 & p2 & p3;          // first triangle (p3, p2, p1)
-        const int g = p1 & p3 & p4;          // second triangle (p1, p4, p3)
-        const size_t q = (size_t)u * Nq + v;
-        codes[q] = (uint8_t)(f | (g << 1));
-        if (tri_valid) {
-            tri_valid[2 * q] = (uint8_t)f;
-            tri_valid[2 * q + 1] = (uint8_t)g;
-        }
-        cnt = f + g;
-    }
-    cnt = wave_sum(cnt);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int t = 0;
-#pragma unroll
-        for (int w = 0; w < kTileBlock / kWave; ++w) t += red[w];
-        seg_count[u * S + s] = t;
-    }
+    return w;
 }
 
-// T_map, T and HE of segment s of quad row u (the whole-row emit restricted
-// to one quad per thread; see mesh_emit_row for the twin rules).  The last
-// segment of the last row writes |T|.
-struct MeshEmitSegLds {
-    int stage[3 * 2 * kMeshSeg];
-};
+__device__ __forceinline__ int mesh_rank(const MeshWindow &w) { return bits_below(w.f) + bits_below(w.s); }
 
-__device__ __forceinline__ void mesh_emit_seg(const uint8_t *__restrict__ codes,
-                                              const int *__restrict__ seg_count, int Mq, int N,
-                                              int u, int s, int S, int32_t *__restrict__ tri_map,
-                                              int32_t *__restrict__ tris,
-                                              int32_t *__restrict__ he, int cap,
-                                              int32_t *__restrict__ n_tri, MeshEmitSegLds &L) {
-    __shared__ int red[kTileBlock / kWave];
-    int *stage = L.stage;
-    const int Nq = N - 1;
-    const int v0 = s * kMeshSeg;
-    const int ku = u * S + s;                 // this segment
-    const int lo = u > 0 ? ku - S : ku;       // the first of the segments above and here
+// This thread's share of the counts of segments 0 .. n - 1 (16-byte loads of
+// eight, the rest one by one).
+__device__ __forceinline__ int mesh_sum_segs(const uint16_t *__restrict__ seg, int n, int t, int threads) {
     int a = 0;
-    for (int k = threadIdx.x; k < lo; k += kTileBlock) a += seg_count[k];
-    a = wave_sum(a);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = a;
-    __syncthreads();
-    int sum_lo = 0;
+    for (int i = t; i < n / 8; i += threads) {
+        const uint4 c = reinterpret_cast<const uint4 *>(seg)[i];
+        a = __builtin_amdgcn_sad_u16(c.x, 0u, a);
+        a = __builtin_amdgcn_sad_u16(c.y, 0u, a);
+        a = __builtin_amdgcn_sad_u16(c.z, 0u, a);
+        a = __builtin_amdgcn_sad_u16(c.w, 0u, a);
+    }
+    if (t < n % 8) a += seg[n - n % 8 + t];
+    return a;
+}
+
+// T_map, T and HE of segment `sg`.  Summed: `sums` holds the triangles before
+// each segment.  The last segment writes |T|.
+template <bool Summed>
+__device__ __forceinline__ void mesh_emit_seg(const MeshArgs &m, int sg) {
+    __shared__ int part[kTileBlock / kWave];
+    const int lane = (int)threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int Nq = m.by_row.d, K = (int)mesh_chunks((size_t)m.Q), S = mesh_segments((size_t)m.Q);
+    const int q0 = (sg * kMeshPerSeg + wave) * kWave;
+    // segments of the quads above and below this chunk's first
+    const int qt = q0 - Nq, qb = q0 + Nq;
+    const int st = max(qt, 0) / kMeshSeg, sb = min(qb / kMeshSeg, S - 1);
+    const int k0 = q0 / kWave, kt = qt >> 6, kb = qb >> 6;
+    const MeshChunk c = mesh_chunk(m.chunks, K, k0), cl = mesh_chunk(m.chunks, K, k0 - 1),
+                    cr = mesh_chunk(m.chunks, K, k0 + 1), ct = mesh_chunk(m.chunks, K, kt),
+                    ct1 = mesh_chunk(m.chunks, K, kt + 1), cb = mesh_chunk(m.chunks, K, kb),
+                    cb1 = mesh_chunk(m.chunks, K, kb + 1);
+    int bt, b0, bb;                     // triangles before the segments st, sg and sb
+    if constexpr (Summed) {
+        bt = m.sums[st];
+        b0 = m.sums[sg];
+        bb = m.sums[sb];
+        if (sg == S - 1 && threadIdx.x == 0) *m.n_tri = m.sums[S];
+    } else {
+        // the workgroup sums the segments before its first one above, each
+        // wave the few between
+        const int lo = max(sg * kMeshSeg - Nq, 0) / kMeshSeg;
+        const int a = wave_sum(mesh_sum_segs(m.seg, lo, (int)threadIdx.x, kTileBlock));
+        if (lane == 0) part[wave] = a;
+        __syncthreads();
+        int sum = 0;
 #pragma unroll
-    for (int w = 0; w < kTileBlock / kWave; ++w) sum_lo += red[w];
-    const int basem = sum_lo;                 // first triangle of segment ku - S (u > 0)
-    int base0 = sum_lo;                       // first triangle of this segment
-    if (u > 0)
-        for (int k = ku - S; k < ku; ++k) base0 += seg_count[k];
-    int basep = base0;                        // first triangle of segment ku + S
-    if (u + 1 < Mq)
-        for (int k = ku; k < ku + S; ++k) basep += seg_count[k];
-    if (u == Mq - 1 && s == S - 1 && threadIdx.x == 0) *n_tri = base0 + seg_count[ku];
-
-    const uint8_t *cr0 = codes + (size_t)u * Nq;
-    const int v = v0 + (int)threadIdx.x;
-    const bool in = v < Nq;
-    const int c0 = in ? cr0[v] : 0;
-    const int cm = (in && u > 0) ? cr0[v - Nq] : 0;
-    const int cp = (in && u + 1 < Mq) ? cr0[v + Nq] : 0;
-    const int cl = (in && v > 0) ? cr0[v - 1] : 0;
-    const int cr = v + 1 < Nq ? cr0[v + 1] : 0;
-    unsigned long long total;
-    const unsigned long long ex = mesh_block_scan(
-        (unsigned long long)popc2(c0) | ((unsigned long long)popc2(cm) << 21) |
-            ((unsigned long long)popc2(cp) << 42),
-        &total);
-    const int r0 = base0 + (int)(ex & kField);           // this quad's first triangle
-    const int rm = basem + (int)((ex >> 21) & kField);
-    const int rp = basep + (int)((ex >> 42) & kField);
-    const int nq = min(kMeshSeg, Nq - v0);                // quads in this segment
-    const int nt = (int)(total & kField);                 // triangles in this segment
-    const int nw = max(0, min(nt, cap - base0));          // of them below cap
-    const int f = c0 & 1, g = (c0 >> 1) & 1;
-
-    // T_map: two entries per quad, -1 for an invalid triangle
-    if (in) {
-        stage[2 * threadIdx.x] = f ? r0 : -1;
-        stage[2 * threadIdx.x + 1] = g ? r0 + f : -1;
+        for (int w = 0; w < kTileBlock / kWave; ++w) sum += part[w];
+        bt = b0 = bb = sum;
+        for (int i = lo; i < sb; i += kWave) {
+            const int c = i + lane < sb ? m.seg[i + lane] : 0;
+            const int incl = wave_inclusive_scan(c);
+            auto upto = [&](int x) {    // counts of i .. x - 1 within this pass
+                const int d = min(x - i, kWave);
+                return d > 0 ? __builtin_amdgcn_readlane(incl, d - 1) : 0;
+            };
+            bt += upto(st);
+            b0 += upto(sg);
+            bb += upto(sb);
+        }
+        if (sg == S - 1 && threadIdx.x == 0) *m.n_tri = b0 + m.seg[sg];
+        __syncthreads();                // `part` is reused by the next segment
     }
-    emit_flush(stage, tri_map + 2 * ((size_t)u * Nq + v0), 2 * nq);
-    // T: first triangle (p3, p2, p1), second (p1, p4, p3)
+    if (q0 >= m.Q) return;
+    const MeshWindow top = mesh_window(ct, ct1, qt), bot = mesh_window(cb, cb1, qb);
+    const unsigned long long left_f = (c.f << 1) | (cl.f >> 63), left_s = (c.s << 1) | (cl.s >> 63);
+    const unsigned long long right_f = (c.f >> 1) | (cr.f << 63), right_s = (c.s >> 1) | (cr.s << 63);
+    const int q = q0 + lane;
+    if (q >= m.Q) return;
+    const int u0 = m.by_row.div(q0);
+    const int t = q0 - u0 * Nq + lane;
+    const int du = Nq >= kWave ? (t >= Nq ? 1 : 0) : m.by_row.div(t);
+    const int v = t - du * Nq;
+    const int f = lane_bit(c.f), g = lane_bit(c.s);
+    const int r0 = b0 + c.pre + mesh_rank(MeshWindow{c.f, c.s, 0});   // this quad's first triangle
     {
-        const int i1 = u * N + v, i2 = i1 + 1, i3 = i1 + N + 1, i4 = i1 + N;
-        const int at = 3 * (r0 - base0);
-        if (f) { stage[at] = i3; stage[at + 1] = i2; stage[at + 2] = i1; }
-        if (g) { stage[at + 3 * f] = i1; stage[at + 3 * f + 1] = i4; stage[at + 3 * f + 2] = i3; }
-        emit_flush(stage, tris + 3 * (size_t)base0, 3 * nw);
+        // T_map: two entries per quad, -1 for an invalid triangle
+        typedef int i2v __attribute__((ext_vector_type(2)));
+        i2v w;
+        w.x = f ? r0 : -1;
+        w.y = g ? r0 + f : -1;
+        __builtin_nontemporal_store(w, reinterpret_cast<i2v *>(m.tri_map + 2 * (size_t)q));
     }
+    const bool wf = f && r0 < m.cap, wg = g && r0 + f < m.cap;
+    // T: first triangle (p3, p2, p1), second (p1, p4, p3)
+    const int i1 = q + u0 + du, i4 = i1 + m.N;
+    // plain stores: a lane writes 12 of its 24 bytes at a time, which the L2
+    // puts together (with streaming ones a 1200 x 1944 frame's emit took 48.9
+    // us, where these take 22.2 us)
+    int32_t *T0 = m.tris + 3 * (size_t)r0, *T1 = m.tris + 3 * (size_t)(r0 + f);
+    if (wf) { T0[0] = i4 + 1; T0[1] = i1 + 1; T0[2] = i1; }
+    if (wg) { T1[0] = i1; T1[1] = i4; T1[2] = i4 + 1; }
     // HE: Right = (u, v+1, 1), Top = (u-1, v, 1), Left = (u, v-1, 0),
     // Bottom = (u+1, v, 0)
-    if (he) {
-        const int right = (cr & 2) ? r0 + f + g + (cr & 1) : -1;
-        const int left = (cl & 1) ? r0 - popc2(cl) : -1;
-        const int top = (cm & 2) ? rm + (cm & 1) : -1;
-        const int bottom = (cp & 1) ? rp : -1;
-        const int at = 3 * (r0 - base0);
-        if (f) {
-            stage[at] = right >= 0 ? 3 * right : -1;
-            stage[at + 1] = top >= 0 ? 3 * top + 1 : -1;
-            stage[at + 2] = g ? 3 * (r0 + f) + 2 : -1;
-        }
-        if (g) {
-            stage[at + 3 * f] = left >= 0 ? 3 * left : -1;
-            stage[at + 3 * f + 1] = bottom >= 0 ? 3 * bottom + 1 : -1;
-            stage[at + 3 * f + 2] = f ? 3 * r0 + 2 : -1;
-        }
-        emit_flush(stage, he + 3 * (size_t)base0, 3 * nw);
+    if (m.he) {
+        const int rt = bt + top.before + mesh_rank(top), rb = bb + bot.before + mesh_rank(bot);
+        const int lf = lane_bit(left_f), ls = lane_bit(left_s);
+        const int rf = lane_bit(right_f), rs = lane_bit(right_s);
+        const int right_t = rs && v + 1 < Nq ? 3 * (r0 + f + g + rf) : -1;
+        const int left_t = lf && v > 0 ? 3 * (r0 - lf - ls) : -1;
+        const int top_t = lane_bit(top.s) ? 3 * (rt + (int)lane_bit(top.f)) + 1 : -1;
+        const int bot_t = lane_bit(bot.f) ? 3 * rb + 1 : -1;
+        int32_t *H0 = m.he + 3 * (size_t)r0, *H1 = m.he + 3 * (size_t)(r0 + f);
+        if (wf) { H0[0] = right_t; H0[1] = top_t; H0[2] = g ? 3 * (r0 + f) + 2 : -1; }
+        if (wg) { H1[0] = left_t; H1[1] = bot_t; H1[2] = f ? 3 * r0 + 2 : -1; }
     }
 }
 
@@ -789,13 +659,13 @@ __host__ __device__ constexpr size_t bil_lds_bytes(int R, int F, int TQH, int TQ
            (waves ? sizeof(float) * (size_t)bil_xch_floats(R) : 0) + S;
 }
 
-// The mesh's codes and per-segment counts (pl_mesh_opc's first pass): with
+// The mesh's chunks and per-segment counts (pl_mesh_opc's first pass): with
 // them the gather finds each triangle's place in T itself instead of reading
 // T_map, so the pass can run in the same launch as the mesh emit.
 struct GatherCodes {
-    const uint8_t *codes;       // [Mq][Nq] validity codes (bit k: triangle k)
-    const int *seg_count;       // [Mq][S] valid triangles per row segment
-    int S;                      // segments per quad row (mesh_segments(Nq))
+    const MeshChunk *chunks;
+    const uint16_t *seg;
+    int K;                      // chunks of the frame
 };
 
 // Output stores of the filter: streaming for float32 normals, plain for
@@ -1200,42 +1070,35 @@ __device__ __forceinline__ void bil_sweep_waves(const float4 *st, const uint8_t 
 
 // T ranks of a tile's quads for the gather: rank[ty TQW + tx] is the index
 // in T of quad (qy0 + ty, qx0 + tx)'s first valid triangle, with the quad's
-// code in bits 30..31 (T has fewer than 2^30 triangles).  T is the valid
-// triangles in GID order, so the rank is the number of valid triangles in
-// the segments before the quad's row segment, plus those before it in its
-// segment: each wave takes tile rows, sums the counts of the segments
-// before the row's first column and the codes from that segment's start,
-// then scans the row.  Quads off the grid get code 0.  No barrier: the
-// caller's next one publishes the ranks.
+// validity in bits 30..31 (T has fewer than 2^30 triangles).  T is the valid
+// triangles in GID order, so the rank is the count of the segments before the
+// quad's, plus the valid triangles before it in its segment (mesh_window):
+// each wave takes tile rows.  Quads off the grid have no valid triangle.  No
+// barrier: the caller's next one publishes the ranks.
 __device__ __forceinline__ void bil_gather_ranks(const GatherCodes &gc, int Mq, int Nq, int qy0,
                                                  int qx0, int TQH, int TQW, int *rank) {
-    const int lane = (int)threadIdx.x & (kWave - 1), wave = (int)threadIdx.x / kWave;
-    const int s0 = qx0 / kMeshSeg;
+    const int lane = (int)threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     // segments before the tile's first row: the same for every row of it
-    const int k0 = qy0 * gc.S;
-    int before = 0;
-    for (int k = lane; k < k0; k += kWave) before += gc.seg_count[k];
-    before = wave_sum(before);
+    const int k0 = (int)(((long)qy0 * Nq + qx0) / kMeshSeg);
+    const int before = wave_sum(mesh_sum_segs(gc.seg, k0, lane, kWave));
     for (int ty = wave; ty < TQH; ty += kTileBlock / kWave) {
         const int u = qy0 + ty;
-        if (u >= Mq) {
-            for (int tx = lane; tx < TQW; tx += kWave) rank[ty * TQW + tx] = 0;
-            continue;
-        }
-        const uint8_t *row = gc.codes + (size_t)u * Nq;
-        // the rows between, the row's segments before s0, and its codes
-        // from the segment's first column up to qx0
-        int c = 0;
-        for (int k = k0 + lane; k < u * gc.S + s0; k += kWave) c += gc.seg_count[k];
-        for (int v = s0 * kMeshSeg + lane; v < qx0; v += kWave) c += popc2(row[v]);
-        int run = before + wave_sum(c);
         for (int t0 = 0; t0 < TQW; t0 += kWave) {
             const int tx = t0 + lane, v = qx0 + tx;
-            const int code = tx < TQW && v < Nq ? row[v] : 0;
-            const int n = popc2(code);
-            const int incl = wave_inclusive_scan(n);
-            if (tx < TQW) rank[ty * TQW + tx] = (run + incl - n) | (code << 30);
-            run += __shfl(incl, kWave - 1, kWave);
+            int r = 0;
+            if (u < Mq && qx0 + t0 < Nq) {
+                const int q = u * Nq + qx0 + t0;
+                int c = 0;
+                for (int k = k0 + lane; k < q / kMeshSeg; k += kWave) c += gc.seg[k];
+                const int base = before + wave_sum(c);
+                const MeshWindow w = mesh_window(mesh_chunk(gc.chunks, gc.K, q >> 6),
+                                                 mesh_chunk(gc.chunks, gc.K, (q >> 6) + 1), q);
+                if (v < Nq)
+                    r = (base + w.before + mesh_rank(w)) | ((int)lane_bit(w.f) << 30) |
+                        (int)((unsigned)lane_bit(w.s) << 31);
+            }
+            if (tx < TQW) rank[ty * TQW + tx] = r;
         }
     }
 }
@@ -1254,7 +1117,7 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
                                          const int32_t *__restrict__ tri_map, NT *__restrict__ nT,
                                          float4 *lds, const float *__restrict__ pts = nullptr,
                                          float *__restrict__ cen_out = nullptr,
-                                         GatherCodes gc = GatherCodes{nullptr, nullptr, 0}) {
+                                         GatherCodes gc = GatherCodes{}) {
     const int halo = R * F;
     const int H = TQH + 2 * halo, W = TQW + 2 * halo, S = H * W;
     float4 *st = lds;                   // [3][S] staged quads

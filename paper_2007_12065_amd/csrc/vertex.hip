@@ -36,9 +36,7 @@ struct P3 {
     float x, y, z;
 };
 
-__device__ __forceinline__ bool p_ok(P3 p) {
-    return !(is_nan_bits(p.x) || is_nan_bits(p.y) || is_nan_bits(p.z));
-}
+__device__ __forceinline__ bool p_ok(P3 p) { return !any_nan(p.x, p.y, p.z); }
 
 // s += the part of a triangle with corners (a, b, d) and normal n, if `in`
 // (a triangle that does not count has n = 0, and its projection, which an

@@ -152,6 +152,24 @@ def test_row_meshed_frame(pl):
                        "300x7000")
 
 
+def test_frame_and_batch_with_summed_segments(pl):
+    """A frame of more than 16,384 mesh segments, alone and in a batch beside a
+    small one, twice with the large one left out of the second run."""
+    import torch
+    big = spec(random_grid(1100, 4000, 14, nan_frac=0.05), 3, 1.0, 1, 3, 0.1, 0.1, 1)
+    small = spec(random_grid(37, 90, 15), 3, 1.0, 1, 3, 0.1, 0.1, 1)
+    print("[case] pl_smooth_frame 1100x4000", flush=True)
+    want = single(pl, big, torch.float32)
+    assert_frame_equal(pl.pl_smooth_frame(big, torch.float32), want, "1100x4000")
+    b = pl.Batch([big, small], torch.float32)
+    b.run()
+    b.run(torch.tensor([0, 1], dtype=torch.uint8, device="cuda:0"))
+    torch.cuda.synchronize()
+    assert_frame_equal(b.outputs[0], want, "1100x4000 in a batch")
+    assert_frame_equal(b.outputs[1], single(pl, small, torch.float32), "37x90 in a batch")
+    b.close()
+
+
 @pytest.mark.parametrize("dtype_name", ["float32", "float16"])
 def test_groups(pl, dtype_name):
     import torch

@@ -122,6 +122,15 @@ def test_mesh_frames(pl, kind):
     mesh_compare(pl, make_frame(kind, 11))
 
 
+@pytest.mark.parametrize("M,N", [(2, 65), (2, 64), (66, 2), (130, 3), (9, 33), (5, 65), (6, 66), (17, 129),
+                                 (257, 17), (3, 1000), (40, 257), (2, 4000), (1100, 4000)])
+def test_mesh_chunk_edges(pl, M, N):
+    """Quads are meshed in chunks of 64 and segments of 256 across rows: rows
+    shorter and longer than a chunk, remainders of both, and a frame of more
+    than 16,384 segments (1100 x 4000), whose counts a launch of its own sums."""
+    mesh_compare(pl, random_grid(M, N, M + N, nan_frac=0.15))
+
+
 def test_mesh_all_nan_and_cap(pl):
     mesh_compare(pl, np.full((6, 9, 3), np.nan, dtype=np.float32))
     g = random_grid(20, 40, 3, nan_frac=0.2)
