@@ -800,16 +800,36 @@ __device__ __forceinline__ V3 bil_close(bool ok, const V3 &n, BilAcc s, bool &pe
     return ok ? bil_finish<NT>(s, n) : n;
 }
 
+// Minimum and sum over the wave, every lane active, the same on every lane: the
+// tree of pairs 1, 2, 4, 8, 16 and 32 lanes apart.  The first four steps are
+// lane permutations within rows of 16 (by then every lane of a group of 4 or 8
+// holds the group's value, so a mirror reaches the partner group), the four
+// rows' values then meet as scalars.  (As six dependent trips through LDS each,
+// the four reductions of a triangle took about 3,000 clocks at the end of a
+// workgroup.)
+template <int Ctrl> __device__ __forceinline__ float row_perm(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), Ctrl, 0xf, 0xf, true));
+}
+constexpr int kQuadXor1 = 0xb1, kQuadXor2 = 0x4e, kHalfMirror = 0x141, kRowMirror = 0x140;
+
+__device__ __forceinline__ float row_value(float x, int row) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16 * row));
+}
+
 __device__ __forceinline__ float wave_min_f(float x) {
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) x = fminf(x, __shfl_xor(x, m, kWave));
-    return x;
+    x = fminf(x, row_perm<kQuadXor1>(x));
+    x = fminf(x, row_perm<kQuadXor2>(x));
+    x = fminf(x, row_perm<kHalfMirror>(x));
+    x = fminf(x, row_perm<kRowMirror>(x));
+    return fminf(fminf(row_value(x, 0), row_value(x, 1)), fminf(row_value(x, 2), row_value(x, 3)));
 }
 
 __device__ __forceinline__ float wave_sum_f(float x) {
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) x += __shfl_xor(x, m, kWave);
-    return x;
+    x += row_perm<kQuadXor1>(x);
+    x += row_perm<kQuadXor2>(x);
+    x += row_perm<kHalfMirror>(x);
+    x += row_perm<kRowMirror>(x);
+    return (row_value(x, 0) + row_value(x, 1)) + (row_value(x, 2) + row_value(x, 3));
 }
 
 // The underflowed triangle k of the quad at LDS index a, by one whole wave:
