@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kTileBlock) void k_batch_laplacian(const BFrame *__
 
 // FromPts: the first pass (raw normals and centroids from the points).
 template <int R, typename NT, bool FromPts>
-__global__ __launch_bounds__(kTileBlock, kBilWavesPerSimd) void k_batch_bilateral(const BFrame *__restrict__ fr,
+__global__ __launch_bounds__(kTileBlock, bil_waves_per_simd(R, true)) void k_batch_bilateral(const BFrame *__restrict__ fr,
                                                                 const PassFrame *__restrict__ pass,
                                                                 QueueDev Q, int n) {
     extern __shared__ float4 lds[];

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kTileBlock) void k_frame_laplacian(
 // ByCodes: the gathering pass beside the emit, ranking triangles from the
 // mesh codes (GatherCodes) instead of reading T_map.
 template <int R, typename NT, bool FromPts, int Kind, bool ByCodes = false>
-__global__ __launch_bounds__(kTileBlock, kBilWavesPerSimd) void k_frame_bilateral(
+__global__ __launch_bounds__(kTileBlock, bil_waves_per_simd(R, false)) void k_frame_bilateral(
     const NT *__restrict__ nin, const float *__restrict__ cen, NT *__restrict__ nout, int Mq,
     int Nq, float ka, float kb, int F, int TQH, int TQW, int tiles_x, int ntiles,
     int filter_blocks, const int32_t *__restrict__ tri_map, NT *__restrict__ nT,

@@ -622,9 +622,12 @@ __device__ __forceinline__ void normals_block(const float *__restrict__ pts, int
 // ---------------------------------------------------------------------------
 
 constexpr float kBilUnderflow2 = 0x1p-120f;       // (2^-60)^2
-// register budget of the bilateral kernels: at least 6 waves per SIMD
-// (<= 80 VGPRs), more than the LDS of a typical tile lets reside anyway
-constexpr int kBilWavesPerSimd = 6;
+// Register budget of the bilateral kernels, in waves per SIMD: 7 (<= 72 VGPRs)
+// for 3x3 windows and 8 (<= 64) for 5x5 ones in the single-frame kernels, 6
+// (<= 80) elsewhere.  A 720 x 1280 frame takes 83.7 us at 7 (85.1 at 6, 84.5 at
+// 8), a 128 x 2048 one 80.8 us at 8 (81.8 at 6 and 7); the batch, whose lanes
+// hold four partial sums, 231.8 us at 6 (243.6 at 8).
+constexpr int bil_waves_per_simd(int R, bool batch) { return batch || R > 2 ? 6 : R == 1 ? 7 : 8; }
 constexpr float kBilShift = 48.f;                 // every weight is 2^(48 - e)
 constexpr int kBilMaxSweeps = 8;                  // fused sweeps per launch at most
 #ifndef PL_BIL_PARTS_K3
