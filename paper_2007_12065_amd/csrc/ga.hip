@@ -25,8 +25,9 @@
 // non-zero cells into one of kGaReplicas copies of the histogram in the
 // accumulator's workspace (copy = workgroup index mod kGaReplicas, which
 // also keeps each copy on one XCD), and a second launch folds the copies
-// into the caller's counts and clears them.  Sums of integers do not depend
-// on the order of the adds.
+// into the caller's counts and clears them; a small integration adds into
+// the counts at once (kGaDirectWork).  Sums of integers do not depend on the
+// order of the adds.
 #include "ga.h"
 #include "tuning.h"
 
@@ -48,11 +49,15 @@ namespace {
 
 constexpr int kGaBlock = 512;
 constexpr int kGaBatch = 6;                // candidate loads issued together
-#ifndef PL_GA_MAX_GRID
-#define PL_GA_MAX_GRID 768
-#endif
-constexpr int kGaMaxGrid = PL_GA_MAX_GRID;  // workgroups of one integration launch
+constexpr int kGaMaxGrid = 768;             // workgroups of one integration launch
 constexpr int kGaReplicas = 16;             // histogram copies the workgroups flush into
+// Up to kGaDirectWork workgroups' worth of rows go to at most kGaDirectGrid
+// workgroups, which add straight into the caller's counts: that many adds to
+// one address cost less than the second launch.  Microseconds by workgroups'
+// worth of rows (512 each), one launch against two: 30: 3.9, 5.9; 150: 6.2,
+// 6.9; 299: 7.2, 7.6; 450: 10.5, 10.8; past that two are as fast or faster
+// (598: 9.9, 9.3).
+constexpr int kGaDirectGrid = 160, kGaDirectWork = 480;
 
 // Bin of a direction with |n|^2 in [0.25, 4]: the cube face of its largest
 // component (+x, -x, +y, -y, +z, -z), then the two other components over
@@ -106,7 +111,7 @@ template <typename NT>
 __global__ __launch_bounds__(kGaBlock) void k_ga_integrate(
     const NT *__restrict__ normals, const int32_t *__restrict__ n_dev, int cap, int stride,
     const float *__restrict__ cells, int n_cells, const int *__restrict__ bin_start,
-    const float4 *__restrict__ bin_cells, int G, uint32_t *__restrict__ replicas,
+    const float4 *__restrict__ bin_cells, int G, uint32_t *__restrict__ copies, int n_copies,
     int32_t *__restrict__ cell_out) {
     extern __shared__ uint32_t hist[];
     const int n = min(max(*n_dev, 0), cap);
@@ -153,7 +158,7 @@ __global__ __launch_bounds__(kGaBlock) void k_ga_integrate(
         if (c >= 0) atomicAdd(&hist[c], 1u);
     }
     __syncthreads();
-    uint32_t *copy = replicas + (size_t)(blockIdx.x % kGaReplicas) * n_cells;
+    uint32_t *copy = copies + (size_t)(blockIdx.x % n_copies) * n_cells;
     for (int i = threadIdx.x; i < n_cells; i += kGaBlock) {
         const uint32_t v = hist[i];
         if (v) atomicAdd(&copy[i], v);
@@ -474,17 +479,22 @@ pl_status ga_integrate(const pl_ga_s *g, const void *normals, pl_dtype ndt, cons
     uint32_t *reps = reinterpret_cast<uint32_t *>(g->ws + T.off_replicas);
     // one row per thread and pass, at most kGaMaxGrid workgroups (past that,
     // threads loop: fewer histograms to clear and flush)
-    const int grid = (int)std::min<long>(kGaMaxGrid, (rows + kGaBlock - 1) / kGaBlock);
+    const long work = (rows + kGaBlock - 1) / kGaBlock;
+    const bool direct = work <= kGaDirectWork;
+    const int grid = (int)std::min<long>(direct ? kGaDirectGrid : kGaMaxGrid, work);
     const size_t lds = g->lds;
+    uint32_t *copies = direct ? counts : reps;
+    const int n_copies = direct ? 1 : kGaReplicas;
     if (ndt == PL_F32)
         k_ga_integrate<float><<<grid, kGaBlock, lds, s>>>(static_cast<const float *>(normals), n_dev,
                                                           cap, stride, cells, T.n_cells, start, list,
-                                                          T.G, reps, cell_out);
+                                                          T.G, copies, n_copies, cell_out);
     else
         k_ga_integrate<__half><<<grid, kGaBlock, lds, s>>>(static_cast<const __half *>(normals), n_dev,
                                                            cap, stride, cells, T.n_cells, start, list,
-                                                           T.G, reps, cell_out);
+                                                           T.G, copies, n_copies, cell_out);
     if (pl_status st = hip_check(hipGetLastError(), "k_ga_integrate")) return st;
+    if (direct) return PL_OK;
     k_ga_fold<<<(T.n_cells + kGaBlock - 1) / kGaBlock, kGaBlock, 0, s>>>(reps, T.n_cells, counts);
     return hip_check(hipGetLastError(), "k_ga_fold");
 }

@@ -127,6 +127,26 @@ def test_integrate_stride_count_and_accumulation(pl):
     ga.close()
 
 
+@pytest.mark.parametrize("rows", [160 * 512, 160 * 512 + 1, 480 * 512, 480 * 512 + 1])
+def test_integrate_one_or_two_launches(pl, rows):
+    """Up to 480 workgroups' worth of rows are added straight into the counts by
+    at most 160 workgroups; one row more goes through the copies and their
+    fold.  Both on the same accumulator and counts."""
+    import torch
+    _, _, C = oracle.ga_icosahedron(2)
+    rng = np.random.default_rng(rows)
+    N = unit_rows(rng.normal(size=(rows, 3))).astype(np.float32)
+    ga = pl.GaussianAccumulator(cells=C)
+    say("ga launches", rows)
+    counts, cells = ga.integrate(to_dev(N), cell_out=True)
+    counts, _ = ga.integrate(to_dev(N[:1000]), counts=counts)
+    torch.cuda.synchronize()
+    want_idx, want_counts = oracle.ga_integrate(C, N)
+    assert np.array_equal(cells.cpu().numpy(), want_idx)
+    assert np.array_equal(counts.cpu().numpy(), want_counts + oracle.ga_integrate(C, N[:1000])[1])
+    ga.close()
+
+
 def test_integrate_scene_normals(pl, orc):
     """The smoothed normals of a 480x640 frame (the oracle's, float32),
     sampled every 8th row, into a level-4 accumulator: identical to the
