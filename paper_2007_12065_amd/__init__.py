@@ -152,11 +152,19 @@ def _check(status: int, where: str) -> None:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+# The current stream's handle without a Stream object around it (about 1.5 us
+# less per call); torch's public way where this one is missing.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(device) -> int:
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    i = device.index
+    return _raw_stream(torch.cuda.current_device() if i is None else i)
 
 
 def _dev_tensor(t: torch.Tensor, dtype, name: str) -> None:
