@@ -12,25 +12,24 @@
 // quad (r-1, c) (as p4).  Their vertices are the point and six of its eight
 // grid neighbours.  Sweeps are Jacobi: each reads the previous sweep's points.
 //
-// Up to kVuMaxSweeps sweeps run in one launch, temporally blocked in LDS: a
-// tile's points with a halo of F points, and the normals of the quads between
-// them.  Validity and the normals are fixed during the sweeps, so whether a
-// triangle counts is settled once while staging (its normal is staged as zero
-// if it does not), and a sweep has no branches and no NaN tests.  One launch
-// per sweep (a thread per point, everything from L2) was bound by the launch
-// and its memory latency: five sweeps of a 480 x 640 frame 28.2 us, now 19.2
-// us, bound by the sweeps' LDS reads.  Two launches of 3 + 2 sweeps measured 22
-// us, tiles of 8 x 32 or 32 x 32 points 26 us.
-#include "tuning.h"
+// Up to kVuMaxSweeps sweeps run in one launch: a workgroup takes a region of 32
+// x 32 points, of which the inner 32 - 2 F squared are still exact after F
+// sweeps.  A thread owns two points of it, one above the other, for all
+// sweeps: their ten triangles' normals, which of them count (validity and the
+// normals are fixed) and the points themselves stay in its registers, and a
+// sweep reads the eight neighbouring points from LDS and writes its two.  Every
+// read of LDS saved counts: with normals and flags in LDS as well, a point read
+// 13 vectors and 4 bytes a sweep, and five sweeps of a 480 x 640 frame took
+// 19.2 us, now 11.9 us (28.2 us as five launches of a thread per point).
 #include "vu.h"
 
 namespace pl {
 
 namespace {
 
-constexpr int kVuBlock = 512;
-constexpr int kVuTH = 16, kVuTW = 32;         // points per tile
-constexpr int kVuMaxSweeps = 5;
+constexpr int kVuDim = 32;                    // points of a region, each way
+constexpr int kVuBlock = kVuDim * kVuDim / 2;
+constexpr int kVuMaxSweeps = 8;
 
 struct P3 {
     float x, y, z;
@@ -38,16 +37,20 @@ struct P3 {
 
 __device__ __forceinline__ bool p_ok(P3 p) { return !any_nan(p.x, p.y, p.z); }
 
-// s += the part of a triangle with corners (a, b, d) and normal n, if `in`
-// (a triangle that does not count has n = 0, and its projection, which an
+__device__ __forceinline__ P3 vu_sum(P3 a, P3 b, P3 d) {
+    return P3{a.x + b.x + d.x, a.y + b.y + d.y, a.z + b.z + d.z};
+}
+
+// s += the part of a triangle with corner sum t and normal n for vertex x, if
+// `in` (a triangle that does not count has n = 0, and its projection, which an
 // infinite corner would make a NaN, is left out).
 // The centroid through a multiply by the rounded 1/3 (within an ulp of the
 // quotient; an IEEE division would cost ten instructions a component).
-__device__ __forceinline__ void vu_add(P3 x, P3 a, P3 b, P3 d, P3 n, bool in, P3 &s) {
+__device__ __forceinline__ void vu_add(P3 x, P3 t, P3 n, bool in, P3 &s) {
     constexpr float kThird = 1.0f / 3.0f;
-    const float cx = fmaf(a.x + b.x + d.x, kThird, -x.x);
-    const float cy = fmaf(a.y + b.y + d.y, kThird, -x.y);
-    const float cz = fmaf(a.z + b.z + d.z, kThird, -x.z);
+    const float cx = fmaf(t.x, kThird, -x.x);
+    const float cy = fmaf(t.y, kThird, -x.y);
+    const float cz = fmaf(t.z, kThird, -x.z);
     const float p = fmaf(n.x, cx, fmaf(n.y, cy, n.z * cz));
     const float proj = in ? p : 0.f;
     s.x = fmaf(n.x, proj, s.x);
@@ -55,10 +58,10 @@ __device__ __forceinline__ void vu_add(P3 x, P3 a, P3 b, P3 d, P3 n, bool in, P3
     s.z = fmaf(n.z, proj, s.z);
 }
 
-// LDS of a tile with its halo of F points.
-__host__ __device__ constexpr size_t vu_lds_bytes(int F) {
-    const size_t S = (size_t)(kVuTH + 2 * F) * (size_t)(kVuTW + 2 * F);
-    return sizeof(P3) * S * 4 + S;            // two point buffers, two normals per quad, flags
+__device__ __forceinline__ P3 vu_move(P3 x, P3 s, int count) {
+    if (count == 0) return x;
+    const float inv = __builtin_amdgcn_rcpf((float)count);   // count in 1..6
+    return P3{fmaf(s.x, inv, x.x), fmaf(s.y, inv, x.y), fmaf(s.z, inv, x.z)};
 }
 
 template <typename NT>
@@ -66,103 +69,137 @@ __global__ __launch_bounds__(kVuBlock) void k_vertex_update(const float *__restr
                                                             float *__restrict__ out, int M, int N,
                                                             const NT *__restrict__ normals, int F,
                                                             int tiles_x, int ntiles) {
-    extern __shared__ float vu_lds[];
+    // a row and a point of slack on either side: the region's outer points
+    // read past it (what they come to is not used)
+    constexpr int kPad = kVuDim + 1, kSize = kVuDim * kVuDim + 2 * kPad;
+    __shared__ P3 buf[2][kSize];
+    __shared__ uint8_t ok[kSize];
     const int tile = xcd_remap((int)blockIdx.x, ntiles);
-    const int H = kVuTH + 2 * F, W = kVuTW + 2 * F, S = H * W;
-    P3 *A = reinterpret_cast<P3 *>(vu_lds);
-    P3 *B = A + S;
-    P3 *n0 = B + S, *n1 = n0 + S;             // the quad whose p1 is point i
-    uint8_t *ok = reinterpret_cast<uint8_t *>(n1 + S);
-    const int ty0 = (tile / tiles_x) * kVuTH, tx0 = (tile % tiles_x) * kVuTW;
-    const int oy = ty0 - F, ox = tx0 - F;
+    const int inner = kVuDim - 2 * F;
+    const int tx = (int)threadIdx.x % kVuDim, ty = 2 * ((int)threadIdx.x / kVuDim);
+    const int r = (tile / tiles_x) * inner - F + ty, c = (tile % tiles_x) * inner - F + tx;
+    const int at = kPad + ty * kVuDim + tx;      // the upper point
     const int Nq = N - 1;
-    const DivBy byW(W);
-    // points; missing and off-grid ones are staged as zeros with ok = 0
-    for (int i = threadIdx.x; i < S; i += kVuBlock) {
-        const int ly = byW.div(i), lx = i - ly * W;
-        const int r = oy + ly, c = ox + lx;
-        P3 p{0.f, 0.f, 0.f};
-        bool v = false;
-        if (r >= 0 && r < M && c >= 0 && c < N) {
-            const float *q = in + 3 * ((size_t)r * N + c);
-            const P3 g{q[0], q[1], q[2]};
-            v = p_ok(g);
-            if (v) p = g;
+    // both triangles' normals of quad (u, v); off the grid: zero
+    struct Quad {
+        NT n[6];
+        bool in;
+    };
+    auto quad = [&](int u, int v) {
+        Quad q;
+        q.in = (unsigned)u < (unsigned)(M - 1) && (unsigned)v < (unsigned)Nq;
+        if (q.in) {
+            const NT *p = normals + 6 * ((size_t)u * Nq + v);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) q.n[i] = p[i];
         }
-        A[i] = p;
-        B[i] = p;
-        ok[i] = v;
-    }
-    __syncthreads();
-    // normals of the quads inside the region, zero for a triangle that does
-    // not count (a missing corner, a NaN normal)
-    for (int i = threadIdx.x; i < S; i += kVuBlock) {
-        const int ly = byW.div(i), lx = i - ly * W;
-        P3 a{0.f, 0.f, 0.f}, b = a;
-        bool ca = false, cb = false;
-        if (ly + 1 < H && lx + 1 < W) {
-            const bool v1 = ok[i] & 1, v2 = ok[i + 1] & 1, v3 = ok[i + W + 1] & 1, v4 = ok[i + W] & 1;
-            if (v1 && v3 && (v2 || v4)) {     // the quad is on the grid
-                const NT *q = normals + 6 * ((size_t)(oy + ly) * Nq + (ox + lx));
-                const P3 a0{ld_f(q), ld_f(q + 1), ld_f(q + 2)};
-                const P3 b0{ld_f(q + 3), ld_f(q + 4), ld_f(q + 5)};
-                ca = v2 && p_ok(a0);
-                cb = v4 && p_ok(b0);
-                if (ca) a = a0;
-                if (cb) b = b0;
-            }
+        return q;
+    };
+    auto point = [&](int row) {
+        P3 p{qnan(), 0.f, 0.f};
+        if ((unsigned)row < (unsigned)M && (unsigned)c < (unsigned)N) {
+            const float *q = in + 3 * ((size_t)row * N + c);
+            p = P3{q[0], q[1], q[2]};
         }
-        n0[i] = a;
-        n1[i] = b;
-        // bits 1, 2: whether the quad's triangles count (bit 0, the point's
-        // validity, is read by other threads meanwhile and keeps its value)
-        ok[i] = (uint8_t)((ok[i] & 1) | (ca ? 2 : 0) | (cb ? 4 : 0));
-    }
+        return p;
+    };
+    P3 x0 = point(r), x1 = point(r + 1);
+    const Quad q00 = quad(r - 1, c - 1), q01 = quad(r - 1, c), q10 = quad(r, c - 1), q11 = quad(r, c),
+               q20 = quad(r + 1, c - 1), q21 = quad(r + 1, c);
+    const bool v0 = p_ok(x0), v1 = p_ok(x1);
+    if (!v0) x0 = P3{0.f, 0.f, 0.f};
+    if (!v1) x1 = P3{0.f, 0.f, 0.f};
+    buf[0][at] = x0;
+    buf[0][at + kVuDim] = x1;
+    ok[at] = v0;
+    ok[at + kVuDim] = v1;
     __syncthreads();
+    // which triangles count: corners valid, normal without a NaN.  Rows a, b,
+    // c, d are r - 1 .. r + 2; b and c hold this thread's points.
+    const uint8_t *o = ok + at;
+    const bool a0 = o[-kVuDim - 1], a1 = o[-kVuDim], b0 = o[-1], b2 = o[1], c0 = o[kVuDim - 1],
+               c2 = o[kVuDim + 1], d1 = o[2 * kVuDim], d2 = o[2 * kVuDim + 1];
+    auto normal = [](const Quad &q, int k, bool corners, bool &counts) {
+        const P3 n{ld_f(&q.n[3 * k]), ld_f(&q.n[3 * k + 1]), ld_f(&q.n[3 * k + 2])};
+        counts = q.in && corners && p_ok(n);
+        return counts ? n : P3{0.f, 0.f, 0.f};
+    };
+    // triangle 0 of quad (u, v) is (p3, p2, p1), triangle 1 is (p1, p4, p3)
+    bool k00, k01, k11, k20, k21, k30, k31, k40, k41, k50;
+    const P3 n00 = normal(q00, 0, v0 && a1 && a0, k00), n01 = normal(q00, 1, a0 && b0 && v0, k01);
+    const P3 n11 = normal(q01, 1, a1 && v0 && b2, k11);
+    const P3 n20 = normal(q10, 0, v1 && v0 && b0, k20), n21 = normal(q10, 1, b0 && c0 && v1, k21);
+    const P3 n30 = normal(q11, 0, c2 && b2 && v0, k30), n31 = normal(q11, 1, v0 && v1 && c2, k31);
+    const P3 n40 = normal(q21, 0, d2 && c2 && v1, k40), n41 = normal(q21, 1, v1 && d1 && d2, k41);
+    const P3 n50 = normal(q20, 0, d1 && v1 && c0, k50);
+    const int count0 = (int)k30 + (int)k31 + (int)k20 + (int)k00 + (int)k01 + (int)k11;
+    const int count1 = (int)k40 + (int)k41 + (int)k50 + (int)k20 + (int)k21 + (int)k31;
     for (int f = 1; f <= F; ++f) {
-        // points still exact after f sweeps
-        const int h = H - 2 * f, w = W - 2 * f;
-        const DivBy byw(w);
-        for (int k = threadIdx.x; k < h * w; k += kVuBlock) {
-            const int ry = byw.div(k), ly = f + ry, lx = f + (k - ry * w);
-            const int i = ly * W + lx;
-            const int q11 = ok[i], q10 = ok[i - 1], q00 = ok[i - W - 1], q01 = ok[i - W];
-            const int count = ((q11 >> 1) & 1) + ((q11 >> 2) & 1) + ((q10 >> 1) & 1) +
-                              ((q00 >> 1) & 1) + ((q00 >> 2) & 1) + ((q01 >> 2) & 1);
-            const P3 x = A[i];
-            const P3 pr = A[i + 1], pl_ = A[i - 1], pd = A[i + W], pu = A[i - W];
-            const P3 pdr = A[i + W + 1], pul = A[i - W - 1];
-            P3 s{0.f, 0.f, 0.f};
-            // triangle k = 0 of quad (u, v) is (p3, p2, p1), k = 1 is (p1, p4, p3)
-            vu_add(x, pdr, pr, x, n0[i], q11 & 2, s);              // quad (r, c): x = p1
-            vu_add(x, x, pd, pdr, n1[i], q11 & 4, s);
-            vu_add(x, pd, x, pl_, n0[i - 1], q10 & 2, s);          // quad (r, c-1): x = p2
-            vu_add(x, x, pu, pul, n0[i - W - 1], q00 & 2, s);      // quad (r-1, c-1): x = p3
-            vu_add(x, pul, pl_, x, n1[i - W - 1], q00 & 4, s);
-            vu_add(x, pu, x, pr, n1[i - W], q01 & 4, s);           // quad (r-1, c): x = p4
-            if (count) {
-                const float inv = __builtin_amdgcn_rcpf((float)count);   // count in 1..6
-                B[i] = P3{fmaf(s.x, inv, x.x), fmaf(s.y, inv, x.y), fmaf(s.z, inv, x.z)};
-            } else {
-                B[i] = x;
-            }
+        const P3 *A = buf[(f - 1) & 1] + at;
+        const P3 pa0 = A[-kVuDim - 1], pa1 = A[-kVuDim], pb0 = A[-1], pb2 = A[1], pc0 = A[kVuDim - 1],
+                 pc2 = A[kVuDim + 1], pd1 = A[2 * kVuDim], pd2 = A[2 * kVuDim + 1];
+        const P3 t20 = vu_sum(x1, x0, pb0), t31 = vu_sum(x0, x1, pc2);      // of both points
+        P3 s0{0.f, 0.f, 0.f}, s1 = s0;
+        vu_add(x0, vu_sum(pc2, pb2, x0), n30, k30, s0);        // quad (r, c): p1
+        vu_add(x0, t31, n31, k31, s0);
+        vu_add(x0, t20, n20, k20, s0);                         // quad (r, c-1): p2
+        vu_add(x0, vu_sum(x0, pa1, pa0), n00, k00, s0);        // quad (r-1, c-1): p3
+        vu_add(x0, vu_sum(pa0, pb0, x0), n01, k01, s0);
+        vu_add(x0, vu_sum(pa1, x0, pb2), n11, k11, s0);        // quad (r-1, c): p4
+        vu_add(x1, vu_sum(pd2, pc2, x1), n40, k40, s1);
+        vu_add(x1, vu_sum(x1, pd1, pd2), n41, k41, s1);
+        vu_add(x1, vu_sum(pd1, x1, pc0), n50, k50, s1);
+        vu_add(x1, t20, n20, k20, s1);
+        vu_add(x1, vu_sum(pb0, pc0, x1), n21, k21, s1);
+        vu_add(x1, t31, n31, k31, s1);
+        x0 = vu_move(x0, s0, count0);
+        x1 = vu_move(x1, s1, count1);
+        if (f < F) {
+            P3 *B = buf[f & 1] + at;
+            B[0] = x0;
+            B[kVuDim] = x1;
+            __syncthreads();
         }
-        __syncthreads();
-        P3 *t = A; A = B; B = t;
     }
-    // one point per thread: the tile itself; a missing point keeps its bits
-    for (int k = threadIdx.x; k < kVuTH * kVuTW; k += kVuBlock) {
-        const int ty = k / kVuTW, tx = k % kVuTW;
-        const int r = ty0 + ty, c = tx0 + tx;
-        if (r >= M || c >= N) continue;
-        const int i = (F + ty) * W + F + tx;
-        const size_t o = 3 * ((size_t)r * N + c);
-        P3 x = A[i];
-        if (!(ok[i] & 1)) x = P3{in[o], in[o + 1], in[o + 2]};
-        st_stream(&out[o], x.x);
-        st_stream(&out[o + 1], x.y);
-        st_stream(&out[o + 2], x.z);
+    // the exact points of the region; a missing point keeps its bits
+    auto store = [&](int y, int row, P3 x, bool valid) {
+        if (y < F || y >= kVuDim - F || tx < F || tx >= kVuDim - F || row >= M || c >= N) return;
+        const size_t g = 3 * ((size_t)row * N + c);
+        if (!valid) x = P3{in[g], in[g + 1], in[g + 2]};
+        st_stream(&out[g], x.x);
+        st_stream(&out[g + 1], x.y);
+        st_stream(&out[g + 2], x.z);
+    };
+    store(ty, r, x0, v0);
+    store(ty + 1, r + 1, x1, v1);
+}
+
+}  // namespace
+
+namespace {
+
+// Launches for `iterations` sweeps over P points, their sweeps as even as they
+// go: few of many sweeps recompute halos, many of few pay the launch and the
+// points' and normals' way through memory.  In units of one point's sweep, a
+// launch costs about 3.3 M + 2.5 P and F sweeps of it F P (32 / (32 - 2F))^2
+// (measured: five sweeps in one launch and as 3 + 2: 480 x 640 11.9 and 15.2
+// us, 1200 x 1944 64.5 and 66.0; six and 3 + 3: 480 x 640 13.3 and 15.9, 720 x
+// 1280 34.2 and 33.9, 1200 x 1944 83.7 and 75.8).
+int vu_launches(int iterations, double P) {
+    auto sweeps = [P](int F) {
+        const double inner = kVuDim - 2 * F;
+        return F * P * (kVuDim * kVuDim / (inner * inner));
+    };
+    int best = iterations;
+    double least = 1e300;
+    for (int L = (iterations + kVuMaxSweeps - 1) / kVuMaxSweeps; L <= iterations; ++L) {
+        const int F = iterations / L, more = iterations % L;      // `more` launches take F + 1
+        const double cost = L * (3.3e6 + 2.5 * P) + (L - more) * sweeps(F) + (more ? more * sweeps(F + 1) : 0.0);
+        if (cost >= least) break;
+        least = cost;
+        best = L;
     }
+    return best;
 }
 
 }  // namespace
@@ -176,10 +213,7 @@ pl_status launch_vertex_update(const float *in, float *out, int M, int N, const 
     const size_t bytes = 12 * (size_t)M * N;
     if (iterations == 0)
         return hip_check(hipMemcpyAsync(out, in, bytes, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync");
-    const int tiles_x = (N + kVuTW - 1) / kVuTW;
-    const int ntiles = tiles_x * ((M + kVuTH - 1) / kVuTH);
-    // the fewest launches, their sweeps as even as they go
-    const int launches = (iterations + kVuMaxSweeps - 1) / kVuMaxSweeps;
+    const int launches = vu_launches(iterations, (double)M * N);
     const float *src = in;
     int left = iterations;
     for (int l = 0; l < launches; ++l) {
@@ -187,16 +221,15 @@ pl_status launch_vertex_update(const float *in, float *out, int M, int N, const 
         left -= F;
         // the last launch lands in `out`; earlier ones alternate with the workspace
         float *dst = ((launches - 1 - l) % 2 == 0) ? out : static_cast<float *>(ws);
-        const size_t lds = vu_lds_bytes(F);
-        if (ndt == PL_F32) {
-            if (pl_status st = allow_lds((const void *)k_vertex_update<float>, lds)) return st;
-            k_vertex_update<float><<<ntiles, kVuBlock, lds, s>>>(
+        const int inner = kVuDim - 2 * F;
+        const int tiles_x = (N + inner - 1) / inner;
+        const int ntiles = tiles_x * ((M + inner - 1) / inner);
+        if (ndt == PL_F32)
+            k_vertex_update<float><<<ntiles, kVuBlock, 0, s>>>(
                 src, dst, M, N, static_cast<const float *>(normals), F, tiles_x, ntiles);
-        } else {
-            if (pl_status st = allow_lds((const void *)k_vertex_update<__half>, lds)) return st;
-            k_vertex_update<__half><<<ntiles, kVuBlock, lds, s>>>(
+        else
+            k_vertex_update<__half><<<ntiles, kVuBlock, 0, s>>>(
                 src, dst, M, N, static_cast<const __half *>(normals), F, tiles_x, ntiles);
-        }
         if (pl_status st = hip_check(hipGetLastError(), "k_vertex_update")) return st;
         src = dst;
     }

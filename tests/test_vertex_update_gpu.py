@@ -71,12 +71,12 @@ def test_full_frames(pl, orc, kind):
     check(pl, pts, nf, 3)
 
 
-@pytest.mark.parametrize("M,N", [(16, 32), (17, 33), (31, 65), (2, 40), (50, 2)])
+@pytest.mark.parametrize("M,N", [(22, 44), (23, 45), (16, 33), (31, 65), (2, 40), (50, 2)])
 def test_sweeps_over_launches(pl, orc, M, N):
-    """Up to five sweeps share a launch: at the edges of its 16 x 32 tiles, in
-    one, two and three launches."""
+    """Several sweeps share a launch, whose regions of 32 x 32 points keep 32 - 2 F
+    squared: at their edges, in one, two and three launches."""
     g = synth.random_grid(M, N, 7 * M + N, nan_frac=0.1, noise=0.02)
     n, _ = orc.tri_normals(g)
-    for iters in (4, 5, 6, 11):
+    for iters in (1, 3, 4, 5, 6, 8, 11, 17):
         say("vertex update", M, N, "iters", iters)
         check(pl, g, n.astype(np.float32), iters)
