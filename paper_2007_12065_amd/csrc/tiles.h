@@ -772,18 +772,19 @@ __device__ __forceinline__ V3 bil_finish(BilAcc s, const V3 &cur) {
     return V3{round_storage<NT>(s.x * k), round_storage<NT>(s.y * k), round_storage<NT>(s.z * k)};
 }
 
-// Weight of a triangle pair (Eqs. 4-5 with log2(e) folded into ka and kb),
-// shifted by the constant 2^48: 2^(48 - e).  The value depends on the pair
-// only: swapping the triangles changes the sign of every difference exactly
-// and none of the squares.  A pair with an off-grid or missing triangle has
-// e = +inf and weight 0 (NaN only when both are missing; no sum uses that).
-__device__ __forceinline__ float bil_w(const V3 &ci, const V3 &ni, const V3 &cj, const V3 &nj,
-                                       float ka, float kb) {
+// Exponent of a triangle pair's weight (Eqs. 4-5 with log2(e) folded into ka
+// and kb), shifted by the constant 48: the weight is 2^(48 - e).  The value
+// depends on the pair only: swapping the triangles changes the sign of every
+// difference exactly and none of the squares.  A pair with an off-grid or missing
+// triangle has e = +inf and weight 0 (NaN only when both are missing; no sum
+// uses that).
+__device__ __forceinline__ float bil_exponent(const V3 &ci, const V3 &ni, const V3 &cj, const V3 &nj,
+                                              float ka, float kb) {
     const float ax = ni.x - nj.x, ay = ni.y - nj.y, az = ni.z - nj.z;
     const float dn2 = fmaf(ax, ax, fmaf(ay, ay, az * az));
     const float dx = ci.x - cj.x, dy = ci.y - cj.y, dz = ci.z - cj.z;
     const float dc2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    return __builtin_amdgcn_exp2f(-fmaf(dc2, ka, fmaf(dn2, kb, -kBilShift)));
+    return -fmaf(dc2, ka, fmaf(dn2, kb, -kBilShift));
 }
 
 // s += w n
@@ -955,6 +956,13 @@ __device__ __forceinline__ BilAcc bil_reduce(BilAcc (&s)[P / PP]) {
 // The terms of the i-th displacement d of D+ for both triangles of the quad
 // at LDS index a (own centroids c, normals n): the two triangles of quad
 // a + d, then the two of quad a - d.
+//
+// Bound by VALU issue: about 48 clocks per pair and SIMD without the
+// exponential, and an exponential among other instructions costs 15 to 24 more
+// where a row of them takes 8 each.  The eight of a displacement are therefore
+// kept together (the barriers stop the scheduler from spreading them): 128 x
+// 2048 points at 5x5 81.1 to 78.6 us a frame, 64 x 1024 39.6 to 38.8, a batch of
+// seven frames 232.5 to 225.3 us, 3x3 frames 0.1 to 0.2 us less.
 template <int R>
 __device__ __forceinline__ void bil_disp(const float4 *st, int a, int pitch, int plane, float ka,
                                          float kb, int i, const BilQuad &q, BilAcc &s0, BilAcc &s1) {
@@ -962,14 +970,22 @@ __device__ __forceinline__ void bil_disp(const float4 *st, int a, int pitch, int
     bil_dplus<R>(i, dy, dx);
     const int off = dy * pitch + dx;
     const BilQuad p = bil_read(st, a + off, plane), m = bil_read(st, a - off, plane);
-    bil_acc(s0, bil_w(q.c0, q.n0, p.c0, p.n0, ka, kb), p.n0);
-    bil_acc(s0, bil_w(q.c0, q.n0, p.c1, p.n1, ka, kb), p.n1);
-    bil_acc(s0, bil_w(m.c0, m.n0, q.c0, q.n0, ka, kb), m.n0);
-    bil_acc(s0, bil_w(m.c1, m.n1, q.c0, q.n0, ka, kb), m.n1);
-    bil_acc(s1, bil_w(q.c1, q.n1, p.c0, p.n0, ka, kb), p.n0);
-    bil_acc(s1, bil_w(q.c1, q.n1, p.c1, p.n1, ka, kb), p.n1);
-    bil_acc(s1, bil_w(m.c0, m.n0, q.c1, q.n1, ka, kb), m.n0);
-    bil_acc(s1, bil_w(m.c1, m.n1, q.c1, q.n1, ka, kb), m.n1);
+    const V3 c[4] = {p.c0, p.c1, m.c0, m.c1}, n[4] = {p.n0, p.n1, m.n0, m.n1};
+    float w[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        w[k] = bil_exponent(q.c0, q.n0, c[k], n[k], ka, kb);
+        w[4 + k] = bil_exponent(q.c1, q.n1, c[k], n[k], ka, kb);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = __builtin_amdgcn_exp2f(w[k]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        bil_acc(s0, w[k], n[k]);
+        bil_acc(s1, w[4 + k], n[k]);
+    }
 }
 
 // Both triangles of the quad at LDS index a, in the fixed summation order:
@@ -977,9 +993,8 @@ __device__ __forceinline__ void bil_disp(const float4 *st, int a, int pitch, int
 // a + d, then the two of quad a - d; the parts' partial sums are added in a
 // fixed tree.  This lane (`lane` of PP) runs parts lane, lane + PP, ...: the
 // i-th displacement belongs to part i mod P, whose set here is
-// (i mod P) / PP.  A pair weight takes its lower quad's triangle first
-// (bil_w is symmetric anyway).  Every lane of the quad returns the same r0,
-// r1 and pending flags.
+// (i mod P) / PP.  Every lane of the quad returns the same r0, r1 and pending
+// flags.
 template <int R, typename NT, int PP>
 __device__ __forceinline__ void bil_sum_quad(const float4 *st, int a, int pitch, int plane, float ka,
                                              float kb, int lane, const BilQuad &q, const uint8_t *flag,
