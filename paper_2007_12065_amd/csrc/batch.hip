@@ -65,8 +65,6 @@ struct BFrame {
     int M, N, Mq, Nq;
     int Rl, Rb;
     float lam, ka, kb;
-    int lap_th, lap_tw, lap_tiles_x;
-    int bil_th, bil_tw, bil_tiles_x;
     const float *dom;              // group assignment (groups != nullptr)
     uint8_t *groups;
     int n_dom;
@@ -78,6 +76,7 @@ struct PassFrame {                 // one frame's part of one sweep pass
     void *dst;
     int F;                         // sweeps in this pass (0: copy)
     int gather;                    // bilateral: last pass, gather onto T
+    int th, tw, tiles_x;           // its tiles
 };
 
 struct QueueDev {                  // one stage's tile queue, in the workspace
@@ -174,9 +173,9 @@ __global__ __launch_bounds__(kTileBlock) void k_batch_laplacian(const BFrame *__
     PL_QUEUE_TILE(Q, n, t)
     const BFrame &f = fr[t.x];
     const PassFrame &p = pass[t.x];
-    const int ty0 = (t.y / f.lap_tiles_x) * f.lap_th, tx0 = (t.y % f.lap_tiles_x) * f.lap_tw;
+    const int ty0 = (t.y / p.tiles_x) * p.th, tx0 = (t.y % p.tiles_x) * p.tw;
     lap_tile<R>(static_cast<const float *>(p.src), static_cast<float *>(p.dst), f.M, f.N, f.lam,
-                p.F, f.lap_th, f.lap_tw, ty0, tx0, lds);
+                p.F, p.th, p.tw, ty0, tx0, lds);
 }
 
 // FromPts: the first pass (raw normals and centroids from the points).
@@ -188,10 +187,10 @@ __global__ __launch_bounds__(kTileBlock, bil_waves_per_simd(R, true)) void k_bat
     PL_QUEUE_TILE(Q, n, t)
     const BFrame &f = fr[t.x];
     const PassFrame &p = pass[t.x];
-    const int qy0 = (t.y / f.bil_tiles_x) * f.bil_th, qx0 = (t.y % f.bil_tiles_x) * f.bil_tw;
+    const int qy0 = (t.y / p.tiles_x) * p.th, qx0 = (t.y % p.tiles_x) * p.tw;
     bil_tile<R, NT, FromPts, false, bil_batch_lanes<R>()>(
         FromPts ? nullptr : static_cast<const NT *>(p.src), f.centroids, static_cast<NT *>(p.dst),
-        f.Mq, f.Nq, f.ka, f.kb, p.F, f.bil_th, f.bil_tw, qy0, qx0, p.gather ? f.tri_map : nullptr,
+        f.Mq, f.Nq, f.ka, f.kb, p.F, p.th, p.tw, qy0, qx0, p.gather ? f.tri_map : nullptr,
         static_cast<NT *>(f.normals_T), lds, f.pts_out, f.centroids);
 }
 
@@ -239,6 +238,11 @@ struct Pass {                      // one sweep pass: one launch per window radi
 size_t nt_size(pl_dtype ndt) { return ndt == PL_F32 ? 4 : 2; }
 
 int passes_for(int iters, int fuse) { return iters == 0 ? 1 : (iters + fuse - 1) / fuse; }
+// sweeps of pass p
+int sweeps_in(int iters, int fuse, int p) { return std::min(iters - p * fuse, fuse); }
+int tiles_of(int rows, int cols, TileCfg c) {
+    return ((cols + c.tw - 1) / c.tw) * ((rows + c.th - 1) / c.th);
+}
 
 }  // namespace
 
@@ -308,11 +312,12 @@ size_t batch_layout(const pl_frame *frames, int n, pl_dtype ndt, pl_batch_s *pla
         b.mesh_sums |= b.mc.count[i] > kMeshSegMax;
         const TileCfg cl = tile_cfg(kStageBatchLaplacian, f.kernel_lap / 2);
         const TileCfg cb = tile_cfg(kStageBatchBilateral, f.kernel_bil / 2);
-        const int ltiles = ((f.N + cl.tw - 1) / cl.tw) * ((f.M + cl.th - 1) / cl.th);
-        const int btiles = ((Nq + cb.tw - 1) / cb.tw) * ((Mq + cb.th - 1) / cb.th);
+        const int ltiles = tiles_of(f.M, f.N, cl);
         const int lp = passes_for(f.iters_lap, cl.fuse), bp = passes_for(f.iters_bil, cb.fuse);
         for (int p = 0; p < lp; ++p) b.lap[p].q[f.kernel_lap / 2 - 1].count[i] = ltiles;
-        for (int p = 0; p < bp; ++p) b.bil[p].q[f.kernel_bil / 2 - 1].count[i] = btiles;
+        for (int p = 0; p < bp; ++p)
+            b.bil[p].q[f.kernel_bil / 2 - 1].count[i] =
+                tiles_of(Mq, Nq, bil_launch_tile(f.kernel_bil / 2, cb, sweeps_in(f.iters_bil, cb.fuse, p)));
         const long rows_per_tile = (long)kGroupBlock * kGroupPer;
         if (f.groups) b.grp.count[i] = (int)((2L * Mq * Nq + rows_per_tile - 1) / rows_per_tile);
     }
@@ -369,8 +374,6 @@ size_t batch_layout(const pl_frame *frames, int n, pl_dtype ndt, pl_batch_s *pla
         d.ka = log2e / (2.0f * f.sigma_length * f.sigma_length);
         d.kb = log2e / (2.0f * f.sigma_angle * f.sigma_angle);
         const TileCfg cl = tile_cfg(kStageBatchLaplacian, d.Rl), cb = tile_cfg(kStageBatchBilateral, d.Rb);
-        d.lap_th = cl.th; d.lap_tw = cl.tw; d.lap_tiles_x = (f.N + cl.tw - 1) / cl.tw;
-        d.bil_th = cb.th; d.bil_tw = cb.tw; d.bil_tiles_x = (f.N - 1 + cb.tw - 1) / cb.tw;
         d.dom = f.groups ? f.dominant : nullptr;
         d.groups = f.groups;
         d.n_dom = f.groups ? f.n_dominant : 0;
@@ -378,23 +381,20 @@ size_t batch_layout(const pl_frame *frames, int n, pl_dtype ndt, pl_batch_s *pla
         d.ang_min = f.groups ? f.ang_min : 0.0f;
         // sweep passes, the last of each stage landing in the caller's output
         const int lp = passes_for(f.iters_lap, cl.fuse);
-        int left = f.iters_lap;
         const void *src = f.pts;
         for (int p = 0; p < lp; ++p) {
-            const int F = left < cl.fuse ? left : cl.fuse;
-            left -= F;
+            const int F = sweeps_in(f.iters_lap, cl.fuse, p);
             void *dst = ((lp - 1 - p) % 2 == 0) ? static_cast<void *>(f.pts_out) : static_cast<void *>(d.lap_tmp);
-            b.lap[p].tab[i] = PassFrame{src, dst, F, 0};
+            b.lap[p].tab[i] = PassFrame{src, dst, F, 0, cl.th, cl.tw, (d.N + cl.tw - 1) / cl.tw};
             src = dst;
         }
         const int bp = passes_for(f.iters_bil, cb.fuse);
-        left = f.iters_bil;
         src = f.pts_out;                 // first pass: from the smoothed points
         for (int p = 0; p < bp; ++p) {
-            const int F = left < cb.fuse ? left : cb.fuse;
-            left -= F;
+            const int F = sweeps_in(f.iters_bil, cb.fuse, p);
+            const TileCfg c = bil_launch_tile(d.Rb, cb, F);
             void *dst = ((bp - 1 - p) % 2 == 0) ? f.normals : d.bil_tmp;
-            b.bil[p].tab[i] = PassFrame{src, dst, F, p == bp - 1};
+            b.bil[p].tab[i] = PassFrame{src, dst, F, p == bp - 1, c.th, c.tw, (d.Nq + c.tw - 1) / c.tw};
             src = dst;
         }
     }
@@ -455,8 +455,8 @@ pl_status plan_grids(pl_batch_s &b, const pl_frame *frames) {
             size_t lds = 0;
             for (int i = 0; i < b.n; ++i) {
                 if (!p.q[r].count[i]) continue;
-                const TileCfg c = tile_cfg(kStageBatchLaplacian, r + 1);
-                lds = std::max(lds, lap_lds_bytes(r + 1, p.tab[i].F, c.th, c.tw));
+                const PassFrame &t = p.tab[i];
+                lds = std::max(lds, lap_lds_bytes(r + 1, t.F, t.th, t.tw));
             }
             if (pl_status st = size_grid(p.q[r], lap_k[r], lds)) return st;
         }
@@ -466,8 +466,8 @@ pl_status plan_grids(pl_batch_s &b, const pl_frame *frames) {
             size_t lds = 0;
             for (int i = 0; i < b.n; ++i) {
                 if (!p.q[r].count[i]) continue;
-                const TileCfg c = tile_cfg(kStageBatchBilateral, r + 1);
-                lds = std::max(lds, bil_lds_bytes(r + 1, p.tab[i].F, c.th, c.tw, bil_waves(r + 1, true)));
+                const PassFrame &t = p.tab[i];
+                lds = std::max(lds, bil_lds_bytes(r + 1, t.F, t.th, t.tw, bil_waves(r + 1, true)));
             }
             if (pl_status st = size_grid(p.q[r], bil_k[pi == 0][r], lds)) return st;
         }

@@ -28,8 +28,6 @@ pl_status run(const NT *nin, const float *cen, int M, int N, float sl, float sa,
               NT *nout, const int32_t *tri_map, NT *nT, NT *tmp, hipStream_t s) {
     const TileCfg c = tile_cfg(frame_stage(false, M, N), R);
     const int Mq = M - 1, Nq = N - 1;
-    const int tiles_x = (Nq + c.tw - 1) / c.tw;
-    const int ntiles = tiles_x * ((Mq + c.th - 1) / c.th);
     const float log2e = 1.4426950408889634f;
     const float ka = log2e / (2.0f * sl * sl);
     const float kb = log2e / (2.0f * sa * sa);
@@ -42,10 +40,13 @@ pl_status run(const NT *nin, const float *cen, int M, int N, float sl, float sa,
         left -= F;
         const bool last = l == launches - 1;
         NT *dst = ((launches - 1 - l) % 2 == 0) ? nout : tmp;    // last launch lands in nout
-        const size_t lds = bil_lds_bytes(R, F, c.th, c.tw, bil_waves(R, false));
+        const TileCfg t = bil_launch_tile(R, c, F);
+        const int tiles_x = (Nq + t.tw - 1) / t.tw;
+        const int ntiles = tiles_x * ((Mq + t.th - 1) / t.th);
+        const size_t lds = bil_lds_bytes(R, F, t.th, t.tw, bil_waves(R, false));
         if (pl_status st = allow_lds((const void *)k_bilateral<R, NT>, lds)) return st;
         k_bilateral<R, NT><<<ntiles, kTileBlock, lds, s>>>(cur, cen, dst, Mq, Nq, ka, kb, F,
-                                                            c.th, c.tw, tiles_x, ntiles,
+                                                            t.th, t.tw, tiles_x, ntiles,
                                                             last ? tri_map : nullptr, nT);
         if (pl_status st = hip_check(hipGetLastError(), "k_bilateral")) return st;
         cur = dst;

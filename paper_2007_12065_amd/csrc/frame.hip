@@ -19,7 +19,7 @@
 // launch.  When that one is the gathering bilateral pass, the gather cannot
 // read T_map (written by the same launch): it ranks each triangle in T
 // from the mesh's masks and segment counts instead (the same numbers), so a
-// 480 x 640 frame whose two bilateral sweeps fuse into one pass takes two
+// frame of up to four 3x3 Laplacian sweeps and two bilateral ones takes two
 // launches.
 //
 // A launch that carries mesh work has two kinds of workgroups: the filter's
@@ -145,6 +145,7 @@ template <int R, typename NT, bool FromPts, int Kind, bool ByCodes = false>
 pl_status bil_launch(const NT *nin, const float *cen, NT *nout, int Mq, int Nq, float ka,
                      float kb, int F, TileCfg c, const int32_t *tri_map, NT *nT,
                      const float *pts, float *cen_out, const MeshArgs &mj, hipStream_t s) {
+    c = bil_launch_tile(R, c, F);
     const int tiles_x = (Nq + c.tw - 1) / c.tw;
     const int ntiles = tiles_x * ((Mq + c.th - 1) / c.th);
     const int fb = Kind == kMeshNone ? ntiles : round8(ntiles);

@@ -615,19 +615,19 @@ __device__ __forceinline__ void normals_block(const float *__restrict__ pts, int
 // input bits).  Float16-stored normals produced by an intermediate sweep are
 // re-rounded to float16, as if stored between launches, so results do not
 // depend on F.  F = 0 copies the tile (and gathers).
-// LDS: (TQH + 2RF) * (TQW + 2RF) quads of 48 bytes, twice with F > 1 (a sweep
-// writes the second buffer, centroids along), a byte of flags per quad and
-// the queue of underflowed triangles (16 bits per triangle of the region, and
-// its counts).
+// LDS: (TQH + 2RF) * (TQW + 2RF) quads of 48 bytes, twice with F > 1 unless
+// the sweeps run in place (bil_in_place; else a sweep writes the second buffer,
+// centroids along), a byte of flags per quad and the queue of underflowed
+// triangles (16 bits per triangle of the region, and its counts).
 // ---------------------------------------------------------------------------
 
 constexpr float kBilUnderflow2 = 0x1p-120f;       // (2^-60)^2
-// Register budget of the bilateral kernels, in waves per SIMD: 7 (<= 72 VGPRs)
-// for 3x3 windows and 8 (<= 64) for 5x5 ones in the single-frame kernels, 6
-// (<= 80) elsewhere.  A 720 x 1280 frame takes 83.7 us at 7 (85.1 at 6, 84.5 at
-// 8), a 128 x 2048 one 80.8 us at 8 (81.8 at 6 and 7); the batch, whose lanes
-// hold four partial sums, 231.8 us at 6 (243.6 at 8).
-constexpr int bil_waves_per_simd(int R, bool batch) { return batch || R > 2 ? 6 : R == 1 ? 7 : 8; }
+// Register budget of the bilateral kernels, in waves per SIMD: 8 (<= 64 VGPRs)
+// for 3x3 and 5x5 windows in the single-frame kernels, 6 (<= 80) elsewhere.  A
+// 720 x 1280 frame takes 77.7 us at 8 (79.2 at 7), a 128 x 2048 one 80.8 us at
+// 8 (81.8 at 6 and 7); the batch, whose lanes hold four partial sums at 5x5,
+// 231.8 us at 6 (243.6 at 8), and its 3x3 kernels are the same at 6, 7 and 8.
+constexpr int bil_waves_per_simd(int R, bool batch) { return batch || R > 2 ? 6 : 8; }
 constexpr float kBilShift = 48.f;                 // every weight is 2^(48 - e)
 constexpr int kBilMaxSweeps = 8;                  // fused sweeps per launch at most
 #ifndef PL_BIL_PARTS_K3
@@ -654,9 +654,16 @@ __host__ __device__ constexpr bool bil_waves(int R, bool batch) {
 __host__ __device__ constexpr int bil_xch_floats(int R) {
     return R >= 2 ? (PL_BIL_PARTS_K5 - 1) * 6 * 64 : 0;
 }
+// Whether a launch of F sweeps runs the sweeps before the last in place: every
+// quad of their regions has a thread of its own (3x3 windows), which keeps its
+// result in registers until all have read.
+__host__ __device__ constexpr bool bil_in_place(int R, int F, int TQH, int TQW) {
+    return R == 1 && PL_BIL_PARTS_K3 == 1 && F > 1 &&
+           (long)(TQH + 2 * (F - 1)) * (TQW + 2 * (F - 1)) <= kTileBlock;
+}
 __host__ __device__ constexpr size_t bil_lds_bytes(int R, int F, int TQH, int TQW, bool waves) {
     const size_t S = (size_t)(TQH + 2 * R * F) * (size_t)(TQW + 2 * R * F);
-    return (F > 1 ? 6 : 3) * sizeof(float4) * S +
+    return (F > 1 && !bil_in_place(R, F, TQH, TQW) ? 6 : 3) * sizeof(float4) * S +
            sizeof(int) * (kBilMaxSweeps + 1) + sizeof(uint16_t) * 2 * S +
            sizeof(int) * (size_t)TQH * TQW +    // T ranks of the tile (gather from the mesh codes)
            (waves ? sizeof(float) * (size_t)bil_xch_floats(R) : 0) + S;
@@ -711,6 +718,11 @@ __device__ __forceinline__ void bil_write(float4 *s, int a, int plane, const V3 
                                           const V3 &n0, const V3 &n1) {
     s[a] = make_float4(c0.x, c0.y, c0.z, c1.x);
     s[plane + a] = make_float4(c1.y, c1.z, n0.x, n0.y);
+    s[2 * plane + a] = make_float4(n0.z, n1.x, n1.y, n1.z);
+}
+
+__device__ __forceinline__ void bil_write_normals(float4 *s, int a, int plane, const V3 &n0, const V3 &n1) {
+    *reinterpret_cast<float2 *>(&s[plane + a].z) = make_float2(n0.x, n0.y);
     s[2 * plane + a] = make_float4(n0.z, n1.x, n1.y, n1.z);
 }
 
@@ -1158,9 +1170,10 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
                                          GatherCodes gc = GatherCodes{}) {
     const int halo = R * F;
     const int H = TQH + 2 * halo, W = TQW + 2 * halo, S = H * W;
+    const bool in_place = bil_in_place(R, F, TQH, TQW);
     float4 *st = lds;                   // [3][S] staged quads
-    float4 *st2 = lds + 3 * S;          // [3][S] the next sweep's (F > 1)
-    int *counts = reinterpret_cast<int *>(lds + (F > 1 ? 6 : 3) * S);
+    float4 *st2 = lds + 3 * S;          // [3][S] the next sweep's (F > 1, not in place)
+    int *counts = reinterpret_cast<int *>(lds + (F > 1 && !in_place ? 6 : 3) * S);
     if (threadIdx.x < kBilMaxSweeps + 1) counts[threadIdx.x] = 0;
     // T ranks of the tile when the gather takes them from the mesh codes
     int *rank = counts + kBilMaxSweeps + 1;
@@ -1285,8 +1298,49 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
         else
             bil_sweep<R, NT, PP>(cur, flag, W, S, o0, o0, OH, OW, ka, kb, pre, out);
     };
-    // intermediate sweeps: LDS to LDS over the shrinking exact region
-    for (int f = 1; f < F; ++f) {
+    // Intermediate sweeps over the shrinking exact region, in place: a quad's
+    // normals stay in its thread's registers until every thread has read, and a
+    // wave sums the underflowed triangles of its own quads.  With one buffer eight
+    // workgroups fit a CU where two buffers left four, so two sweeps fused beat two
+    // launches on large frames too: the second launch's read of normals and
+    // centroids and the first one's store of normals (66 of 240 MB on a 720 x 1280
+    // frame) outweigh the halo computed twice.  480 x 640 frame 35.4 to 33.7 us,
+    // 720 x 1280 83.3 to 77.7, a batch of seven frames 231 to 216 (between two
+    // buffers such a tile took 91 us at 720 x 1280).
+    if constexpr (R == 1 && PP == 1) {
+        if (in_place) {
+            for (int f = 1; f < F; ++f) {
+                const int lo = R * f, OH = H - 2 * lo, OW = W - 2 * lo;
+                const DivBy byOW(OW);
+                const int idx = (int)threadIdx.x;
+                const bool have = idx < OH * OW;
+                const int ry = have ? byOW.div(idx) : 0, rx = have ? idx - ry * OW : 0;
+                const int a = (lo + ry) * W + lo + rx;
+                V3 r[2];
+                bool pend[2] = {false, false};
+                if (have) {
+                    const BilQuad q = bil_read(st, a, S);
+                    int fl;
+                    bil_sum_quad<R, NT, PP>(st, a, W, S, ka, kb, 0, q, flag, fl, r[0], r[1], pend[0],
+                                            pend[1]);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    for (unsigned long long m = __ballot(pend[k]); m; m &= m - 1) {
+                        const int l = __builtin_ctzll(m);
+                        const V3 x = bil_fallback_wave<R, NT>(st, __builtin_amdgcn_readlane(a, l), k, W, S,
+                                                              ka, kb);
+                        if (lane == l) r[k] = x;
+                    }
+                }
+                __syncthreads();
+                if (have) bil_write_normals(st, a, S, r[0], r[1]);
+                __syncthreads();
+            }
+        }
+    }
+    // else from one buffer to the other
+    for (int f = in_place ? F : 1; f < F; ++f) {
         const int lo = R * f;
         sweep(lo, H - 2 * lo, W - 2 * lo, [](int, int) { return make_int2(-1, -1); },
               [&](int, int, int a, const BilQuad &q, int, int2, const V3 &r0, const V3 &r1, bool p0, bool p1) {

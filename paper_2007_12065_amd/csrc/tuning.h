@@ -34,6 +34,11 @@ struct TileCfg {
     int fuse;        // sweeps fused per launch
 };
 
+// Tile of a bilateral launch of F of the c.fuse sweeps (the last launch may have
+// fewer): where they run in place, it grows by the halo it does not need, so
+// that every thread keeps a quad.
+TileCfg bil_launch_tile(int R, TileCfg c, int F);
+
 // Current configuration for a stage and window radius (1..4).
 TileCfg tile_cfg(Stage s, int R);
 // Replace it; returns false if the shape does not fit the kernels' limits.

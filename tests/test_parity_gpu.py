@@ -269,6 +269,34 @@ def test_bilateral_lidar128(pl):
                                               k.sigma_angle, k.iters_bil, THREADS))
 
 
+@pytest.mark.parametrize("dtype_name", ["float32", "float16"])
+@pytest.mark.parametrize("M,N", [(2, 2), (7, 31), (8, 32), (14, 62), (21, 18), (40, 95)])
+def test_bilateral_sweeps_in_place(pl, M, N, dtype_name):
+    # sweeps fused in place (one buffer) or between two, against one sweep per
+    # launch: the same bits, with missing triangles and, from the scaled
+    # centroids, underflowed sums in every sweep
+    import torch
+    g = random_grid(M, N, seed=7 * M + N, nan_frac=0.1, noise=0.02)
+    n, c = bil_inputs(g)
+    n = to_dev(n).to(getattr(torch, dtype_name))
+    saved = [(st, pl.pl_tune_get(st, 3)) for st in (1, 5)]
+    try:
+        for scale in (1.0, 30.0):
+            cd = to_dev((c * scale).astype(np.float32))
+            for iters in (1, 2, 3, 5):
+                want = None
+                for cfg in [(8, 32, 1), (6, 30, 2), (12, 16, 2), (4, 32, 2), (4, 28, 3), (4, 32, 3)]:
+                    for st in (1, 5):
+                        pl.pl_tune_set(st, 3, *cfg)
+                    say("in place", (M, N), dtype_name, "scale", scale, "iters", iters, "tile", cfg)
+                    out = host(pl.pl_bilateral(n, cd, 3, 0.1, 0.3, iters)[0]).view(np.uint8)
+                    want = out if want is None else want
+                    assert np.array_equal(out, want)
+    finally:
+        for st, cfg in saved:
+            pl.pl_tune_set(st, 3, *cfg)
+
+
 def test_bilateral_far_neighbourhood(pl):
     # every neighbour 5 m away with sigma_length 0.1: all weights underflow
     # unless the exponents are shifted; the renormalised mean is still defined
