@@ -370,6 +370,10 @@ void pl_ga_destroy(pl_ga ga);
  * entry.  The table is process-wide; pl_tune_set is meant for a
  * tuner run before work is enqueued (it does not affect launches already
  * enqueued or plans already created).
+ * Single frames whose fused 3x3 bilateral sweeps run in place (the tile with the
+ * halo of all sweeps but one has at most 256 quads) may use a part of the
+ * tile's rows where the frame has few tiles, and launches of fewer than `fuse`
+ * sweeps a tile larger by the halo they do not need.
  * kernel      odd window size, 3..9.
  * tile_rows * tile_cols <= 16384; the LDS the shape needs must fit 156 KB.
  * Returns PL_ERR_KERNEL / PL_ERR_ARG for an invalid request.

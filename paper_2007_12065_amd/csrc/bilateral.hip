@@ -40,7 +40,7 @@ pl_status run(const NT *nin, const float *cen, int M, int N, float sl, float sa,
         left -= F;
         const bool last = l == launches - 1;
         NT *dst = ((launches - 1 - l) % 2 == 0) ? nout : tmp;    // last launch lands in nout
-        const TileCfg t = bil_launch_tile(R, c, F);
+        const TileCfg t = bil_frame_tile(R, c, F, Mq, Nq);
         const int tiles_x = (Nq + t.tw - 1) / t.tw;
         const int ntiles = tiles_x * ((Mq + t.th - 1) / t.th);
         const size_t lds = bil_lds_bytes(R, F, t.th, t.tw, bil_waves(R, false));

@@ -12,6 +12,7 @@ namespace pl {
 
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kNumXcd = 8;       // MI355X: 8 accelerator complex dies, 32 CUs each
+constexpr int kNumCu = 256;      // in all
 
 // Whether any of three values is NaN: two unordered comparisons (each takes
 // two operands), where three bit-pattern tests take six instructions.  The

@@ -145,7 +145,7 @@ template <int R, typename NT, bool FromPts, int Kind, bool ByCodes = false>
 pl_status bil_launch(const NT *nin, const float *cen, NT *nout, int Mq, int Nq, float ka,
                      float kb, int F, TileCfg c, const int32_t *tri_map, NT *nT,
                      const float *pts, float *cen_out, const MeshArgs &mj, hipStream_t s) {
-    c = bil_launch_tile(R, c, F);
+    c = bil_frame_tile(R, c, F, Mq, Nq);
     const int tiles_x = (Nq + c.tw - 1) / c.tw;
     const int ntiles = tiles_x * ((Mq + c.th - 1) / c.th);
     const int fb = Kind == kMeshNone ? ntiles : round8(ntiles);

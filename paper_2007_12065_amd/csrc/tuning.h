@@ -38,6 +38,14 @@ struct TileCfg {
 // fewer): where they run in place, it grows by the halo it does not need, so
 // that every thread keeps a quad.
 TileCfg bil_launch_tile(int R, TileCfg c, int F);
+// The same for a single frame of Mq x Nq quads.  Tiles of an in-place shape may
+// first be cut to two thirds or half of their rows (6 x 30 quads to 4 x 32 or
+// 3 x 32): of the three the one that gives a CU the fewest tiles, then the one
+// of fewest rows (a small frame's launch takes as long as the CU with the most
+// rows).  At 6, 4 and 3 rows a 120 x 160 frame takes 13.5, 13.0 and 12.4 us (one
+// tile per CU each), a 200 x 220 one 15.7, 14.9 and 15.4 (2, 2 and 3 tiles), a
+// 240 x 320 one 16.6, 17.7 and 17.5 (2, 3 and 4).
+TileCfg bil_frame_tile(int R, TileCfg c, int F, int Mq, int Nq);
 
 // Current configuration for a stage and window radius (1..4).
 TileCfg tile_cfg(Stage s, int R);

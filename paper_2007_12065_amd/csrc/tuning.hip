@@ -25,8 +25,9 @@ TileCfg g_cfg[kNumStages][kMaxRadius + 1] = {
     {{0, 0, 0}, {12, 16, 2}, {16, 16, 1}, {8, 32, 1}, {8, 32, 1}},
     // Laplacian, small frames (120x160, 64x1024)
     {{0, 0, 0}, {8, 16, 4}, {8, 16, 2}, {8, 32, 1}, {8, 32, 1}},
-    // bilateral, small frames
-    {{0, 0, 0}, {4, 32, 2}, {2, 32, 1}, {4, 16, 1}, {4, 16, 1}},
+    // bilateral, small frames (3x3: cut to fewer rows where a frame has few
+    // tiles, bil_frame_tile)
+    {{0, 0, 0}, {6, 30, 2}, {2, 32, 1}, {4, 16, 1}, {4, 16, 1}},
 };
 
 // gfx950 LDS per workgroup, less room for the batched kernels' static LDS
@@ -43,6 +44,20 @@ TileCfg bil_launch_tile(int R, TileCfg c, int F) {
     if (!bil_in_place(R, c.fuse, c.th, c.tw) || F >= c.fuse) return c;
     const int grow = 2 * R * (c.fuse - std::max(F, 1));
     return TileCfg{c.th + grow, c.tw + grow, c.fuse};
+}
+
+TileCfg bil_frame_tile(int R, TileCfg c, int F, int Mq, int Nq) {
+    if (!bil_in_place(R, c.fuse, c.th, c.tw)) return c;
+    auto per_cu = [&](const TileCfg &cfg) {
+        const TileCfg t = bil_launch_tile(R, cfg, F);
+        const long tiles = (long)((Mq + t.th - 1) / t.th) * ((Nq + t.tw - 1) / t.tw);
+        return (tiles + kNumCu - 1) / kNumCu;
+    };
+    TileCfg best = c;
+    for (const TileCfg &t : {TileCfg{c.th * 2 / 3, c.tw + 2, c.fuse}, TileCfg{c.th / 2, c.tw + 2, c.fuse}})
+        if (t.th > 0 && t.th < best.th && bil_in_place(R, t.fuse, t.th, t.tw) && per_cu(t) <= per_cu(best))
+            best = t;
+    return bil_launch_tile(R, best, F);
 }
 
 TileCfg tile_cfg(Stage s, int R) {

@@ -270,7 +270,7 @@ def test_bilateral_lidar128(pl):
 
 
 @pytest.mark.parametrize("dtype_name", ["float32", "float16"])
-@pytest.mark.parametrize("M,N", [(2, 2), (7, 31), (8, 32), (14, 62), (21, 18), (40, 95)])
+@pytest.mark.parametrize("M,N", [(2, 2), (7, 31), (8, 32), (14, 62), (21, 18), (40, 95), (150, 421)])
 def test_bilateral_sweeps_in_place(pl, M, N, dtype_name):
     # sweeps fused in place (one buffer) or between two, against one sweep per
     # launch: the same bits, with missing triangles and, from the scaled
