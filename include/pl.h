@@ -108,7 +108,7 @@ pl_status pl_mesh_opc(const float *pts, int32_t M, int32_t N,
  * pl_mesh_opc without a workspace, for callers that cannot allocate device
  * memory: code being captured into a HIP graph, tight serving loops, and
  * harnesses that forbid allocation.  Arguments, outputs and errors are those
- * of pl_mesh_opc, whose outputs it reproduces bit for bit; the validity codes
+ * of pl_mesh_opc, whose outputs it reproduces bit for bit; the validity masks
  * and segment counts that pl_mesh_opc keeps in the workspace live instead in
  * a static device array of 8 MiB (one per GPU, held until the process ends,
  * its address looked up on the first call on that GPU).
@@ -495,10 +495,10 @@ pl_status pl_batch_replay_bounded(pl_batch batch, int32_t n_active, hipStream_t 
  * unfiltered normals are not stored.  The mesh's validity pass runs in the
  * same launch as the Laplacian's first pass, the mesh emit in the launch
  * after it (whose gather, if it is the last bilateral pass, ranks the
- * triangles in T from the validity codes instead of reading T_map), and the
+ * triangles in T from the validity masks instead of reading T_map), and the
  * first bilateral pass computes the normals and centroids itself: one
- * launch per filter pass (a 480 x 640 frame with the committed tuning: 3
- * launches instead of 6; a 120 x 160 frame: 2).
+ * launch per filter pass (with the committed tuning a frame of four 3x3
+ * Laplacian sweeps and two bilateral ones: 2 launches instead of 5).
  *
  * frame      HOST pointer to one pl_frame (the layout is documented with the
  *            batched path below); its buffers are device memory owned by
@@ -536,7 +536,7 @@ enum {
     PL_LAUNCH_BILATERAL = 2,     /* bilateral sweeps over quad tiles        */
     PL_LAUNCH_NORMALS = 4,       /* centroids and normals from the points  */
     PL_LAUNCH_GATHER = 8,        /* filtered normals gathered onto T       */
-    PL_LAUNCH_MESH_COUNT = 16,   /* validity codes and counts (a1)         */
+    PL_LAUNCH_MESH_COUNT = 16,   /* validity masks and counts (a1)         */
     PL_LAUNCH_MESH_EMIT = 32,    /* T_map, T, HE (a2, a3)                  */
     PL_LAUNCH_GROUPS = 64        /* group assignment (Alg. 4)              */
 };

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kTileBlock) void k_frame_laplacian(
 
 // FromPts: the first pass (raw normals and centroids from the smoothed points).
 // ByCodes: the gathering pass beside the emit, ranking triangles from the
-// mesh codes (GatherCodes) instead of reading T_map.
+// mesh masks (GatherCodes) instead of reading T_map.
 template <int R, typename NT, bool FromPts, int Kind, bool ByCodes = false>
 __global__ __launch_bounds__(kTileBlock, bil_waves_per_simd(R, false)) void k_frame_bilateral(
     const NT *__restrict__ nin, const float *__restrict__ cen, NT *__restrict__ nout, int Mq,

@@ -468,7 +468,8 @@ __device__ void he_bucket_global(const HeEntry *__restrict__ r, int m,
 }
 
 // One workgroup per bucket (two per CU, by the LDS of their tables).  Bound by
-// latency and by the twins' scattered 4-byte writes.  A thread holds its entries of the region in
+// the twins' scattered 4-byte writes (22.6 us for 1.6 M half-edges in random
+// order, 9.4 without them; four workgroups per CU change nothing).  A thread holds its entries of the region in
 // registers, loaded at once, and the slots they found: the twins then need
 // neither a second read of the entries nor a second probe.
 // ctl: [0] overflow entries, [1] slots taken of the global table `tab`, whose

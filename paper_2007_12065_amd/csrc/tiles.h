@@ -665,7 +665,7 @@ __host__ __device__ constexpr size_t bil_lds_bytes(int R, int F, int TQH, int TQ
     const size_t S = (size_t)(TQH + 2 * R * F) * (size_t)(TQW + 2 * R * F);
     return (F > 1 && !bil_in_place(R, F, TQH, TQW) ? 6 : 3) * sizeof(float4) * S +
            sizeof(int) * (kBilMaxSweeps + 1) + sizeof(uint16_t) * 2 * S +
-           sizeof(int) * (size_t)TQH * TQW +    // T ranks of the tile (gather from the mesh codes)
+           sizeof(int) * (size_t)TQH * TQW +    // T ranks of the tile (gather from the mesh masks)
            (waves ? sizeof(float) * (size_t)bil_xch_floats(R) : 0) + S;
 }
 
@@ -1175,7 +1175,7 @@ __device__ __forceinline__ void bil_tile(const NT *__restrict__ nin, const float
     float4 *st2 = lds + 3 * S;          // [3][S] the next sweep's (F > 1, not in place)
     int *counts = reinterpret_cast<int *>(lds + (F > 1 && !in_place ? 6 : 3) * S);
     if (threadIdx.x < kBilMaxSweeps + 1) counts[threadIdx.x] = 0;
-    // T ranks of the tile when the gather takes them from the mesh codes
+    // T ranks of the tile when the gather takes them from the mesh masks
     int *rank = counts + kBilMaxSweeps + 1;
     // the parts' exchange (parts on waves)
     float *xch = reinterpret_cast<float *>(rank + TQH * TQW);

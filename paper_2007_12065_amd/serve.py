@@ -79,7 +79,7 @@ def slot_bytes(c: FrameClass, normal_bytes: int = 2, lap_fuse: int = 4, bil_fuse
     total += a(3 * T * normal_bytes) * 2      # filtered normals, normals of T
     total += a(12 * T)                        # centroids
     total += a(T) + a(4 * T) + a(12 * T) + a(12 * T) + a(4)   # tri_valid, T_map, T, HE, n_tri
-    total += a(Q) + a(4 * (c.M - 1))          # validity codes, row counts
+    total += a(Q) + a(4 * (c.M - 1))          # mesh scratch (masks, counts)
     total += a(12 * P) if lap_passes > 1 else 0
     total += a(3 * T * normal_bytes) * (2 if bil_passes > 1 else 1)
     return total
