@@ -161,6 +161,11 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device) -> int:
+    if type(device) is not torch.device:
+        device = torch.device("cuda" if device is None else device)
+    if device.type != "cuda":
+        # a plan or accumulator on another device: its buffers are not the GPU's
+        raise ValueError(f"expected a CUDA (HIP) device, got {device}")
     if _raw_stream is None:
         return torch.cuda.current_stream(device).cuda_stream
     i = device.index

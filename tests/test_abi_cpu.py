@@ -258,3 +258,22 @@ def test_tuning_table_stages(pl):
     finally:
         for (s, k), v in saved.items():
             pl.pl_tune_set(s, k, *v)
+
+
+@pytest.mark.parametrize("call", ["run", "run_fused", "run_groups", "accumulator", "device", "name"])
+def test_plans_on_another_device_are_refused(pl, call):
+    """A plan whose buffers are host memory never passes them to the library."""
+    import torch
+    plan = pl.FramePlan(8, 9, 3, 1.0, 1, 3, 0.1, 0.1, 1, device="cpu")
+    pts = torch.zeros((8, 9, 3))
+    with pytest.raises(ValueError, match="device"):
+        if call == "run":
+            plan.run(pts)
+        elif call == "run_fused":
+            plan.run_fused(pts)
+        elif call == "run_groups":
+            plan.run_groups(torch.zeros((1, 3)), 0.05, 0.96)
+        elif call == "accumulator":
+            pl.GaussianAccumulator(1, device="cpu")
+        else:
+            pl._stream(torch.device("cpu") if call == "device" else "cpu")
