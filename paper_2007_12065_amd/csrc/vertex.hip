@@ -15,12 +15,20 @@
 // Up to kVuMaxSweeps sweeps run in one launch: a workgroup takes a region of 32
 // x 32 points, of which the inner 32 - 2 F squared are still exact after F
 // sweeps.  A thread owns two points of it, one above the other, for all
-// sweeps: their ten triangles' normals, which of them count (validity and the
-// normals are fixed) and the points themselves stay in its registers, and a
-// sweep reads the eight neighbouring points from LDS and writes its two.  Every
-// read of LDS saved counts: with normals and flags in LDS as well, a point read
-// 13 vectors and 4 bytes a sweep, and five sweeps of a 480 x 640 frame took
-// 19.2 us, now 11.9 us (28.2 us as five launches of a thread per point).
+// sweeps: their ten triangles' normals, which of them count and the points
+// themselves stay in its registers, and a sweep reads the eight neighbouring
+// points from LDS and writes its two.  Every read of LDS saved counts: with
+// normals and flags in LDS as well, a point read 13 vectors and 4 bytes a
+// sweep, and five sweeps of a 480 x 640 frame took 19.2 us, now 11.9 us (28.2
+// us as five launches of a thread per point).
+//
+// Which triangles count is a matter of the sweep: a point that turns NaN in one
+// (beside an infinite coordinate, or when one overflows) is a missing one from
+// the next on.  A triangle that counted at the launch's start and has lost a
+// corner makes each component of its sum NaN, so a thread that sees a NaN in
+// its result, and no other, sums again with the corners looked at.  For the
+// rest that is one comparison and a branch a sweep: 0.06 us of the 0.6 us one
+// takes on a frame too small to fill the CUs, nothing measurable from 480 x 640.
 #include "vu.h"
 
 namespace pl {
@@ -30,6 +38,9 @@ namespace {
 constexpr int kVuDim = 32;                    // points of a region, each way
 constexpr int kVuBlock = kVuDim * kVuDim / 2;
 constexpr int kVuMaxSweeps = 8;
+// Register budget (80 VGPRs), for three workgroups per CU: with the rare second
+// sum in registers beside the first (95) 1200 x 1944 points took 26.6 us a sweep.
+constexpr int kVuWavesPerSimd = 6;
 
 struct P3 {
     float x, y, z;
@@ -64,11 +75,37 @@ __device__ __forceinline__ P3 vu_move(P3 x, P3 s, int count) {
     return P3{fmaf(s.x, inv, x.x), fmaf(s.y, inv, x.y), fmaf(s.z, inv, x.z)};
 }
 
+// The point at `at` after a sweep, by triangles whose corners are valid now: of
+// its six (normals and whether they counted at the launch's start: quad (r, c)'s
+// two, the one of (r, c-1), (r-1, c-1)'s two, the one of (r-1, c)).  Points
+// missing from the start are zero in LDS, and their triangles never counted.
+__device__ __forceinline__ P3 vu_recheck(const P3 *buf, int at, P3 n0, bool k0, P3 n1, bool k1, P3 n2, bool k2,
+                                         P3 n3, bool k3, P3 n4, bool k4, P3 n5, bool k5) {
+    // an address the compiler cannot see through: kept from the first sum, the
+    // points would not leave registers for it
+    asm volatile("" : "+v"(at));
+    const P3 *A = buf + at;
+    const P3 x = A[0], a0 = A[-kVuDim - 1], a1 = A[-kVuDim], b0 = A[-1], b2 = A[1], c1 = A[kVuDim], c2 = A[kVuDim + 1];
+    P3 s{0.f, 0.f, 0.f};
+    int count = 0;
+    auto add = [&](P3 t, P3 n, bool k, P3 p, P3 q) {
+        k = (int)k & (int)p_ok(x) & (int)p_ok(p) & (int)p_ok(q);      // no branches
+        vu_add(x, t, k ? n : P3{0.f, 0.f, 0.f}, k, s);
+        count += (int)k;
+    };
+    add(vu_sum(c2, b2, x), n0, k0, c2, b2);
+    add(vu_sum(x, c1, c2), n1, k1, c1, c2);
+    add(vu_sum(c1, x, b0), n2, k2, c1, b0);
+    add(vu_sum(x, a1, a0), n3, k3, a1, a0);
+    add(vu_sum(a0, b0, x), n4, k4, a0, b0);
+    add(vu_sum(a1, x, b2), n5, k5, a1, b2);
+    return vu_move(x, s, count);
+}
+
 template <typename NT>
-__global__ __launch_bounds__(kVuBlock) void k_vertex_update(const float *__restrict__ in,
-                                                            float *__restrict__ out, int M, int N,
-                                                            const NT *__restrict__ normals, int F,
-                                                            int tiles_x, int ntiles) {
+__global__ __launch_bounds__(kVuBlock, kVuWavesPerSimd) void k_vertex_update(
+    const float *__restrict__ in, float *__restrict__ out, int M, int N,
+    const NT *__restrict__ normals, int F, int tiles_x, int ntiles) {
     // a row and a point of slack on either side: the region's outer points
     // read past it (what they come to is not used)
     constexpr int kPad = kVuDim + 1, kSize = kVuDim * kVuDim + 2 * kPad;
@@ -113,6 +150,7 @@ __global__ __launch_bounds__(kVuBlock) void k_vertex_update(const float *__restr
     buf[0][at + kVuDim] = x1;
     ok[at] = v0;
     ok[at + kVuDim] = v1;
+    if (threadIdx.x < kPad) ok[threadIdx.x] = ok[kSize - 1 - threadIdx.x] = 0;   // the slack: no triangle
     __syncthreads();
     // which triangles count: corners valid, normal without a NaN.  Rows a, b,
     // c, d are r - 1 .. r + 2; b and c hold this thread's points.
@@ -154,6 +192,11 @@ __global__ __launch_bounds__(kVuBlock) void k_vertex_update(const float *__restr
         vu_add(x1, t31, n31, k31, s1);
         x0 = vu_move(x0, s0, count0);
         x1 = vu_move(x1, s1, count1);
+        if (__builtin_expect(__ballot(__builtin_isunordered(x0.x, x1.x)) != 0, 0)) {
+            x0 = vu_recheck(buf[(f - 1) & 1], at, n30, k30, n31, k31, n20, k20, n00, k00, n01, k01, n11, k11);
+            x1 = vu_recheck(buf[(f - 1) & 1], at + kVuDim, n40, k40, n41, k41, n50, k50, n20, k20, n21, k21,
+                            n31, k31);
+        }
         if (f < F) {
             P3 *B = buf[f & 1] + at;
             B[0] = x0;

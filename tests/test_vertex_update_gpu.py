@@ -80,3 +80,33 @@ def test_sweeps_over_launches(pl, orc, M, N):
     for iters in (1, 3, 4, 5, 6, 8, 11, 17):
         say("vertex update", M, N, "iters", iters)
         check(pl, g, n.astype(np.float32), iters)
+
+
+@pytest.mark.parametrize("M,N", [(16, 33), (40, 50), (31, 65), (64, 257), (300, 3)])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_points_lost_during_the_sweeps(pl, orc, M, N, dtype):
+    """A point that turns NaN in a sweep (infinite coordinates beside it) is a
+    missing one from the next sweep on, however the sweeps share launches:
+    the oracle's missing and infinite coordinates, finite ones within the
+    bound."""
+    import torch
+    rng = np.random.default_rng(M * N)
+    g = synth.random_grid(M, N, 3 * M + N, nan_frac=0.05, noise=0.02).astype(np.float32)
+    n, _ = orc.tri_normals(g.astype(np.float64))
+    n = n.astype(dtype)
+    n[M // 2:, :, :, 0] = np.where(np.isnan(n[M // 2:, :, :, 0]), n[M // 2:, :, :, 0], 0)   # planes along x
+    at = rng.choice(M * N, max(2, M * N // 200), replace=False)
+    g.reshape(-1, 3)[at, rng.integers(0, 3, len(at))] = rng.choice([np.inf, -np.inf], len(at))
+    for iters in (1, 2, 3, 4, 5, 7, 8, 11, 17):
+        say("vertex update with infinities", M, N, dtype.__name__, "iters", iters)
+        got = pl.pl_vertex_update(to_dev(g), to_dev(n), iters)
+        torch.cuda.synchronize()
+        got = got.cpu().numpy()
+        with np.errstate(all="ignore"):
+            want = oracle.vertex_update(g.astype(np.float64), n.astype(np.float64), iters)
+        assert np.array_equal(np.isnan(got), np.isnan(want)), np.count_nonzero(np.isnan(got) != np.isnan(want))
+        inf = np.isinf(want)
+        assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+        fin = np.isfinite(want).all(-1)
+        rel = np.linalg.norm(got[fin] - want[fin], axis=-1) / np.linalg.norm(want[fin], axis=-1)
+        assert rel.max() <= VERTEX_RTOL, rel.max()
