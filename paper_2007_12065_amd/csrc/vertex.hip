@@ -29,6 +29,9 @@
 // its result, and no other, sums again with the corners looked at.  For the
 // rest that is one comparison and a branch a sweep: 0.06 us of the 0.6 us one
 // takes on a frame too small to fill the CUs, nothing measurable from 480 x 640.
+//
+// Frames whose regions would be mostly halo, and small frames' single sweeps,
+// take a launch of a thread per point for each sweep (k_vertex_sweep).
 #include "vu.h"
 
 namespace pl {
@@ -217,6 +220,54 @@ __global__ __launch_bounds__(kVuBlock, kVuWavesPerSimd) void k_vertex_update(
     store(ty + 1, r + 1, x1, v1);
 }
 
+// One sweep, a thread per point, row-major over the frame: where a launch of
+// fused sweeps has nothing to win (vu_by_points).  The 3 x 3 points around one
+// and its normals come from cache.  Same bits: the same sums in the same order.
+constexpr int kVuPointBlock = 256;
+
+template <typename NT>
+__global__ __launch_bounds__(kVuPointBlock) void k_vertex_sweep(const float *__restrict__ in,
+                                                                float *__restrict__ out, int M, int N,
+                                                                const NT *__restrict__ normals) {
+    const long long idx =
+        (long long)xcd_remap((int)blockIdx.x, (int)gridDim.x) * kVuPointBlock + threadIdx.x;
+    if (idx >= (long long)M * N) return;
+    const int r = (int)(idx / N), c = (int)(idx - (long long)r * N), Nq = N - 1;
+    auto point = [&](int row, int col) {
+        P3 p{qnan(), 0.f, 0.f};
+        if ((unsigned)row < (unsigned)M && (unsigned)col < (unsigned)N) {
+            const float *q = in + 3 * ((size_t)row * N + col);
+            p = P3{q[0], q[1], q[2]};
+        }
+        return p;
+    };
+    const P3 x = point(r, c), a0 = point(r - 1, c - 1), a1 = point(r - 1, c), b0 = point(r, c - 1),
+             b2 = point(r, c + 1), c1 = point(r + 1, c), c2 = point(r + 1, c + 1);
+    P3 s{0.f, 0.f, 0.f};
+    int count = 0;
+    // triangle k of quad (u, v), p and q its corners beside x (all three on the
+    // grid, so the quad is)
+    auto add = [&](int u, int v, int k, P3 t, P3 p, P3 q) {
+        if (!(p_ok(x) && p_ok(p) && p_ok(q))) return;
+        const NT *m = normals + 3 * (2 * ((size_t)u * Nq + v) + k);
+        const P3 n{ld_f(m), ld_f(m + 1), ld_f(m + 2)};
+        if (!p_ok(n)) return;
+        vu_add(x, t, n, true, s);
+        ++count;
+    };
+    add(r, c, 0, vu_sum(c2, b2, x), c2, b2);               // quad (r, c): p1
+    add(r, c, 1, vu_sum(x, c1, c2), c1, c2);
+    add(r, c - 1, 0, vu_sum(c1, x, b0), c1, b0);           // quad (r, c-1): p2
+    add(r - 1, c - 1, 0, vu_sum(x, a1, a0), a1, a0);       // quad (r-1, c-1): p3
+    add(r - 1, c - 1, 1, vu_sum(a0, b0, x), a0, b0);
+    add(r - 1, c, 1, vu_sum(a1, x, b2), a1, b2);           // quad (r-1, c): p4
+    const P3 y = vu_move(x, s, count);
+    float *o = out + 3 * idx;
+    st_stream(&o[0], y.x);
+    st_stream(&o[1], y.y);
+    st_stream(&o[2], y.z);
+}
+
 }  // namespace
 
 namespace {
@@ -245,6 +296,25 @@ int vu_launches(int iterations, double P) {
     return best;
 }
 
+// Whether a launch per sweep, a thread per point, is the faster way: a single
+// sweep of a small frame, and frames so narrow that the regions' halo is most
+// of the work.  In microseconds, a launch of F fused sweeps over t regions takes
+// about 4.5 + 0.55 F + t (2.7 + 1.45 F) / 1000 where its points come from
+// cache, and a sweep over P points 3.3 + 6.2 P / 10^6.  By points against
+// regions: one sweep of 40 x 50 4.6, 5.2; 120 x 160 4.8, 5.4; 480 x 640 6.0, 6.6
+// (720 x 1280: 12.8, 11.5); 70000 x 3 5.3, 15.2, and twenty 86, 162; 20000 x 16
+// one 5.8, 7.3, and six as fused 18.2 (by points about 30).
+bool vu_by_points(int M, int N, int iterations, int launches) {
+    double fused = 0.0;
+    for (int l = 0, left = iterations; l < launches; ++l) {
+        const int F = (left + launches - l - 1) / (launches - l), inner = kVuDim - 2 * F;
+        left -= F;
+        fused += 4.5 + 0.55 * F +
+                 (double)((M + inner - 1) / inner) * ((N + inner - 1) / inner) * (2.7 + 1.45 * F) * 1e-3;
+    }
+    return 1.0 + iterations * (3.3 + 6.2e-6 * M * N) < fused;
+}
+
 }  // namespace
 
 size_t vertex_update_workspace(int M, int N, int iterations) {
@@ -256,23 +326,31 @@ pl_status launch_vertex_update(const float *in, float *out, int M, int N, const 
     const size_t bytes = 12 * (size_t)M * N;
     if (iterations == 0)
         return hip_check(hipMemcpyAsync(out, in, bytes, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync");
-    const int launches = vu_launches(iterations, (double)M * N);
+    int launches = vu_launches(iterations, (double)M * N);
+    const bool by_points = vu_by_points(M, N, iterations, launches);
+    if (by_points) launches = iterations;
     const float *src = in;
     int left = iterations;
+    auto launch = [&](float *dst, int F, const auto *n) {
+        if (by_points) {
+            const unsigned grid = (unsigned)(((size_t)M * N + kVuPointBlock - 1) / kVuPointBlock);
+            k_vertex_sweep<<<grid, kVuPointBlock, 0, s>>>(src, dst, M, N, n);
+            return;
+        }
+        const int inner = kVuDim - 2 * F;
+        const int tiles_x = (N + inner - 1) / inner;
+        const int ntiles = tiles_x * ((M + inner - 1) / inner);
+        k_vertex_update<<<ntiles, kVuBlock, 0, s>>>(src, dst, M, N, n, F, tiles_x, ntiles);
+    };
     for (int l = 0; l < launches; ++l) {
         const int F = (left + launches - l - 1) / (launches - l);
         left -= F;
         // the last launch lands in `out`; earlier ones alternate with the workspace
         float *dst = ((launches - 1 - l) % 2 == 0) ? out : static_cast<float *>(ws);
-        const int inner = kVuDim - 2 * F;
-        const int tiles_x = (N + inner - 1) / inner;
-        const int ntiles = tiles_x * ((M + inner - 1) / inner);
         if (ndt == PL_F32)
-            k_vertex_update<float><<<ntiles, kVuBlock, 0, s>>>(
-                src, dst, M, N, static_cast<const float *>(normals), F, tiles_x, ntiles);
+            launch(dst, F, static_cast<const float *>(normals));
         else
-            k_vertex_update<__half><<<ntiles, kVuBlock, 0, s>>>(
-                src, dst, M, N, static_cast<const __half *>(normals), F, tiles_x, ntiles);
+            launch(dst, F, static_cast<const __half *>(normals));
         if (pl_status st = hip_check(hipGetLastError(), "k_vertex_update")) return st;
         src = dst;
     }

@@ -110,3 +110,15 @@ def test_points_lost_during_the_sweeps(pl, orc, M, N, dtype):
         fin = np.isfinite(want).all(-1)
         rel = np.linalg.norm(got[fin] - want[fin], axis=-1) / np.linalg.norm(want[fin], axis=-1)
         assert rel.max() <= VERTEX_RTOL, rel.max()
+
+
+@pytest.mark.parametrize("M,N", [(5000, 2), (3, 5000), (8000, 5), (6000, 16), (40, 50)])
+def test_narrow_frames(pl, orc, M, N):
+    """Frames narrower than a region, and single sweeps of small ones: around
+    where a thread per point takes over from the regions."""
+    g = synth.random_grid(M, N, M + N, nan_frac=0.1, noise=0.02)
+    n, _ = orc.tri_normals(g)
+    for iters in (1, 2, 3, 7):
+        say("vertex update narrow", M, N, "iters", iters)
+        check(pl, g, n.astype(np.float32), iters)
+        check(pl, g, n.astype(np.float16), iters)
