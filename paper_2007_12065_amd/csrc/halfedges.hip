@@ -33,6 +33,9 @@
 //                  keys than its LDS table has slots (only inputs built
 //                  against the hash hold one) is solved by its workgroup in
 //                  a table of its own in global memory
+// A chunk past the mesh (a buffer may hold more triangles than |T|) is left by
+// its workgroup at once: one triangle in a buffer of 5.5 M takes 145 us (370
+// when its chunks were read and scanned, 147 before loads were kept in flight).
 // All of a thread's loads of a pass are issued before the first is used (eight
 // dependent rounds of memory latency were most of a pass before).  On 533 k
 // triangles in a buffer for 612 k, count / offsets / scatter / solve take
@@ -214,13 +217,16 @@ __device__ __forceinline__ int he_bucket(unsigned long long mix, int lg) {
     return lg == 0 ? 0 : (int)(mix >> (64 - lg));
 }
 
+// The half-edges of the mesh.
+__device__ __forceinline__ int he_number(const int32_t *__restrict__ n_tri, int cap) {
+    return 3 * min(max(*n_tri, 0), cap);
+}
+
 // A thread's half-edges base + i kHePartBlock + threadIdx.x of its chunk, all
-// loads in flight at once: rows at or past n (known only when the device-side
-// count has arrived, but inside the capacity) are left out by a == b.
-__device__ __forceinline__ void he_chunk_ends(const int32_t *__restrict__ tris,
-                                              const int32_t *__restrict__ n_tri, int cap, int base,
-                                              int (&a)[kHePer], int (&b)[kHePer], int &n) {
-    const int cnt = *n_tri;
+// loads in flight at once.  Rows from n on hold whatever the buffer does, or
+// (0, 0) past the capacity: the caller leaves them out by their index.
+__device__ __forceinline__ void he_chunk_ends(const int32_t *__restrict__ tris, int cap, int base,
+                                              int (&a)[kHePer], int (&b)[kHePer]) {
 #pragma unroll
     for (int i = 0; i < kHePer; ++i) {
         const int h = base + i * kHePartBlock + (int)threadIdx.x;
@@ -228,7 +234,6 @@ __device__ __forceinline__ void he_chunk_ends(const int32_t *__restrict__ tris,
         b[i] = 0;
         if (h < 3 * cap) he_ends(tris, h, a[i], b[i]);
     }
-    n = 3 * min(max(cnt, 0), cap);
 }
 
 __global__ __launch_bounds__(kHePartBlock) void k_he_count(const int32_t *__restrict__ tris,
@@ -237,9 +242,14 @@ __global__ __launch_bounds__(kHePartBlock) void k_he_count(const int32_t *__rest
                                                            int32_t *__restrict__ hist_out) {
     extern __shared__ int hist[];
     const int nb = 1 << lg;
-    const int base = (int)blockIdx.x * kHeChunk;
-    int a[kHePer], b[kHePer], n;
-    he_chunk_ends(tris, n_tri, cap, base, a, b, n);
+    const int base = (int)blockIdx.x * kHeChunk, n = he_number(n_tri, cap);
+    int32_t *row = hist_out + (size_t)blockIdx.x * nb;
+    if (base >= n) {                     // a chunk past the mesh: no counts
+        for (int i = threadIdx.x; i < nb; i += kHePartBlock) row[i] = 0;
+        return;
+    }
+    int a[kHePer], b[kHePer];
+    he_chunk_ends(tris, cap, base, a, b);
     for (int i = threadIdx.x; i < nb; i += kHePartBlock) hist[i] = 0;
     __syncthreads();
 #pragma unroll
@@ -249,7 +259,6 @@ __global__ __launch_bounds__(kHePartBlock) void k_he_count(const int32_t *__rest
             atomicAdd(&hist[he_bucket(he_mix(he_key(min(a[i], b[i]), max(a[i], b[i]))), lg)], 1);
     }
     __syncthreads();
-    int32_t *row = hist_out + (size_t)blockIdx.x * nb;
     for (int i = threadIdx.x; i < nb; i += kHePartBlock) row[i] = hist[i];
 }
 
@@ -334,11 +343,12 @@ __global__ __launch_bounds__(kHePartBlock) void k_he_scatter(
     int *shd = reinterpret_cast<int *>(skey + kHeChunk);                 // [kHeChunk]
     int *lcur = shd + kHeChunk;                                          // [nb]
     int *ldelta = lcur + nb;                                             // [nb]
-    const int base = (int)blockIdx.x * kHeChunk;
+    const int base = (int)blockIdx.x * kHeChunk, n = he_number(n_tri, cap);
+    if (base >= n) return;               // a chunk past the mesh
     const int32_t *crow = hist + (size_t)blockIdx.x * nb;
     const int32_t *srow = start + (size_t)blockIdx.x * nb;
-    int a[kHePer], b[kHePer], n;
-    he_chunk_ends(tris, n_tri, cap, base, a, b, n);
+    int a[kHePer], b[kHePer];
+    he_chunk_ends(tris, cap, base, a, b);
     // the chunk's starts per bucket: each thread scans `per` consecutive
     // counts (nb < kHePartBlock: one or none)
     const int per = (nb + kHePartBlock - 1) / kHePartBlock;
