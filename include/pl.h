@@ -288,8 +288,8 @@ pl_status pl_vertex_update(const float *pts_in, float *pts_out, int32_t M, int32
  * power of two at or above 3 cap / 2048) and each bucket is solved in one
  * workgroup's LDS: the workspace holds per-chunk bucket counts and starts,
  * bucket regions of 3072 entries of 12 bytes, an overflow list of 3 cap
- * entries and 4 cap slots of 16 bytes for buckets that outgrow LDS (about
- * 165 bytes per triangle at cap = 612k); four launches.
+ * half-edges of 4 bytes and 4 cap slots of 4 bytes for buckets that outgrow
+ * LDS (about 96 bytes per triangle at cap = 612k); four launches.
  * Larger capacities use one hash table of 4 cap slots of 16 bytes and a
  * slot index per half-edge; three launches.  PL_ERR_ARG / PL_ERR_SHAPE /
  * PL_ERR_WORKSPACE / PL_ERR_ALIAS on invalid arguments (nothing enqueued).

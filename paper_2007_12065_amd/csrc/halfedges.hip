@@ -24,7 +24,7 @@
 //   k_he_scatter   every half-edge's key and index into its bucket's region
 //                  (kHeRegion entries), staged in LDS in bucket order first
 //                  so that each chunk writes one contiguous run per bucket;
-//                  entries past a full region go to an overflow list, which
+//                  half-edges past a full region go to an overflow list, which
 //                  only the buckets that overflowed read
 //   k_he_solve     one workgroup per bucket: an LDS hash table of the
 //                  bucket's keys (compare-and-swap on the key, atomic min of
@@ -334,7 +334,7 @@ __device__ __forceinline__ int block_exclusive_scan(int x, int *tmp, int *all) {
 __global__ __launch_bounds__(kHePartBlock) void k_he_scatter(
     const int32_t *__restrict__ tris, const int32_t *__restrict__ n_tri, int cap, int lg,
     const int32_t *__restrict__ hist, const int32_t *__restrict__ start,
-    HeEntry *__restrict__ region, int32_t *__restrict__ ctl, HeEntry *__restrict__ over,
+    HeEntry *__restrict__ region, int32_t *__restrict__ ctl, int32_t *__restrict__ over,
     int32_t *__restrict__ he) {
     extern __shared__ unsigned long long lds_u64[];
     __shared__ int tmp[kHePartBlock / kWave];
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kHePartBlock) void k_he_scatter(
         if (pos < kHeRegion)
             region[(size_t)bk * kHeRegion + pos] = e;
         else
-            over[atomicAdd(&ctl[0], 1)] = e;
+            over[atomicAdd(&ctl[0], 1)] = e.hd & INT_MAX;
     }
 }
 
@@ -430,50 +430,60 @@ __device__ __forceinline__ int he_twin(int2 f, int hd) {
 }
 
 // A bucket with more distinct keys than the LDS table has slots, by its
-// workgroup alone: its entries (the first m of its region, then its own of
-// the overflow list's no) through `slots` > their number slots of a table in
-// global memory, all through atomics (which meet in L2).
-__device__ void he_bucket_global(const HeEntry *__restrict__ r, int m,
-                                 const HeEntry *__restrict__ over, int no, int bk, int lg, HeSlot *tab, unsigned long long slots, int32_t *__restrict__ he) {
-    for (size_t i = threadIdx.x; i < slots; i += kHePartBlock) {
-        __hip_atomic_store(&tab[i].key, kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&tab[i].fwd, INT_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&tab[i].bwd, INT_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+// workgroup alone: its half-edges (the first m in its region, then its own of
+// the overflow list's no) through a hash table of directed edges in global
+// memory.  A slot is the first half-edge of its edge so far (-1: empty), whose
+// points T holds: 4 bytes, of `slots` more than there are half-edges.  All
+// accesses are atomic (they meet in L2).
+__device__ void he_bucket_global(const int32_t *__restrict__ tris, const HeEntry *__restrict__ r, int m,
+                                 const int32_t *__restrict__ over, int no, int bk, int lg, int *tab,
+                                 int slots, int32_t *__restrict__ he) {
+    for (int i = threadIdx.x; i < slots; i += kHePartBlock)
+        __hip_atomic_store(&tab[i], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
+    // the i-th half-edge, from a to b; false for another bucket's
+    auto take = [&](int i, int &h, int &a, int &b) {
+        h = i < m ? r[i].hd & INT_MAX : over[i - m];
+        he_ends(tris, h, a, b);
+        return i < m || he_bucket(he_mix(he_key(min(a, b), max(a, b))), lg) == bk;
+    };
+    // the slot of a -> b, or the empty one where it belongs: the bucket's keys
+    // share the mix's top bits, so the rest spreads them, either direction over
+    // a half of its own; `v`: what it held
+    auto find = [&](int a, int b, int &v) {
+        unsigned long long x = he_mix(he_key(min(a, b), max(a, b))) << lg;
+        if (a > b) x ^= 1ull << 63;
+        int slot = (int)__umul64hi(x, (unsigned long long)slots);
+        for (int p = 0; p < slots; ++p) {                     // a free slot is always left
+            v = __hip_atomic_load(&tab[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v < 0) return slot;
+            int c, d;
+            he_ends(tris, v, c, d);
+            if (c == a && d == b) return slot;
+            slot = slot + 1 == slots ? 0 : slot + 1;
+        }
+        return -1;
+    };
     for (int i = threadIdx.x; i < m + no; i += kHePartBlock) {
-        const HeEntry e = i < m ? r[i] : over[i - m];
-        const unsigned long long key = he_key(e.lo, e.hi), mix = he_mix(key);
-        if (i >= m && he_bucket(mix, lg) != bk) continue;
-        const int hd = e.hd;
-        // the bucket's keys share the mix's top bits: the rest spreads them
-        unsigned long long slot = __umul64hi(mix << lg, slots);
-        for (unsigned long long p = 0; p < slots; ++p) {     // a free slot is always left
-            const unsigned long long prev = atomicCAS(&tab[slot].key, kEmpty, key);
-            if (prev == kEmpty || prev == key) {
-                atomicMin(hd < 0 ? &tab[slot].bwd : &tab[slot].fwd, hd & INT_MAX);
+        int h, a, b;
+        if (!take(i, h, a, b)) continue;
+        for (;;) {
+            int v;
+            const int slot = find(a, b, v);
+            if (slot < 0) break;
+            if (v >= 0) {
+                atomicMin(&tab[slot], h);
                 break;
             }
-            slot = slot + 1 == slots ? 0 : slot + 1;
+            if (atomicCAS(&tab[slot], -1, h) == -1) break;    // else another took it: look again
         }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < m + no; i += kHePartBlock) {
-        const HeEntry e = i < m ? r[i] : over[i - m];
-        const unsigned long long key = he_key(e.lo, e.hi), mix = he_mix(key);
-        if (i >= m && he_bucket(mix, lg) != bk) continue;
-        const int hd = e.hd;
-        unsigned long long slot = __umul64hi(mix << lg, slots);
-        for (unsigned long long p = 0; p < slots; ++p) {     // found at once or soon
-            if (__hip_atomic_load(&tab[slot].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == key) {
-                int2 f;
-                f.x = __hip_atomic_load(&tab[slot].fwd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                f.y = __hip_atomic_load(&tab[slot].bwd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                he[hd & INT_MAX] = he_twin(f, hd);
-                break;
-            }
-            slot = slot + 1 == slots ? 0 : slot + 1;
-        }
+        int h, a, b, own, other;
+        if (!take(i, h, a, b)) continue;
+        const bool in = find(a, b, own) >= 0 && own == h;
+        he[h] = in && find(b, a, other) >= 0 ? other : -1;
     }
 }
 
@@ -482,12 +492,13 @@ __device__ void he_bucket_global(const HeEntry *__restrict__ r, int m,
 // order, 9.4 without them; four workgroups per CU change nothing).  A thread holds its entries of the region in
 // registers, loaded at once, and the slots they found: the twins then need
 // neither a second read of the entries nor a second probe.
-// ctl: [0] overflow entries, [1] slots taken of the global table `tab`, whose
-// 4 cap slots suffice: a bucket takes 4/3 of its entries, and all buckets
-// together hold at most 3 cap.
+// ctl: [0] half-edges on the overflow list, [1] slots taken of the global table
+// `tab`, whose 4 cap slots suffice: a bucket takes 4/3 of its half-edges, and all
+// buckets together hold at most 3 cap.
 __global__ __launch_bounds__(kHePartBlock) void k_he_solve(
-    const HeEntry *__restrict__ region, const int32_t *__restrict__ total, int32_t *ctl,
-    const HeEntry *__restrict__ over, int lg, HeSlot *tab, int32_t *__restrict__ he) {
+    const int32_t *__restrict__ tris, const HeEntry *__restrict__ region,
+    const int32_t *__restrict__ total, int32_t *ctl, const int32_t *__restrict__ over, int lg, int *tab,
+    int32_t *__restrict__ he) {
     __shared__ HeLdsTable t;
     __shared__ int full, tab_base;
     const int bk = (int)blockIdx.x;
@@ -517,33 +528,37 @@ __global__ __launch_bounds__(kHePartBlock) void k_he_solve(
         }
     }
     for (int i = threadIdx.x; i < no; i += kHePartBlock) {
-        const HeEntry o = over[i];
-        const unsigned long long k = he_key(o.lo, o.hi);
-        if (he_bucket(he_mix(k), lg) == bk && he_lds_insert(t, k, o.hd) < 0) full = 1;
+        const int h = over[i];
+        int a, b;
+        he_ends(tris, h, a, b);
+        const unsigned long long k = he_key(min(a, b), max(a, b));
+        if (he_bucket(he_mix(k), lg) == bk && he_lds_insert(t, k, a < b ? h : (h | INT_MIN)) < 0) full = 1;
     }
     __syncthreads();
     if (full) {
         if (threadIdx.x == 0) tab_base = atomicAdd(&ctl[1], tot + tot / 3);
         __syncthreads();
-        he_bucket_global(r, m, over, no, bk, lg, tab + tab_base,
-                         (unsigned long long)(tot + tot / 3), he);
+        he_bucket_global(tris, r, m, over, no, bk, lg, tab + tab_base, tot + tot / 3, he);
         return;
     }
 #pragma unroll
     for (int k = 0; k < kHeSolvePer; ++k)
         if (slot[k] >= 0) he[e[k].hd & INT_MAX] = he_twin(t.first[slot[k]], e[k].hd);
     for (int i = threadIdx.x; i < no; i += kHePartBlock) {
-        const HeEntry o = over[i];
-        const unsigned long long k = he_key(o.lo, o.hi);
+        const int h = over[i];
+        int a, b;
+        he_ends(tris, h, a, b);
+        const unsigned long long k = he_key(min(a, b), max(a, b));
         if (he_bucket(he_mix(k), lg) != bk) continue;
         const int s = he_lds_find(t, k);
-        if (s >= 0) he[o.hd & INT_MAX] = he_twin(t.first[s], o.hd);
+        if (s >= 0) he[h] = he_twin(t.first[s], a < b ? h : (h | INT_MIN));
     }
 }
 
 // Workspace of the partitioned way: the histogram rows and their starts,
-// the bucket totals, two control words, the regions, the overflow list and
-// the global table of buckets that outgrow their LDS table.
+// the bucket totals, two control words, the regions, the overflow list (a
+// half-edge's index, 4 bytes; its points are T's) and the global table of
+// buckets that outgrow their LDS table.
 struct HeParts {
     int lg, nb, chunks;
     size_t hist, start, total, ctl, region, over, tab, end;
@@ -561,8 +576,8 @@ HeParts he_parts(int cap) {
     p.total = take(4 * (size_t)p.nb);
     p.ctl = take(8);
     p.region = take(sizeof(HeEntry) * (size_t)p.nb * kHeRegion);
-    p.over = take(sizeof(HeEntry) * 3 * (size_t)cap);
-    p.tab = take(sizeof(HeSlot) * 4 * (size_t)cap);
+    p.over = take(4 * 3 * (size_t)cap);
+    p.tab = take(4 * 4 * (size_t)cap);
     p.end = o;
     return p;
 }
@@ -587,7 +602,7 @@ pl_status launch_user_halfedges(const int32_t *tris, const int32_t *n_tri, int c
         auto *total = reinterpret_cast<int32_t *>(w + p.total);
         auto *ctl = reinterpret_cast<int32_t *>(w + p.ctl);
         auto *region = reinterpret_cast<HeEntry *>(w + p.region);
-        auto *over = reinterpret_cast<HeEntry *>(w + p.over);
+        auto *over = reinterpret_cast<int32_t *>(w + p.over);
         const size_t hist_lds = 4 * (size_t)p.nb;
         k_he_count<<<p.chunks, kHePartBlock, hist_lds, s>>>(tris, n_tri, cap, p.lg, hist);
         if (pl_status st = hip_check(hipGetLastError(), "k_he_count")) return st;
@@ -599,8 +614,8 @@ pl_status launch_user_halfedges(const int32_t *tris, const int32_t *n_tri, int c
         k_he_scatter<<<p.chunks, kHePartBlock, scatter_lds, s>>>(tris, n_tri, cap, p.lg, hist, start,
                                                                  region, ctl, over, he);
         if (pl_status st = hip_check(hipGetLastError(), "k_he_scatter")) return st;
-        k_he_solve<<<p.nb, kHePartBlock, 0, s>>>(region, total, ctl, over, p.lg,
-                                                 reinterpret_cast<HeSlot *>(w + p.tab), he);
+        k_he_solve<<<p.nb, kHePartBlock, 0, s>>>(tris, region, total, ctl, over, p.lg,
+                                                 reinterpret_cast<int *>(w + p.tab), he);
         return hip_check(hipGetLastError(), "k_he_solve");
     }
     const size_t slots = table_slots(cap);

@@ -277,3 +277,11 @@ def test_plans_on_another_device_are_refused(pl, call):
             pl.GaussianAccumulator(1, device="cpu")
         else:
             pl._stream(torch.device("cpu") if call == "device" else "cpu")
+
+
+@pytest.mark.parametrize("cap,most", [(1, 38400), (100, 41728), (5000, 476160), (20000, 1904384),
+                                      (612000, 63463424), (2000000, 271016704), (5592405, 771784960)])
+def test_user_halfedges_workspace_has_no_room_for_rare_inputs_alone(pl, cap, most):
+    """The table of buckets that outgrow LDS and the overflow list take no more
+    than the list of whole entries did: 104 bytes per triangle at 612 k."""
+    assert 0 < pl._lib.pl_user_halfedges_workspace(cap) <= most

@@ -276,3 +276,29 @@ def test_cost_follows_the_mesh_not_its_buffer(pl):
     full, one = least(cap), least(1)
     say("user halfedges full", full, "ms, one triangle", one, "ms")
     assert one < 0.32 * full
+
+
+def test_full_bucket_of_repeated_edges(pl):
+    """A bucket that outgrows its LDS table, every edge once to four times and in
+    either direction: only first half-edges are paired."""
+    cap, lg, bucket = 20000, 5, 11
+    rng = np.random.default_rng(31)
+    edges = set()
+    while len(edges) < 4500:
+        key = _unmix((bucket << (64 - lg)) | int(rng.integers(0, 1 << (64 - lg))))
+        lo, hi = _signed(key >> 32), _signed(key & 0xffffffff)
+        if lo < hi:
+            edges.add((lo, hi))
+    E = np.repeat(np.array(sorted(edges), dtype=np.int64), rng.integers(1, 5, 4500), axis=0)
+    flip = rng.random(len(E)) < 0.5
+    E[flip] = E[flip][:, ::-1]
+    T = np.concatenate([E, rng.integers(-1000, 1000, size=(len(E), 1))], axis=1)
+    T = T[rng.permutation(len(T))].astype(np.int32)
+    assert len(T) <= cap
+    P = np.zeros((cap, 3), dtype=np.int32)
+    P[:len(T)] = T
+    say("user halfedges full bucket, repeated edges", len(T), "cap", cap)
+    got = gpu_he(pl, P, len(T))
+    want = oracle.user_halfedges(T)
+    assert np.array_equal(got[:3 * len(T)], want)
+    assert (want >= 0).sum() >= 2000
