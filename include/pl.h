@@ -525,8 +525,9 @@ pl_status pl_smooth_frame(const pl_frame *frame, pl_dtype ndt, void *ws, size_t 
  * n_kinds entries, may be NULL) describing launch k: PL_LAUNCH_* bits of the
  * work it carries and, in bits 8..15, the number of filter sweeps it fuses.
  * *n_launches (HOST, may be NULL) receives the number of launches.  A frame
- * meshed by whole rows reports pl_mesh_opc's two launches as one count and
- * one emit launch.  Recording events costs the stream a few microseconds
+ * of more than 2^22 quads starts with pl_mesh_opc's own three launches: the
+ * masks and counts, the counts' sums (PL_LAUNCH_MESH_COUNT as well) and the
+ * emit.  Recording events costs the stream a few microseconds
  * each, so the per-launch durations are upper bounds.
  * Errors: those of pl_smooth_frame; PL_ERR_ARG for a negative count or a
  * positive count with a NULL array.

@@ -189,10 +189,11 @@ pl_status run(const pl_frame &f, void *ws, hipStream_t s, LaunchLog *log) {
     const bool apart = mesh_segments(Q) > kMeshSegMax;
     if (pl_status st = log_start(log, s)) return st;
     if (apart) {
-        if (pl_status st = launch_mesh(f.pts, M, N, f.tri_valid, f.tri_map, f.triangles,
-                                       f.halfedges, (int)T, f.n_tri, ws, s))
-            return st;
+        if (pl_status st = launch_mesh_count(mj, s)) return st;
         if (pl_status st = log_launch(log, PL_LAUNCH_MESH_COUNT, s)) return st;
+        if (pl_status st = launch_mesh_sums(mj, s)) return st;
+        if (pl_status st = log_launch(log, PL_LAUNCH_MESH_COUNT, s)) return st;
+        if (pl_status st = launch_mesh_emit(mj, s)) return st;
         if (pl_status st = log_launch(log, PL_LAUNCH_MESH_EMIT, s)) return st;
     }
     w += mesh_workspace(M, N);

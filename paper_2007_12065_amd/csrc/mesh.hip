@@ -97,21 +97,31 @@ MeshArgs mesh_args(const float *pts, int M, int N, uint8_t *tri_valid, int32_t *
                     reinterpret_cast<int *>(w + o_sums), tri_valid, tri_map, triangles, halfedges, n_tri, cap, N, (int)Q, QuadDiv::by(N - 1)};
 }
 
+pl_status launch_mesh_count(const MeshArgs &m, hipStream_t s) {
+    k_mesh_count<<<mesh_segments((size_t)m.Q), kTileBlock, 0, s>>>(m);
+    return hip_check(hipGetLastError(), "k_mesh_count");
+}
+
+pl_status launch_mesh_sums(const MeshArgs &m, hipStream_t s) {
+    k_mesh_sums<<<1, kMeshSumBlock, 0, s>>>(m);
+    return hip_check(hipGetLastError(), "k_mesh_sums");
+}
+
+pl_status launch_mesh_emit(const MeshArgs &m, hipStream_t s) {
+    const int blocks = mesh_segments((size_t)m.Q);
+    if (blocks > kMeshSegMax) k_mesh_emit<true><<<blocks, kTileBlock, 0, s>>>(m);
+    else k_mesh_emit<false><<<blocks, kTileBlock, 0, s>>>(m);
+    return hip_check(hipGetLastError(), "k_mesh_emit");
+}
+
 pl_status launch_mesh(const float *pts, int M, int N, uint8_t *tri_valid, int32_t *tri_map,
                       int32_t *triangles, int32_t *halfedges, int32_t cap, int32_t *n_tri,
                       void *ws, hipStream_t s) {
     const MeshArgs m = mesh_args(pts, M, N, tri_valid, tri_map, triangles, halfedges, cap, n_tri, ws);
-    const int blocks = mesh_segments((size_t)m.Q);
-    k_mesh_count<<<blocks, kTileBlock, 0, s>>>(m);
-    if (pl_status st = hip_check(hipGetLastError(), "k_mesh_count")) return st;
-    if (blocks > kMeshSegMax) {
-        k_mesh_sums<<<1, kMeshSumBlock, 0, s>>>(m);
-        if (pl_status st = hip_check(hipGetLastError(), "k_mesh_sums")) return st;
-        k_mesh_emit<true><<<blocks, kTileBlock, 0, s>>>(m);
-    } else {
-        k_mesh_emit<false><<<blocks, kTileBlock, 0, s>>>(m);
-    }
-    return hip_check(hipGetLastError(), "k_mesh_emit");
+    if (pl_status st = launch_mesh_count(m, s)) return st;
+    if (mesh_segments((size_t)m.Q) > kMeshSegMax)
+        if (pl_status st = launch_mesh_sums(m, s)) return st;
+    return launch_mesh_emit(m, s);
 }
 
 }  // namespace pl

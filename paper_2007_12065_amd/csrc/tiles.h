@@ -62,6 +62,10 @@ struct MeshArgs {
 // The arguments of a frame whose mesh buffers lie in `ws` (mesh_workspace).
 MeshArgs mesh_args(const float *pts, int M, int N, uint8_t *tri_valid, int32_t *tri_map,
                    int32_t *triangles, int32_t *halfedges, int32_t cap, int32_t *n_tri, void *ws);
+// pl_mesh_opc's launches (the sums for frames of more than kMeshSegMax segments).
+pl_status launch_mesh_count(const MeshArgs &m, hipStream_t s);
+pl_status launch_mesh_sums(const MeshArgs &m, hipStream_t s);
+pl_status launch_mesh_emit(const MeshArgs &m, hipStream_t s);
 
 // Masks and count of segment `sg`.
 __device__ __forceinline__ void mesh_count_seg(const MeshArgs &m, int sg) {

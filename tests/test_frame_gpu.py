@@ -250,3 +250,22 @@ def test_launch_layout(pl, kind):
     assert sum((x >> 8) & 0xff for x in bil) == k.iters_bil
     if kind.startswith("rgbd"):
         assert len(kinds) <= 3
+
+
+def test_launch_layout_with_summed_segments(pl):
+    """A frame whose mesh segments are summed by a launch of its own reports that
+    launch too: as many kinds as launches, an event after each."""
+    import torch
+    M, N = 1100, 4000
+    plan = pl.FramePlan(M, N, 3, 1.0, 1, 3, 0.1, 0.1, 1, torch.float32, torch.device("cuda:0"))
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(8)]
+    print("[case] run_fused_events 1100x4000", flush=True)
+    x = dev_t(random_grid(M, N, 14, nan_frac=0.05))
+    plan.run_fused_events(x, events)
+    kinds = plan.run_fused_events(x, events)
+    torch.cuda.synchronize()
+    count, emit = pl.PL_LAUNCH_MESH_COUNT, pl.PL_LAUNCH_MESH_EMIT
+    assert kinds[:3] == [count, count, emit] and len(kinds) == 5, kinds
+    assert kinds[3] & pl.PL_LAUNCH_LAPLACIAN and kinds[4] & pl.PL_LAUNCH_BILATERAL
+    times = [events[k].elapsed_time(events[k + 1]) for k in range(5)]
+    assert min(times) > 0, times
