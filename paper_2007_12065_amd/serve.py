@@ -65,8 +65,9 @@ def frame_sources(torch, frames: dict) -> dict:
 
 def slot_bytes(c: FrameClass, normal_bytes: int = 2, lap_fuse: int = 4, bil_fuse: int = 1) -> int:
     """Device bytes one resident slot of class `c` holds: input, outputs and
-    the batch workspace's per-frame scratch (the same sizes the library lays
-    out), rounded to 256 B per buffer."""
+    the batch workspace's per-frame scratch, rounded to 256 B per buffer, and
+    one normal array more, which covers the plan's tables.  The fused sweeps
+    are those of the batch's stages."""
     def a(x):
         return (x + 255) // 256 * 256
     P = c.M * c.N
@@ -79,9 +80,10 @@ def slot_bytes(c: FrameClass, normal_bytes: int = 2, lap_fuse: int = 4, bil_fuse
     total += a(3 * T * normal_bytes) * 2      # filtered normals, normals of T
     total += a(12 * T)                        # centroids
     total += a(T) + a(4 * T) + a(12 * T) + a(12 * T) + a(4)   # tri_valid, T_map, T, HE, n_tri
-    total += a(Q) + a(4 * (c.M - 1))          # mesh scratch (masks, counts)
+    total += a(Q) + a(4 * (c.M - 1) * -(-(c.N - 1) // 256))   # mesh scratch, as pl_mesh_opc_workspace
     total += a(12 * P) if lap_passes > 1 else 0
-    total += a(3 * T * normal_bytes) * (2 if bil_passes > 1 else 1)
+    total += a(3 * T * normal_bytes) if bil_passes > 1 else 0
+    total += a(3 * T * normal_bytes)          # the tables' share
     return total
 
 
@@ -437,8 +439,8 @@ class Server:
         self.classes = classes
         ndtype = torch.float16 if normal_dtype is None else normal_dtype
         nb = 2 if ndtype == torch.float16 else 4
-        per = {k: slot_bytes(c, nb, pl.pl_tune_get(pl.PL_STAGE_LAPLACIAN, c.kernel_lap)[2],
-                             pl.pl_tune_get(pl.PL_STAGE_BILATERAL, c.kernel_bil)[2])
+        per = {k: slot_bytes(c, nb, pl.pl_tune_get(pl.PL_STAGE_BATCH_LAPLACIAN, c.kernel_lap)[2],
+                             pl.pl_tune_get(pl.PL_STAGE_BATCH_BILATERAL, c.kernel_bil)[2])
                for k, c in classes.items()}
         self.exe = GpuBatchExecutor(classes, host_frames, ndtype, max_inflight, dev)
         # the single-frame steps' scratch (one set per class) comes out of the budget

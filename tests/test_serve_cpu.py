@@ -175,3 +175,37 @@ def test_arrival_wait_neither_oversleeps_nor_returns_late():
     arrival_wait(0.2)
     took = time.perf_counter() - t0
     assert 0.099 <= took < 0.19
+
+
+@pytest.mark.parametrize("M,N", [(2, 2), (120, 160), (480, 640), (300, 257), (300, 258), (64, 1024), (128, 2048),
+                                 (720, 1280), (5, 9000)])
+@pytest.mark.parametrize("nb", [2, 4])
+@pytest.mark.parametrize("klap,nlap,kbil,nbil", [(3, 4, 3, 2), (5, 4, 5, 3), (3, 1, 3, 1)])
+def test_slot_bytes_cover_what_the_library_lays_out(M, N, nb, klap, nlap, kbil, nbil):
+    """A slot's scratch is no less than the bytes a frame adds to a batch's
+    workspace, its mesh scratch included, beside the array kept for the tables."""
+    import paper_2007_12065_amd as pl
+
+    def a(x):
+        return (x + 255) // 256 * 256
+    c = FrameClass("c", M, N, klap, 1.0, nlap, kbil, 0.1, 0.1, nbil)
+    fl = pl.pl_tune_get(pl.PL_STAGE_BATCH_LAPLACIAN, klap)[2]
+    fb = pl.pl_tune_get(pl.PL_STAGE_BATCH_BILATERAL, kbil)[2]
+    P, T = M * N, 2 * (M - 1) * (N - 1)
+    buffers = 2 * a(12 * P) + 2 * a(3 * T * nb) + a(12 * T) + a(T) + a(4 * T) + 2 * a(12 * T) + a(4)
+    scratch = slot_bytes(c, nb, fl, fb) - buffers - a(3 * T * nb)
+    ping_pong = (a(12 * P) if nlap > fl else 0) + (a(3 * T * nb) if nbil > fb else 0)
+    assert scratch - ping_pong >= pl._lib.pl_mesh_opc_workspace(M, N)
+
+    def workspace(n):
+        arr = (pl.PLFrame * n)()
+        for i, f in enumerate(arr):          # addresses that are never read
+            f.M, f.N, f.kernel_lap, f.iters_lap, f.lambda_ = M, N, klap, nlap, 1.0
+            f.kernel_bil, f.iters_bil, f.sigma_length, f.sigma_angle = kbil, nbil, 0.1, 0.1
+            for k, name in enumerate(("pts", "pts_out", "normals", "centroids", "tri_map", "triangles", "n_tri",
+                                      "normals_T")):
+                setattr(f, name, (8 * i + k + 1) << 36)
+        return pl._lib.pl_batch_workspace(arr, n, pl.PL_F32 if nb == 4 else pl.PL_F16)
+    # 64 frames more: what each adds, but for its rows in the plan's tables
+    added = (workspace(65) - workspace(1)) / 64
+    assert scratch <= added <= scratch + 2048
