@@ -498,7 +498,8 @@ pl_status pl_batch_replay_bounded(pl_batch batch, int32_t n_active, hipStream_t 
  * triangles in T from the validity masks instead of reading T_map), and the
  * first bilateral pass computes the normals and centroids itself: one
  * launch per filter pass (with the committed tuning a frame of four 3x3
- * Laplacian sweeps and two bilateral ones: 2 launches instead of 5).
+ * Laplacian sweeps and two bilateral ones: 2 launches instead of 5).  Frames
+ * of more than 2^21 quads may be meshed by launches of their own instead.
  *
  * frame      HOST pointer to one pl_frame (the layout is documented with the
  *            batched path below); its buffers are device memory owned by
@@ -525,9 +526,9 @@ pl_status pl_smooth_frame(const pl_frame *frame, pl_dtype ndt, void *ws, size_t 
  * n_kinds entries, may be NULL) describing launch k: PL_LAUNCH_* bits of the
  * work it carries and, in bits 8..15, the number of filter sweeps it fuses.
  * *n_launches (HOST, may be NULL) receives the number of launches.  A frame
- * of more than 2^22 quads starts with pl_mesh_opc's own three launches: the
- * masks and counts, the counts' sums (PL_LAUNCH_MESH_COUNT as well) and the
- * emit.  Recording events costs the stream a few microseconds
+ * of more than 2^22 quads, or of more than 2^21 whose filters take one launch
+ * each, starts with pl_mesh_opc's own launches: the masks and counts, past 2^22
+ * the counts' sums (PL_LAUNCH_MESH_COUNT as well), and the emit.  Recording events costs the stream a few microseconds
  * each, so the per-launch durations are upper bounds.
  * Errors: those of pl_smooth_frame; PL_ERR_ARG for a negative count or a
  * positive count with a NULL array.

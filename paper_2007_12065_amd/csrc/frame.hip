@@ -25,8 +25,9 @@
 // A launch that carries mesh work has two kinds of workgroups: the filter's
 // tiles first, then one workgroup per 256-quad segment of the mesh.  (Frames
 // of more than kMeshSegMax segments need the segments' sums between count and
-// emit; they get pl_mesh_opc's own launches before the filters, which at that
-// size cost little.)  Each kind is dealt over the eight XCDs on its own (each
+// emit, and past kFrameGatherMax the emit costs more beside a gathering pass
+// than by itself: those get pl_mesh_opc's own launches before the filters.)
+// Each kind is dealt over the eight XCDs on its own (each
 // part padded to a multiple of eight workgroups, and xcd_remap_active gives
 // each XCD a contiguous run).
 #include "groups.h"
@@ -38,6 +39,15 @@ namespace pl {
 namespace {
 
 enum MeshKind { kMeshNone = 0, kMeshCount = 1, kMeshEmit = 2 };
+
+// Segments of a frame up to which the emit rides in a gathering bilateral pass,
+// whose every tile sums the counts before it to rank its triangles.  Beside it
+// against before the filters (one Laplacian launch; 3x3 with four and two
+// sweeps, 5x5 with two and one): 5,459 segments 126 and 130 us, 146 and 145;
+// 8,088: 185 and 179, 221 and 203; 11,986: 288 and 258, 340 and 287.  In a
+// second Laplacian launch the emit is the better for it up to kMeshSegMax
+// (11,986: 300 and 308, 16,304: 419 and 422).
+constexpr int kFrameGatherMax = 8192;
 
 // Mesh workgroups of a launch, padded to whole rounds of the eight XCDs.
 __host__ __device__ inline int mesh_blocks(const MeshArgs &m) {
@@ -184,15 +194,23 @@ pl_status run(const pl_frame &f, void *ws, hipStream_t s, LaunchLog *log) {
     char *w = static_cast<char *>(ws);
     const MeshArgs mj = mesh_args(f.pts, M, N, f.tri_valid, f.tri_map, f.triangles, f.halfedges,
                                   (int)T, f.n_tri, ws);
-    // frames whose segments are summed by a launch: pl_mesh_opc's launches
-    // first, and no mesh work in the filter launches
-    const bool apart = mesh_segments(Q) > kMeshSegMax;
+    const int Rl = f.kernel_lap / 2, Rb = f.kernel_bil / 2;
+    const TileCfg cl = tile_cfg(frame_stage(true, M, N), Rl), cb = tile_cfg(frame_stage(false, M, N), Rb);
+    const int Ll = f.iters_lap == 0 ? 1 : (f.iters_lap + cl.fuse - 1) / cl.fuse;
+    const int Lb = f.iters_bil == 0 ? 1 : (f.iters_bil + cb.fuse - 1) / cb.fuse;
+    // pl_mesh_opc's launches first, and no mesh work in the filter launches:
+    // frames whose segments are summed by a launch, and where the emit would
+    // ride in the one bilateral pass of a frame too large for that
+    const int segments = mesh_segments(Q);
+    const bool apart = segments > kMeshSegMax || (Ll + Lb == 2 && segments > kFrameGatherMax);
     if (pl_status st = log_start(log, s)) return st;
     if (apart) {
         if (pl_status st = launch_mesh_count(mj, s)) return st;
         if (pl_status st = log_launch(log, PL_LAUNCH_MESH_COUNT, s)) return st;
-        if (pl_status st = launch_mesh_sums(mj, s)) return st;
-        if (pl_status st = log_launch(log, PL_LAUNCH_MESH_COUNT, s)) return st;
+        if (segments > kMeshSegMax) {
+            if (pl_status st = launch_mesh_sums(mj, s)) return st;
+            if (pl_status st = log_launch(log, PL_LAUNCH_MESH_COUNT, s)) return st;
+        }
         if (pl_status st = launch_mesh_emit(mj, s)) return st;
         if (pl_status st = log_launch(log, PL_LAUNCH_MESH_EMIT, s)) return st;
     }
@@ -200,11 +218,6 @@ pl_status run(const pl_frame &f, void *ws, hipStream_t s, LaunchLog *log) {
     float *lap_tmp = f.iters_lap > 1 ? reinterpret_cast<float *>(w) : nullptr;
     w += f.iters_lap > 1 ? align_up(12 * P, 256) : 0;
     NT *bil_tmp = f.iters_bil > 1 ? reinterpret_cast<NT *>(w) : nullptr;
-
-    const int Rl = f.kernel_lap / 2, Rb = f.kernel_bil / 2;
-    const TileCfg cl = tile_cfg(frame_stage(true, M, N), Rl), cb = tile_cfg(frame_stage(false, M, N), Rb);
-    const int Ll = f.iters_lap == 0 ? 1 : (f.iters_lap + cl.fuse - 1) / cl.fuse;
-    const int Lb = f.iters_bil == 0 ? 1 : (f.iters_bil + cb.fuse - 1) / cb.fuse;
 
     const float *cur = f.pts;
     int left = f.iters_lap;

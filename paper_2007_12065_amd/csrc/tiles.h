@@ -33,9 +33,12 @@ constexpr int kTileBlock = 256;        // threads per workgroup for every tile b
 constexpr int kMeshSeg = kTileBlock;           // quads per segment
 constexpr int kMeshPerSeg = kMeshSeg / kWave;  // chunks per segment
 // Segments per frame up to which an emit workgroup sums the counts before its
-// segment itself; past it a launch of one workgroup does for all of them
-// (6 us and more, where the workgroups' own sums grow with the square: 9,101
-// segments take 26.6 us to emit, 22.8 us with the sums at hand).
+// segment itself; past it a launch of one workgroup does for all of them.  The
+// workgroups' own sums grow with the square (9,101 segments take 26.6 us to
+// emit, 22.8 us with the sums at hand), the launch takes 6 to 9 us.  A mesh by
+// own sums against by a launch: 9,100 segments 38.3 and 40.9 us, 11,986 47.4
+// and 49.5, 15,184 57.8 and 59.7, 16,304 61.8 and 62.2, 18,383 71.2 and 72.5
+// (equal within its runs' spread); a batch is the same either way.
 constexpr int kMeshSegMax = 16384;
 
 struct MeshChunk {

@@ -269,3 +269,18 @@ def test_launch_layout_with_summed_segments(pl):
     assert kinds[3] & pl.PL_LAUNCH_LAPLACIAN and kinds[4] & pl.PL_LAUNCH_BILATERAL
     times = [events[k].elapsed_time(events[k + 1]) for k in range(5)]
     assert min(times) > 0, times
+
+
+@pytest.mark.parametrize("M,N,laps,apart", [(300, 7000, 1, False), (310, 7000, 1, True), (310, 7000, 5, False)])
+def test_mesh_of_large_frames_beside_or_before_the_filters(pl, M, N, laps, apart):
+    """Past 8,192 segments the emit does not ride in a frame's only bilateral
+    pass (310 x 7000: 8,449), but in a second Laplacian launch."""
+    import torch
+    s = spec(random_grid(M, N, 16, nan_frac=0.05), 3, 1.0, laps, 3, 0.1, 0.1, 1)
+    print(f"[case] pl_smooth_frame {M}x{N} {laps} sweeps", flush=True)
+    assert_frame_equal(pl.pl_smooth_frame(s, torch.float32), single(pl, s, torch.float32), f"{M}x{N}")
+    plan = pl.FramePlan(M, N, 3, 1.0, laps, 3, 0.1, 0.1, 1, torch.float32, torch.device("cuda:0"))
+    kinds = plan.run_fused_events(s["pts"], [torch.cuda.Event(enable_timing=True) for _ in range(8)])
+    torch.cuda.synchronize()
+    mesh = [x for x in kinds if not x & (pl.PL_LAUNCH_LAPLACIAN | pl.PL_LAUNCH_BILATERAL)]
+    assert mesh == ([pl.PL_LAUNCH_MESH_COUNT, pl.PL_LAUNCH_MESH_EMIT] if apart else []), kinds
