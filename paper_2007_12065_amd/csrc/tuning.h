@@ -42,9 +42,11 @@ TileCfg bil_launch_tile(int R, TileCfg c, int F);
 // first be cut to two thirds or half of their rows (6 x 30 quads to 4 x 32 or
 // 3 x 32): of the three the one that gives a CU the fewest tiles, then the one
 // of fewest rows (a small frame's launch takes as long as the CU with the most
-// rows).  At 6, 4 and 3 rows a 120 x 160 frame takes 13.5, 13.0 and 12.4 us (one
-// tile per CU each), a 200 x 220 one 15.7, 14.9 and 15.4 (2, 2 and 3 tiles), a
-// 240 x 320 one 16.6, 17.7 and 17.5 (2, 3 and 4).
+// rows).  Frames of four and two sweeps, us (tiles of the fullest CU) at 6, 4
+// and 3 rows: 120 x 160 15.1 (1), 14.2 (1), 13.6 (1); 200 x 220 17.2 (2), 16.6
+// (2), 16.1 (2); 200 x 300 18.5 (2), 17.1 (2), 17.4 (3); 240 x 320 18.1 (2),
+// 19.5 (3), 19.3 (4); 64 x 1024 17.6 (2), 17.0 (2), 17.2 (3).  Two rows or 5 x
+// 30 are best at few sizes and by little (120 x 160 14.1 and 14.3).
 TileCfg bil_frame_tile(int R, TileCfg c, int F, int Mq, int Nq);
 
 // Current configuration for a stage and window radius (1..4).
