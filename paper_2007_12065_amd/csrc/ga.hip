@@ -26,7 +26,7 @@
 // accumulator's workspace (copy = workgroup index mod kGaReplicas, which
 // also keeps each copy on one XCD), and a second launch folds the copies
 // into the caller's counts and clears them; a small integration adds into
-// the counts at once (kGaDirectWork).  Sums of integers do not depend on the
+// the counts at once (ga_direct_work).  Sums of integers do not depend on the
 // order of the adds.
 #include "ga.h"
 #include "tuning.h"
@@ -51,13 +51,19 @@ constexpr int kGaBlock = 512;
 constexpr int kGaBatch = 6;                // candidate loads issued together
 constexpr int kGaMaxGrid = 768;             // workgroups of one integration launch
 constexpr int kGaReplicas = 16;             // histogram copies the workgroups flush into
-// Up to kGaDirectWork workgroups' worth of rows go to at most kGaDirectGrid
-// workgroups, which add straight into the caller's counts: that many adds to
-// one address cost less than the second launch.  Microseconds by workgroups'
-// worth of rows (512 each), one launch against two: 30: 3.9, 5.9; 150: 6.2,
-// 6.9; 299: 7.2, 7.6; 450: 10.5, 10.8; past that two are as fast or faster
-// (598: 9.9, 9.3).
-constexpr int kGaDirectGrid = 160, kGaDirectWork = 480;
+// Up to ga_direct_work(cells) workgroups' worth of rows (512 each) go to at most
+// kGaDirectGrid workgroups, which add straight into the caller's counts: that
+// many adds to one address cost less than the second launch, unless the cells
+// are few, so that every workgroup adds to every one.  Microseconds by cells and
+// workgroups' worth of evenly spread directions, one launch against two:
+//      80 cells   80: 5.6, 6.3   150: 6.8, 6.3   299: 7.8, 7.1   479: 9.3, 7.1
+//     320         80: 5.7, 6.4   150: 7.0, 6.5   299: 8.0, 7.6   479: 9.5, 7.8
+//   1,280         80: 5.9, 7.0   150: 7.7, 7.3   420: 8.7, 9.0   479: 9.8, 9.3
+//   5,120         80: 6.3, 8.0   150: 7.7, 8.7   420: 9.7, 13.0  479: 11.1, 14.0
+// and of directions in three clusters, at 1,280 cells 420: 8.1, 8.0, 479: 9.0, 8.0,
+// at 5,120 cells 420: 9.1, 9.3, 479: 10.5, 9.6.
+constexpr int kGaDirectGrid = 160;
+constexpr int ga_direct_work(int cells) { return cells < 1000 ? 100 : cells < 4000 ? 420 : 480; }
 
 // Bin of a direction with |n|^2 in [0.25, 4]: the cube face of its largest
 // component (+x, -x, +y, -y, +z, -z), then the two other components over
@@ -480,7 +486,7 @@ pl_status ga_integrate(const pl_ga_s *g, const void *normals, pl_dtype ndt, cons
     // one row per thread and pass, at most kGaMaxGrid workgroups (past that,
     // threads loop: fewer histograms to clear and flush)
     const long work = (rows + kGaBlock - 1) / kGaBlock;
-    const bool direct = work <= kGaDirectWork;
+    const bool direct = work <= ga_direct_work(T.n_cells);
     const int grid = (int)std::min<long>(direct ? kGaDirectGrid : kGaMaxGrid, work);
     const size_t lds = g->lds;
     uint32_t *copies = direct ? counts : reps;

@@ -240,3 +240,23 @@ def test_arbitrary_cell_sets(pl, n_cells, seed):
     assert np.array_equal(cells.cpu().numpy(), want_idx)
     assert np.array_equal(counts.cpu().numpy(), want_counts)
     ga.close()
+
+
+@pytest.mark.parametrize("level,work", [(2, 100), (3, 420), (4, 480)])
+@pytest.mark.parametrize("extra", [0, 1])
+def test_one_launch_and_two_add_to_given_counts(pl, level, work, extra):
+    """The most rows that are added in one launch (512 a workgroup's worth, fewer
+    of them for few cells), and one more: counts that are passed in are added to,
+    twice, and equal the cells' histogram."""
+    import torch
+    rng = np.random.default_rng(level + extra)
+    N = to_dev(unit_rows(rng.normal(size=(512 * work + extra, 3))).astype(np.float32))
+    ga = pl.GaussianAccumulator(level)
+    counts = torch.full((ga.n_cells,), 3, dtype=torch.int32, device="cuda:0").view(torch.uint32)
+    say("ga one launch or two", level, work, extra)
+    _, cells = ga.integrate(N, counts=counts, cell_out=True)
+    ga.integrate(N, counts=counts)
+    torch.cuda.synchronize()
+    want = 3 + 2 * np.bincount(cells.cpu().numpy(), minlength=ga.n_cells)
+    assert np.array_equal(counts.cpu().numpy(), want)
+    ga.close()
