@@ -481,3 +481,10 @@ def test_bilateral_keeps_the_bits_of_unusable_normals(pl, kernel, iters, f16):
     got = out.cpu().numpy()
     assert np.array_equal(got.view(bits.dtype)[kind <= 3], bits[kind <= 3])
     assert not np.isnan(got[kind > 3]).any()
+
+
+@pytest.mark.parametrize("M,N", [(2, 513), (2, 514), (2, 70000), (3, 257), (3, 300), (3, 20001), (4, 1025)])
+def test_mesh_of_few_long_rows(pl, M, N):
+    """Rows longer than a segment, with none above or none below: the counts
+    before a segment's own, above and below are summed apart."""
+    mesh_compare(pl, random_grid(M, N, 2 * M + N, nan_frac=0.15))
