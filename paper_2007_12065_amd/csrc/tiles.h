@@ -225,7 +225,7 @@ __device__ __forceinline__ void mesh_emit_seg(const MeshArgs &m, int sg) {
     const int q0 = (sg * kMeshPerSeg + wave) * kWave;
     // segments of the quads above and below this chunk's first
     const int qt = q0 - Nq, qb = q0 + Nq;
-    const int st = max(qt, 0) / kMeshSeg, sb = qb < m.Q ? qb / kMeshSeg : sg;    // (no row below: not used)
+    const int st = max(qt, 0) / kMeshSeg, sb = qb < m.Q ? qb / kMeshSeg : sg;   // no row below: none to sum
     const int k0 = q0 / kWave, kt = qt >> 6, kb = qb >> 6;
     const MeshChunk c = mesh_chunk(m.chunks, K, k0), cl = mesh_chunk(m.chunks, K, k0 - 1),
                     cr = mesh_chunk(m.chunks, K, k0 + 1), ct = mesh_chunk(m.chunks, K, kt),
@@ -238,9 +238,9 @@ __device__ __forceinline__ void mesh_emit_seg(const MeshArgs &m, int sg) {
         bb = m.sums[sb];
         if (sg == S - 1 && threadIdx.x == 0) *m.n_tri = m.sums[S];
     } else {
-        // the workgroup sums the segments before its first one above (before its
-        // own in the first row: nothing above), each wave the few between
-        const int lo = (sg + 1) * kMeshSeg <= Nq ? sg : max(sg * kMeshSeg - Nq, 0) / kMeshSeg;
+        // the workgroup sums the segments before its first one above, each
+        // wave the few between
+        const int lo = max(sg * kMeshSeg - Nq, 0) / kMeshSeg;
         const int a = wave_sum(mesh_sum_segs(m.seg, lo, (int)threadIdx.x, kTileBlock));
         if (lane == 0) part[wave] = a;
         __syncthreads();
