@@ -488,3 +488,25 @@ def test_mesh_of_few_long_rows(pl, M, N):
     """Rows longer than a segment, with none above or none below: the counts
     before a segment's own, above and below are summed apart."""
     mesh_compare(pl, random_grid(M, N, 2 * M + N, nan_frac=0.15))
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("M,N", [(2, 2), (2, 3), (17, 17), (3, 130), (40, 95)])
+def test_bilateral_zero_sweeps_copy_the_bits(pl, M, N, f16):
+    """No sweeps: every bit of the normals, payloads of NaNs and signs of zeros
+    included, in the output and at its triangle's place in T."""
+    import torch
+    rng = np.random.default_rng(M * N)
+    word = np.uint16 if f16 else np.uint32
+    bits = rng.integers(0, np.iinfo(word).max, size=(M - 1, N - 1, 2, 3), dtype=word, endpoint=True)
+    n = to_dev(bits.view(np.float16 if f16 else np.float32))
+    c = torch.zeros((M - 1, N - 1, 2, 3), device="cuda:0")
+    mesh = pl.pl_mesh_opc(to_dev(random_grid(M, N, M + N, nan_frac=0.2)))
+    say("bilateral zero sweeps", (M, N), "f16" if f16 else "f32")
+    for tri_map in (None, mesh["tri_map"]):
+        for kernel in (3, 9):
+            out, nT = pl.pl_bilateral(n, c, kernel, 0.1, 0.1, 0, tri_map=tri_map)
+            torch.cuda.synchronize()
+            assert np.array_equal(host(out).view(word), bits)
+    where, m = host(mesh["tri_map"]), int(mesh["n_tri"].item())
+    assert np.array_equal(host(nT).view(word)[:m], bits.reshape(-1, 3)[where >= 0])
