@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kTileBlock, bil_waves_per_simd(R, false)) void k_bi
 // Zero sweeps: the normals' bits into the output and gathered onto T.  Bound by
 // its bytes; a thread takes 12 of them, a float32 triangle or a float16 quad.  As
 // a pass of k_bilateral over no sweeps (strided streaming stores, the sums'
-// registers and LDS) 720 x 1280 points took 25.5 us, here 12.2 (4.3 TB/s);
+// registers and LDS) 720 x 1280 points took 25.5 us, here 12.2 (70 MB, 5.8 TB/s);
 // 480 x 640 7.6 and 5.1.
 template <typename NT>
 __global__ __launch_bounds__(kTileBlock) void k_copy_normals(const NT *__restrict__ nin, int items,
