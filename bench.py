@@ -1,6 +1,6 @@
 """Benchmark of the whole OPC meshing + smoothing path on one MI355X.
 
-One step = one pass of the single-frame path (pl_smooth_frame, three
+One step = one pass of the single-frame path (pl_smooth_frame, two
 launches) over one 480x640 synthetic RGBD frame (floor, two walls, six boxes,
 8% NaN holes): mesh extraction (Alg. 1-2), 4 Laplacian sweeps (3x3,
 lambda = 1), triangle normals and centroids, 2 bilateral sweeps (3x3 quads,
@@ -121,10 +121,10 @@ def launch_model(kind, c, k):
         ops += F * c["lap_points"] * lap_lane_ops(k.kernel_lap)
         parts.append(f"laplacian x{F}")
     if kind & pl.PL_LAUNCH_MESH_COUNT:
-        nbytes += (0 if reads_pts else 12 * P) + Q + T
+        nbytes += (0 if reads_pts else 12 * P) + 3 * Q / 8 + T
         parts.append("mesh count")
     if kind & pl.PL_LAUNCH_MESH_EMIT:
-        nbytes += Q + 4 * T + 24 * nt
+        nbytes += 3 * Q / 8 + 4 * T + 24 * nt
         parts.append("mesh emit")
     if kind & pl.PL_LAUNCH_BILATERAL:
         if kind & pl.PL_LAUNCH_NORMALS:
@@ -213,7 +213,7 @@ def frame_kernel_name(kind, k):
     mesh = 1 if kind & pl.PL_LAUNCH_MESH_COUNT else 2 if kind & pl.PL_LAUNCH_MESH_EMIT else 0
     if kind & pl.PL_LAUNCH_BILATERAL:
         from_pts = "true" if kind & pl.PL_LAUNCH_NORMALS else "false"
-        # the gathering pass beside the emit ranks the triangles from the codes
+        # the gathering pass beside the emit ranks the triangles from the masks
         by_codes = "true" if (kind & pl.PL_LAUNCH_GATHER and kind & pl.PL_LAUNCH_MESH_EMIT) else "false"
         return f"void k_frame_bilateral<{k.kernel_bil // 2}, float, {from_pts}, {mesh}, {by_codes}>"
     return f"void k_frame_laplacian<{k.kernel_lap // 2}, {mesh}>"
@@ -358,8 +358,8 @@ def ga_bench(plans, stream, reps=200, level=4, stride=1):
 def user_halfedges_bench(plans, stream, reps=100):
     """Half-edges of a user mesh (Sec. 4.3) on each frame's T taken as a
     user-provided triangle list: per-call device time (graph replays) of the
-    partitioned way's five launches (bucket counts, their scan, the scatter
-    into bucket regions, the per-bucket LDS tables, the fallback check),
+    partitioned way's four launches (bucket counts, their scan, the scatter
+    into bucket regions, the per-bucket LDS tables),
     half-edges per second, and the oracle's rate (sort and binary searches,
     one thread) on the same triangles."""
     import numpy as np

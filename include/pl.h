@@ -116,7 +116,7 @@ pl_status pl_mesh_opc(const float *pts, int32_t M, int32_t N,
  * million quads, e.g. 2000 x 4096); larger frames get PL_ERR_SHAPE and
  * nothing is enqueued.  The call allocates nothing and writes no memory the
  * caller did not pass except that array; nothing in it needs clearing (every
- * code and count a call reads, the same call writes first).
+ * mask and count a call reads, the same call writes first).
  * Calls that overlap in time on one GPU (on different streams, or from
  * different threads) share the array and race: order them on one stream.
  * `stream` must belong to a device in 0..63.
@@ -506,7 +506,7 @@ pl_status pl_batch_replay_bounded(pl_batch batch, int32_t n_active, hipStream_t 
  *            the caller, 16-byte aligned, sized as listed there.
  * ndt        storage type of the normals.
  * ws         pl_smooth_frame_workspace(frame, ndt) bytes of device memory
- *            (codes and counts of the mesh, ping-pong buffers when a filter
+ *            (masks and counts of the mesh, ping-pong buffers when a filter
  *            takes more than one sweep); must not overlap the frame's
  *            buffers.  pl_smooth_frame_workspace returns 0 for an invalid
  *            frame.

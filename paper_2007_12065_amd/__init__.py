@@ -607,8 +607,8 @@ class FramePlan:
 
     def run_fused(self, pts: torch.Tensor, s=None) -> None:
         """The same outputs as run() (except the unfiltered normals, which
-        stay internal) through pl_smooth_frame: three to a few launches
-        instead of six."""
+        stay internal) through pl_smooth_frame: two to a few launches
+        instead of five or more."""
         f = self._fused_frame(pts)
         f.pts = pts.data_ptr()
         s = _stream(self.device) if s is None else s

@@ -634,6 +634,9 @@ constexpr float kBilUnderflow2 = 0x1p-120f;       // (2^-60)^2
 // 720 x 1280 frame takes 77.7 us at 8 (79.2 at 7), a 128 x 2048 one 80.8 us at
 // 8 (81.8 at 6 and 7); the batch, whose lanes hold four partial sums at 5x5,
 // 231.8 us at 6 (243.6 at 8), and its 3x3 kernels are the same at 6, 7 and 8.
+// What it costs: at 64 VGPRs every 3x3 and 5x5 single-frame kernel spills 5 to 7
+// (24 to 32 bytes of scratch a lane), at 80 the batch's 5x5 ones 2, its 7x7 and
+// 9x9 ones 52 and 101 (no sensor's window; a budget of their own not tried).
 constexpr int bil_waves_per_simd(int R, bool batch) { return batch || R > 2 ? 6 : 8; }
 constexpr float kBilShift = 48.f;                 // every weight is 2^(48 - e)
 constexpr int kBilMaxSweeps = 8;                  // fused sweeps per launch at most
@@ -1161,7 +1164,7 @@ __device__ __forceinline__ void bil_gather_ranks(const GatherCodes &gc, int Mq, 
 }
 
 // FromPts: the raw normals and centroids are not read but computed here from
-// the (smoothed) points `pts` exactly as normals_quad computes and stores
+// the (smoothed) points `pts` exactly as normals_block computes and stores
 // them (normals rounded to NT), and the tile's centroids are written to
 // `cen` -- the batched path's first pass, which then needs no normals
 // stage.  Otherwise nin / cen are the stored raw normals and centroids.

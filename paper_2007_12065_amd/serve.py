@@ -10,7 +10,7 @@ continuous batching on one GPU.
   device activity mask selecting the slots admitted since the previous step
   and replays a HIP graph of the whole pipeline captured with that mask.  A
   step of a single frame (a lightly loaded stream) instead runs the fused
-  single-frame entry (pl_smooth_frame) on that slot's buffers: three
+  single-frame entry (pl_smooth_frame) on that slot's buffers: a few
   launches sized for one frame, and the same output bits (the batched and
   single-frame paths agree bit for bit).
 * Continuous batching.  The next step is enqueued as soon as requests are
