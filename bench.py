@@ -395,8 +395,9 @@ def user_halfedges_bench(plans, stream, reps=100):
 
 def vertex_update_bench(plans, stream, reps=100, iterations=1):
     """Vertex update from the filtered normals (one sweep per call) on each
-    frame: per-launch device time (graph replays) of k_vertex_update, its algorithmic bytes (points
-    read and written once, the T_FC normals read once) and HBM fraction."""
+    frame: per-launch device time (graph replays) of its launch (by points, k_vertex_sweep,
+    for one sweep), its algorithmic bytes (points read and written once, the T_FC normals
+    read once) and HBM fraction."""
     import numpy as np
     import torch
 
@@ -412,7 +413,7 @@ def vertex_update_bench(plans, stream, reps=100, iterations=1):
                                            pl._stream(p.device)), "pl_vertex_update")
     us = graph_us([lambda i=i: call(i) for i in range(sets)])
     nbytes = 24 * M * N + 12 * 2 * (M - 1) * (N - 1)
-    return {"kernel": "k_vertex_update", "sweeps": iterations, "launch_us": round(us, 2),
+    return {"kernel": "k_vertex_sweep" if iterations == 1 else "k_vertex_update", "sweeps": iterations, "launch_us": round(us, 2),
             "parity": "unpinned: the paper cites this update (Sec. 2.3, Sec. 5.2) but prints no "
                       "formula; the oracle restates it and the kernel matches the oracle within "
                       "1e-5 relative",

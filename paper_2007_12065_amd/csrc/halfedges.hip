@@ -39,8 +39,8 @@
 // All of a thread's loads of a pass are issued before the first is used (eight
 // dependent rounds of memory latency were most of a pass before).  On 533 k
 // triangles in a buffer for 612 k, count / offsets / scatter / solve take
-// 5.1 / 4.4 / 15.2 / 22 us (8.2 / 6.0 / 22.9 / 30.0, and 4.7 for a launch that
-// looked for full tables, before), 46.6 us a call (68.1); streaming stores of
+// 4.9 / 4.9 / 12.8 / 20.2 us (8.2 / 6.0 / 22.9 / 30.0, and 4.7 for a launch that
+// looked for full tables, before), 43.7 us a call (68.1); streaming stores of
 // the twins: solve 47 us; 256 threads: 24 us.
 // Buckets: the power of two nearest above 3 cap / kHeBucketMean; a
 // bucket's keys are the top bits of the hash, its LDS slot the low bits.

@@ -19,7 +19,7 @@
 // themselves stay in its registers, and a sweep reads the eight neighbouring
 // points from LDS and writes its two.  Every read of LDS saved counts: with
 // normals and flags in LDS as well, a point read 13 vectors and 4 bytes a
-// sweep, and five sweeps of a 480 x 640 frame took 19.2 us, now 11.9 us (28.2
+// sweep, and five sweeps of a 480 x 640 frame took 19.2 us, now 12.0 us (28.2
 // us as five launches of a thread per point).
 //
 // Which triangles count is a matter of the sweep: a point that turns NaN in one
